@@ -30,6 +30,30 @@ struct TrainArgs {
     int slot_lo, slot_hi; // positions of `order` this launch covers
 };
 
+// Which literal word register slot r of a lane holds.  With an even number of slots, slots 2k and 2k + 1 hold
+// the plain and the negated literals of feature word 64 k + lane: one word of the example then serves both slots
+// (half the registers and loads for the rows), the sign of a slot is known at compile time, and the entries
+// of the evaluation list come out of one lane.  With an odd number (1 or 3) the literal words follow one
+// another, lw = 64 r + lane, which wastes no lanes where a clause has few of them.
+// What bounds a wide clause is the register file, i.e. how many wavefronts a SIMD holds to hide the latency
+// of each other's multiplies, LDS trips and scalar loads.  With paired slots and the planes of a slot finished in
+// its turn (see the feedback loop) 10 slots take 161 instead of 235 registers (three wavefronts per SIMD instead
+// of two) and 20 slots 256 instead of 462 (two instead of one).  Measured: a batch of 3,328 documents on 20,000
+// clauses of 10,000 features 45.2 -> 32.2 ms, 832 examples on 16,384 clauses of 20,000 features 50.8 -> 28.2 ms.
+template <int WPL>
+struct SlotMap {
+    static constexpr bool PAIRED = WPL % 2 == 0;
+    static constexpr int NX = PAIRED ? WPL / 2 : WPL; // words of an example row per lane
+    static __device__ __forceinline__ bool held(int r, int lane, int Wf)
+    {
+        return PAIRED ? (r / 2) * 64 + lane < Wf : r * 64 + lane < 2 * Wf;
+    }
+    static __device__ __forceinline__ int word(int r, int lane, int Wf) // literal word of the slot
+    {
+        return PAIRED ? (r / 2) * 64 + lane + (r & 1) * Wf : r * 64 + lane;
+    }
+};
+
 constexpr int EVAL_PAD = 16; // empty entries after the list: a group may read that far past its end
 
 // The clause as the evaluation loop wants it: one entry per feature word whose
@@ -41,18 +65,8 @@ template <int WPL>
 __device__ __forceinline__ int build_entries(const u32x8 (&p)[WPL], uint32_t *lmask, uint32_t *eoff,
                                              uint2 *emask, int lane, int Wf, int W, uint32_t row_bytes)
 {
-#pragma unroll
-    for (int r = 0; r < WPL; ++r) {
-        const int lw = r * 64 + lane;
-        if (lw < W) lmask[lw] = p[r][7];
-    }
-    wave_lds_sync();
     int n = 0;
-    for (int f0 = 0; f0 < Wf; f0 += 64) {
-        const int fw = f0 + lane;
-        const bool ok = fw < Wf;
-        const uint32_t mp = ok ? lmask[fw] : 0u;
-        const uint32_t mn = ok ? lmask[Wf + fw] : 0u;
+    auto append = [&](int fw, uint32_t mp, uint32_t mn) {
         const bool nzf = (mp | mn) != 0u;
         const uint64_t b = ballot(nzf);
         const int pre = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
@@ -61,6 +75,22 @@ __device__ __forceinline__ int build_entries(const u32x8 (&p)[WPL], uint32_t *lm
             emask[n + pre] = make_uint2(mp, mn);
         }
         n += __builtin_popcountll(b);
+    };
+    if constexpr (SlotMap<WPL>::PAIRED) { // both masks of a feature word sit in one lane (0 where the lane holds no word)
+#pragma unroll
+        for (int k = 0; k < WPL / 2; ++k) append(k * 64 + lane, p[2 * k][7], p[2 * k + 1][7]);
+    } else {
+#pragma unroll
+        for (int r = 0; r < WPL; ++r) {
+            const int lw = r * 64 + lane;
+            if (lw < W) lmask[lw] = p[r][7];
+        }
+        wave_lds_sync();
+        for (int f0 = 0; f0 < Wf; f0 += 64) {
+            const int fw = f0 + lane;
+            const bool ok = fw < Wf;
+            append(fw, ok ? lmask[fw] : 0u, ok ? lmask[Wf + fw] : 0u);
+        }
     }
     if (lane < EVAL_PAD) {
         eoff[n + lane] = 0u;
@@ -117,11 +147,11 @@ constexpr int SWEEP_WORDS = 2; // words of 32 examples per lane and pass of a sw
 // bit with ballots, a loop-free wave sum.  (An atomic add on one LDS word would do, but the
 // compiler expands it into a 64-step scalar loop over the lanes.)
 template <int WPL>
-__device__ __forceinline__ int count_literals(const u32x8 (&p)[WPL], int lane, int W)
+__device__ __forceinline__ int count_literals(const u32x8 (&p)[WPL])
 {
     uint32_t cnt = 0;
 #pragma unroll
-    for (int r = 0; r < WPL; ++r) cnt += (r * 64 + lane < W) ? (uint32_t)__builtin_popcount(p[r][7]) : 0u;
+    for (int r = 0; r < WPL; ++r) cnt += (uint32_t)__builtin_popcount(p[r][7]); // 0 where a lane holds no word
     int total = 0;
 #pragma unroll
     for (int bit = 0; bit < 8; ++bit) // cnt <= 32 * WPL <= 128 for the narrow clauses this is used for
@@ -135,14 +165,14 @@ __device__ __forceinline__ int count_literals(const u32x8 (&p)[WPL], int lane, i
 // The order of the list does not matter (the output is their conjunction): literals are
 // taken bit position by bit position, each position compacted over the lanes by ballot.
 template <int WPL>
-__device__ __forceinline__ int build_literals(const u32x8 (&p)[WPL], uint32_t *llist, int lane, int Wf, int W, int o,
+__device__ __forceinline__ int build_literals(const u32x8 (&p)[WPL], uint32_t *llist, int lane, int Wf, int o,
                                               uint32_t xb_row_bytes)
 {
     int base = 0;
 #pragma unroll
     for (int r = 0; r < WPL; ++r) {
-        const int lw = r * 64 + lane;
-        const uint32_t m = lw < W ? p[r][7] : 0u;
+        const int lw = SlotMap<WPL>::word(r, lane, Wf);
+        const uint32_t m = p[r][7]; // 0 where the lane holds no word
         if (ballot(m != 0u) == 0) continue;
         const uint32_t k0 = lw >= Wf ? (uint32_t)o + (uint32_t)(lw - Wf) * 32u : (uint32_t)lw * 32u; // literal of bit 0
         for (int b = 0; b < 32; ++b) {
@@ -198,17 +228,17 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
     u32x8 p[WPL];
 #pragma unroll
     for (int r = 0; r < WPL; ++r) {
-        const int lw = r * 64 + lane;
+        const int lw = SlotMap<WPL>::word(r, lane, d.Wf);
         u32x8 t = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
-        if (lw < d.W) t[7] = a.inc[(int64_t)g * d.W + lw];
+        if (SlotMap<WPL>::held(r, lane, d.Wf)) t[7] = a.inc[(int64_t)g * d.W + lw];
         p[r] = t;
     }
     bool have_planes = false;
     auto load_planes = [&]() {
 #pragma unroll
         for (int r = 0; r < WPL; ++r) {
-            const int lw = r * 64 + lane;
-            if (lw < d.W) {
+            const int lw = SlotMap<WPL>::word(r, lane, d.Wf);
+            if (SlotMap<WPL>::held(r, lane, d.Wf)) {
                 const uint4 *src = reinterpret_cast<const uint4 *>(a.planes + ((int64_t)g * d.W + lw) * 8);
                 const uint4 v0 = src[0], v1 = src[1];
                 u32x8 t;
@@ -399,8 +429,8 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
         // clauses (their registers hold the automata) and untrained ones (hundreds of literals).
         if (WPL <= 4 && n_blocks >= (n_listed < 0 ? 8 : 3)) {
             if (n_listed < 0) {
-                n_listed = count_literals<WPL>(p, lane, d.W);
-                if (n_listed <= TRAIN_LIT_MAX) build_literals<WPL>(p, llist, lane, d.Wf, d.W, d.o, (uint32_t)a.QW * 4u);
+                n_listed = count_literals<WPL>(p);
+                if (n_listed <= TRAIN_LIT_MAX) build_literals<WPL>(p, llist, lane, d.Wf, d.o, (uint32_t)a.QW * 4u);
             }
             if (n_listed <= TRAIN_LIT_MAX) {
                 if (s1 < e1) sweep_listed(s1, e1);
@@ -434,19 +464,19 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
         if constexpr (REGR) return ent >= 0 ? a.y_regr[ent >> 1] : 0;
         else return 0;
     };
-    // Slot geometry held in registers for the widths whose register budget has room for it (two per slot):
-    // which bits of the slot's word are literals at all, and whether they are negated ones.
-    constexpr bool GEOM = WPL >= 6 && WPL <= 10;
-    uint32_t geom_valid[GEOM ? WPL : 1], geom_neg[GEOM ? WPL : 1];
-    if constexpr (GEOM) {
+    // Paired slots: which bits of a feature word exist (0 in lanes that hold no word), one register per pair.
+    constexpr bool PAIRED = SlotMap<WPL>::PAIRED;
+    constexpr int NX = SlotMap<WPL>::NX;
+    // With 20 slots the registers for that are not there: all pairs but the one that holds the last word are
+    // whole or empty, which is a scalar.
+    constexpr bool HOLD_VALID = PAIRED && WPL <= 16;
+    uint32_t word_valid[HOLD_VALID ? NX : 1];
+    const int last_pair = (d.Wf - 1) >> 6;
+    if constexpr (PAIRED) {
 #pragma unroll
-        for (int r = 0; r < WPL; ++r) {
-            const uint32_t lw = (uint32_t)(r * 64 + lane);
-            const bool act = lw < (uint32_t)d.W;
-            const bool neg = lw >= (uint32_t)d.Wf;
-            const uint32_t fw = neg ? lw - (uint32_t)d.Wf : lw;
-            geom_valid[r] = act ? (fw == (uint32_t)d.Wf - 1u ? d.tailmask : ~0u) : 0u;
-            geom_neg[r] = neg ? ~0u : 0u;
+        for (int k = 0; k < (HOLD_VALID ? NX : 1); ++k) {
+            const int fw = (HOLD_VALID ? k : last_pair) * 64 + lane;
+            word_valid[k] = fw < d.Wf ? (fw == d.Wf - 1 ? d.tailmask : ~0u) : 0u;
         }
     }
     int ent_cur = load_ent(k_lo);
@@ -497,19 +527,23 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
         // words of a fired example in lane = literal-word layout.  Slot geometry (which half,
         // which bits exist) is recomputed from a laundered index wherever it is needed: it is
         // example-independent, and the compiler would otherwise keep it in VGPRs for every slot.
-        auto load_row = [&](int ii, uint32_t (&dst)[WPL]) {
+        auto load_row = [&](int ii, uint32_t (&dst)[NX]) {
             const uint32_t *xrow = X + (int64_t)ii * d.Wf;
 #pragma unroll
-            for (int r = 0; r < WPL; ++r) {
+            for (int r = 0; r < NX; ++r) {
                 uint32_t lw = (uint32_t)(r * 64 + lane);
                 asm volatile("" : "+v"(lw));
-                const bool act = lw < (uint32_t)d.W;
-                const uint32_t fw = act ? (lw >= (uint32_t)d.Wf ? lw - (uint32_t)d.Wf : lw) : 0u;
-                dst[r] = xrow[fw];
+                if constexpr (PAIRED) {
+                    dst[r] = xrow[min(lw, (uint32_t)d.Wf - 1u)];
+                } else {
+                    const bool act = lw < (uint32_t)d.W;
+                    const uint32_t fw = act ? (lw >= (uint32_t)d.Wf ? lw - (uint32_t)d.Wf : lw) : 0u;
+                    dst[r] = xrow[fw];
+                }
             }
         };
         // the row of the next fired example is requested while the current one is processed
-        uint32_t xnext[WPL];
+        uint32_t xnext[NX];
         if (fmask) load_row(__builtin_amdgcn_readlane(iv, __builtin_ctzll(fmask)), xnext);
 
         for (;;) {
@@ -558,52 +592,46 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
             // Type II feedback to a clause whose output is 0 changes nothing (Table 2): no automata needed
             if (LAZY && !have_planes && (tgt == pos || Cout)) load_planes();
             uint32_t changed = 0;
-            uint32_t xw[WPL];
+            uint32_t xw[NX];
 #pragma unroll
-            for (int r = 0; r < WPL; ++r) xw[r] = xnext[r];
+            for (int r = 0; r < NX; ++r) xw[r] = xnext[r];
             if (fmask) load_row(__builtin_amdgcn_readlane(iv, __builtin_ctzll(fmask)), xnext);
-            auto literal = [&](uint32_t lw, uint32_t x, uint32_t &valid) {
-                const bool act = lw < (uint32_t)d.W;
-                const bool neg = lw >= (uint32_t)d.Wf;
-                const uint32_t fw = neg ? lw - (uint32_t)d.Wf : lw;
-                valid = act ? (fw == (uint32_t)d.Wf - 1u ? d.tailmask : ~0u) : 0u;
-                return (x ^ (neg ? ~0u : 0u)) & valid; // 0 on padding bits and idle lanes
-            };
-            if (tgt != pos) {
-                // Type II feedback (Table 2): where the clause is 1 and the literal 0, push Exclude towards Include
-                if (Cout) {
-                    ++n_type2;
-#pragma unroll
-                    for (int r = 0; r < WPL; ++r) {
-                        uint32_t lw = (uint32_t)(r * 64 + lane);
-                        asm volatile("" : "+v"(lw));
-                        uint32_t valid;
-                        uint32_t lit;
-                        if constexpr (GEOM) {
-                            valid = geom_valid[r];
-                            lit = (xw[r] ^ geom_neg[r]) & valid;
-                        } else {
-                            lit = literal(lw, xw[r], valid);
-                        }
-                        uint32_t sp[8];
-                        get_slot(p[r], sp);
-                        const uint32_t old7 = sp[7];
-                        const uint32_t m = ~lit & ~old7 & valid; // excluded automata (below the top bit) cannot overflow
-                        ripple_inc(sp, m);
-                        changed |= sp[7] ^ old7;
-                        put_slot(p[r], sp);
+            auto literal = [&](int r, uint32_t lw, uint32_t &valid) { // 0 on padding bits and idle lanes
+                if constexpr (PAIRED) {
+                    if constexpr (HOLD_VALID) {
+                        valid = word_valid[r / 2];
+                    } else {
+                        const int k = r / 2;
+                        valid = (word_valid[0] & (k == last_pair ? ~0u : 0u)) | (k < last_pair ? ~0u : 0u);
                     }
+                    return ((r & 1) ? ~xw[r / 2] : xw[r / 2]) & valid;
+                } else {
+                    const bool act = lw < (uint32_t)d.W;
+                    const bool neg = lw >= (uint32_t)d.Wf;
+                    const uint32_t fw = neg ? lw - (uint32_t)d.Wf : lw;
+                    valid = act ? (fw == (uint32_t)d.Wf - 1u ? d.tailmask : ~0u) : 0u;
+                    return (xw[r] ^ (neg ? ~0u : 0u)) & valid;
                 }
-            } else {
-                // Type I feedback (Table 1)
-                ++n_type1;
+            };
+            const bool type1 = tgt == pos;
+            if (!type1 && !Cout) continue; // Type II feedback to a clause whose output is 0 changes nothing (Table 2)
+            if (type1) ++n_type1;
+            else ++n_type2;
+            {
 #pragma unroll
                 for (int r = 0; r < WPL; ++r) {
+                    uint32_t sp[8];
+                    get_slot(p[r], sp);
+                    const uint32_t old7 = sp[7];
+                    uint32_t up, wk; // the automata that move towards Include and towards Exclude (disjoint)
                     // The literal-word index is laundered through an empty asm so that the
                     // compiler does not hoist the example-independent first Philox round of
                     // every slot and block out of the example loop (dozens of live VGPRs per slot).
-                    uint32_t lw = (uint32_t)(r * 64 + lane);
+                    uint32_t lw = (uint32_t)SlotMap<WPL>::word(r, lane, d.Wf);
                     asm volatile("" : "+v"(lw));
+                    uint32_t valid;
+                    const uint32_t lit = literal(r, lw, valid);
+                    if (type1) { // Type I feedback (Table 1)
                     // bit-sliced comparison of 32 16-bit uniforms with thr, least significant bit first:
                     // ge = [u >= thr]; bit b of literal j's uniform is bit j of random word b;
                     // thr bit 1: ge &= w, thr bit 0: ge |= w, i.e. majority(w, ge, ~thr bit)
@@ -654,23 +682,21 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
                             }
                         }
                     }
-                    uint32_t valid;
-                    uint32_t lit;
-                    if constexpr (GEOM) {
-                        valid = geom_valid[r];
-                        lit = (xw[r] ^ geom_neg[r]) & valid;
-                    } else {
-                        lit = literal(lw, xw[r], valid);
-                    }
-                    uint32_t sp[8];
-                    get_slot(p[r], sp);
-                    const uint32_t old7 = sp[7];
-                    uint32_t up = 0u; // strong: literals that are 1 move towards Include with probability (s-1)/s (1 if boosted)
+                    up = 0u; // strong: literals that are 1 move towards Include with probability (s-1)/s (1 if boosted)
                     if (Cout) up = lit & (ge | d.boost) & ~at_value<FULL>(sp, a.sat.kmax, true);
                     // weak: everything else moves towards Exclude with probability 1/s
-                    const uint32_t wk = (Cout ? ~lit : ~0u) & ~ge & valid & ~at_value<FULL>(sp, a.sat.kmin, false);
-                    ripple_updown(sp, up, wk); // the two sets are disjoint: one pass over the planes moves both
+                    wk = (Cout ? ~lit : ~0u) & ~ge & valid & ~at_value<FULL>(sp, a.sat.kmin, false);
+                    } else { // Type II feedback (Table 2): where the clause is 1 and the literal 0, push Exclude towards Include
+                        up = ~lit & ~old7 & valid; // excluded automata (below the top bit) cannot overflow
+                        wk = 0u;
+                    }
+                    ripple_updown(sp, up, wk);
                     changed |= sp[7] ^ old7;
+                    // the planes are final here: without this the compiler moves the updates of all slots behind
+                    // the last slot's draw, and old planes, direction masks and carries of every slot stay in
+                    // registers until then
+                    asm volatile("" : "+v"(sp[0]), "+v"(sp[1]), "+v"(sp[2]), "+v"(sp[3]), "+v"(sp[4]), "+v"(sp[5]),
+                                 "+v"(sp[6]), "+v"(sp[7]), "+v"(changed));
                     put_slot(p[r], sp);
                     // keep the slots apart in the instruction schedule: interleaving them
                     // multiplies the live registers by the number of slots
@@ -694,8 +720,8 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
     if (!LAZY || have_planes) { // a gate fired: the automata may have moved
 #pragma unroll
         for (int r = 0; r < WPL; ++r) {
-            const int lw = r * 64 + lane;
-            if (lw < d.W) {
+            const int lw = SlotMap<WPL>::word(r, lane, d.Wf);
+            if (SlotMap<WPL>::held(r, lane, d.Wf)) {
                 uint4 *dst = reinterpret_cast<uint4 *>(a.planes + ((int64_t)g * d.W + lw) * 8);
                 const u32x8 t = p[r];
                 dst[0] = make_uint4(t[0], t[1], t[2], t[3]);
@@ -724,7 +750,7 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
 constexpr int TRAIN_EAGER_CANDIDATES = 256;
 
 template <int WPL, bool FULL, bool REGR, bool NARROW = false>
-__global__ __launch_bounds__(64 * TRAIN_WAVES_MAX) void k_train(const uint32_t *__restrict__ X, const uint32_t *__restrict__ XT,
+__global__ __launch_bounds__(64 * TRAIN_WAVES_MAX, WPL > 10 ? 2 : 1) void k_train(const uint32_t *__restrict__ X, const uint32_t *__restrict__ XT,
                                                             const uint32_t *__restrict__ XB,
                                                             const int32_t *__restrict__ gate,
                                                             const int32_t *__restrict__ ngate, const TrainArgs a)

@@ -275,6 +275,15 @@ def test_feedback_step_in_every_kernel_width(o, N, s, regression, device):
     gpu.close()
 
 
+# where the pairing of plain and negated literals in neighbouring register slots can go wrong: the last word of a
+# pair whole and the pair full (2048), one word alone in its pair (4097), the widest clause there is (20480)
+@pytest.mark.parametrize("o,N,s,regression", [(2048, 128, 10.0, False), (4097, 128, 2.0, False), (20480, 128, 5.0, False),
+                                              (4097, 100, 1.5, True)])
+def test_feedback_step_at_slot_pair_edges(o, N, s, regression, device):
+    test_feedback_step_in_every_kernel_width(o, N, s, regression, device)
+
+
+
 @pytest.mark.parametrize("s", [1.0, 2.0, 4.0, 3.9, 25.0])
 @pytest.mark.parametrize("N", [3, 100, 128])
 def test_feedback_saturation_and_threshold_paths(s, N, device):
