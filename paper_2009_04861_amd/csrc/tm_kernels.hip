@@ -476,6 +476,10 @@ int launch_train(tm_handle *h, const int32_t *vhat, int64_t i_begin, int64_t i_e
     a.lds_mask_words = (d.W + 3) & ~3;
     a.lds_off_words = (d.Wf + EVAL_PAD + 3) & ~3;
     a.lds_wave_words = a.lds_mask_words + a.lds_off_words + 2 * ((d.Wf + EVAL_PAD + 1) & ~1) + TRAIN_LIT_MAX + 8;
+    // at most 16 literal words: the version whose feedback events touch neither memory nor LDS lists (its
+    // comparison needs a threshold of 1 .. 65535; 0 and 65536, where nothing is drawn, keep to the general one)
+    const bool narrow = d.W <= 16 && d.thr != 0 && d.thr < 65536u;
+    if (narrow) a.lds_wave_words = 8 * 64 + TRAIN_LIT_MAX + 8; // the words of the open block and the list for the sweeps
     a.QW = (int)xb_row_words(h->q);
     const bool full = (d.N == 128);
     const int wpl = (d.W + 63) / 64;
@@ -502,9 +506,6 @@ int launch_train(tm_handle *h, const int32_t *vhat, int64_t i_begin, int64_t i_e
         TM_HIP(h, hipGetLastError());
         int rc = timing_mark(h, TIMED_TRAIN, true, st);
         if (rc) return rc;
-        // at most 16 literal words and a Type I comparison that needs several Philox blocks (the lowest set bit
-        // of the threshold lies below bit 12): the blocks are drawn side by side in the idle lanes
-        const bool narrow = d.W <= 16 && d.thr != 0 && __builtin_ctz(d.thr) < 12;
         if (wpl <= 1 && narrow) launch_train_t<1, true>(p, a, full, st);
         else if (wpl <= 1) launch_train_t<1>(p, a, full, st);
         else if (wpl <= 2) launch_train_t<2>(p, a, full, st);

@@ -40,16 +40,20 @@ struct TrainArgs {
 // its turn (see the feedback loop) 10 slots take 161 instead of 235 registers (three wavefronts per SIMD instead
 // of two) and 20 slots 256 instead of 462 (two instead of one).  Measured: a batch of 3,328 documents on 20,000
 // clauses of 10,000 features 45.2 -> 32.2 ms, 832 examples on 16,384 clauses of 20,000 features 50.8 -> 28.2 ms.
-template <int WPL>
+// Narrow clauses (at most 16 literal words, one slot): lane f holds the plain literals of feature word f, lane 8 + f
+// the negated ones, so that the masks of a feature word sit at fixed lanes.
+template <int WPL, bool NARROW = false>
 struct SlotMap {
     static constexpr bool PAIRED = WPL % 2 == 0;
     static constexpr int NX = PAIRED ? WPL / 2 : WPL; // words of an example row per lane
     static __device__ __forceinline__ bool held(int r, int lane, int Wf)
     {
+        if (NARROW) return lane < 16 && (lane & 7) < Wf;
         return PAIRED ? (r / 2) * 64 + lane < Wf : r * 64 + lane < 2 * Wf;
     }
     static __device__ __forceinline__ int word(int r, int lane, int Wf) // literal word of the slot
     {
+        if (NARROW) return (lane & 7) + (lane >> 3) * Wf;
         return PAIRED ? (r / 2) * 64 + lane + (r & 1) * Wf : r * 64 + lane;
     }
 };
@@ -164,14 +168,14 @@ __device__ __forceinline__ int count_literals(const u32x8 (&p)[WPL])
 // the number of included literals.  Only called for clauses with at most TRAIN_LIT_MAX.
 // The order of the list does not matter (the output is their conjunction): literals are
 // taken bit position by bit position, each position compacted over the lanes by ballot.
-template <int WPL>
+template <int WPL, bool NARROW>
 __device__ __forceinline__ int build_literals(const u32x8 (&p)[WPL], uint32_t *llist, int lane, int Wf, int o,
                                               uint32_t xb_row_bytes)
 {
     int base = 0;
 #pragma unroll
     for (int r = 0; r < WPL; ++r) {
-        const int lw = SlotMap<WPL>::word(r, lane, Wf);
+        const int lw = SlotMap<WPL, NARROW>::word(r, lane, Wf);
         const uint32_t m = p[r][7]; // 0 where the lane holds no word
         if (ballot(m != 0u) == 0) continue;
         const uint32_t k0 = lw >= Wf ? (uint32_t)o + (uint32_t)(lw - Wf) * 32u : (uint32_t)lw * 32u; // literal of bit 0
@@ -206,6 +210,7 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
                                              const int k_hi, const TrainArgs &a, uint32_t *lds, const int g,
                                              const int lane, const int wave)
 {
+    using Map = SlotMap<WPL, NARROW>;
     const Dims &d = a.d;
     uint32_t *lmask = lds + wave * a.lds_wave_words;        // [W] include masks, literal-word order
     uint32_t *eoff = lmask + a.lds_mask_words;              // [Wf + EVAL_PAD] (rounded to 4 words)
@@ -228,17 +233,17 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
     u32x8 p[WPL];
 #pragma unroll
     for (int r = 0; r < WPL; ++r) {
-        const int lw = SlotMap<WPL>::word(r, lane, d.Wf);
+        const int lw = Map::word(r, lane, d.Wf);
         u32x8 t = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
-        if (SlotMap<WPL>::held(r, lane, d.Wf)) t[7] = a.inc[(int64_t)g * d.W + lw];
+        if (Map::held(r, lane, d.Wf)) t[7] = a.inc[(int64_t)g * d.W + lw];
         p[r] = t;
     }
     bool have_planes = false;
     auto load_planes = [&]() {
 #pragma unroll
         for (int r = 0; r < WPL; ++r) {
-            const int lw = SlotMap<WPL>::word(r, lane, d.Wf);
-            if (SlotMap<WPL>::held(r, lane, d.Wf)) {
+            const int lw = Map::word(r, lane, d.Wf);
+            if (Map::held(r, lane, d.Wf)) {
                 const uint4 *src = reinterpret_cast<const uint4 *>(a.planes + ((int64_t)g * d.W + lw) * 8);
                 const uint4 v0 = src[0], v1 = src[1];
                 u32x8 t;
@@ -250,20 +255,114 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
         have_planes = true;
     };
     if (!LAZY) load_planes();
-    int nent = build_entries<WPL>(p, lmask, eoff, emask, lane, d.Wf, d.W, row_bytes);
+    int nent = 0;
+    if constexpr (!NARROW) nent = build_entries<WPL>(p, lmask, eoff, emask, lane, d.Wf, d.W, row_bytes);
+
+    // Narrow clauses.  An epoch of so small a machine is the chain of one clause's feedback events and block
+    // changes, and costs their latency and nothing else.  So the words of the open block of 64 examples stay in
+    // registers (lane = example, at most eight words), the next block's are requested a block ahead, and an event
+    // touches neither LDS lists nor memory.  Measured per epoch: noisy XOR (20 clauses of 2 literal words, 5,000
+    // examples) 1.27 -> 1.00 ms, regression (1,280 clauses of 16 words, 13,911 examples) 0.673 -> 0.657 ms.
+    uint32_t bw[NARROW ? 8 : 1] = {}, bw_next[NARROW ? 8 : 1] = {}, os_next0 = 0u, os_next1 = 0u;
+    int block_next = -1; // block that bw_next holds
+    auto narrow_load = [&](int b, uint32_t (&dst)[NARROW ? 8 : 1]) {
+        if constexpr (NARROW) {
+#pragma unroll
+            for (int f = 0; f < 8; ++f)
+                dst[f] = XT[(uint32_t)min(f, d.Wf - 1) * (uint32_t)a.qp + (uint32_t)(b << 6) + (uint32_t)lane];
+        }
+    };
+    auto narrow_eval = [&](const uint32_t (&x)[NARROW ? 8 : 1]) { // outputs of the clause on the block held in x
+        uint32_t viol = 0u;
+        if constexpr (NARROW) {
+            const uint32_t m7 = p[0][7];
+            auto word = [&](int f) { viol |= bitselect(x[f], readlane(m7, 8 + f), readlane(m7, f)); };
+            word(0);
+            if (d.Wf > 1) {
+                word(1);
+                if (d.Wf > 2) { // masks beyond the last word are 0
+                    word(2);
+                    word(3);
+                    if (d.Wf > 4) {
+#pragma unroll
+                        for (int f = 4; f < 8; ++f) word(f);
+                    }
+                }
+            }
+        }
+        return ballot(viol == 0u);
+    };
+    auto narrow_keep = [&]() { // more than two words: the block also goes to LDS, from where an event takes its row
+        if constexpr (NARROW) {
+            if (d.Wf > 2) {
+#pragma unroll
+                for (int f = 0; f < 8; ++f) lmask[f * 64 + lane] = bw[f];
+                wave_lds_sync();
+            }
+        }
+    };
+    auto narrow_row = [&](int bl) { // word lane & 7 of example bl of the open block
+        uint32_t v = 0u;
+        if constexpr (NARROW) {
+            if (d.Wf > 2) {
+                v = lmask[(lane & 7) * 64 + bl];
+            } else {
+                const uint32_t v0 = readlane(bw[0], bl), v1 = readlane(bw[1], bl);
+                v = (lane & 7) == 0 ? v0 : v1;
+            }
+        }
+        return v;
+    };
 
     // lowest Philox block of the Type I comparator that can matter: bits of the
     // uniform below the lowest set bit of thr never decide u < thr
     const int tz = d.thr ? __builtin_ctz(d.thr) : 16;
     const int first_blk = min(tz >> 2, 4);
     const uint32_t ge_init = d.thr >= 65536u ? 0u : ~0u;
-    // NARROW (chosen by the host for clauses of at most 16 literal words whose comparison needs more
-    // than one Philox block): such clauses leave three quarters of the lanes idle while the 16 word lanes
-    // draw up to four blocks each, one after the other, and an epoch of so small a machine costs the
-    // latency of its feedback events and nothing else.  Here lane 16 t + w draws block t of word w (one
-    // Philox call for all of them) and the word lanes collect the four partial comparisons.  A version of
-    // its own because the extra registers would cost the general one-slot kernel a wavefront per SIMD.
-    const uint32_t thr_nibble_n = NARROW ? ~(d.thr >> (4 * (lane >> 4))) : 0u; // complement of the four thr bits of this lane's block
+    // Narrow clauses leave most lanes idle while their word lanes draw up to four blocks each, one after the
+    // other, for every Type I event.  Their draws depend on nothing but the example, so they are made ahead and
+    // side by side: lane = (event, block t, half h, feature word f), with the words of a half rounded up to wp = 1, 2, 4
+    // or 8, i.e. 8 / wp events per Philox call.  The four partial
+    // comparisons of a word are folded at once for all events; an event takes its lanes with one shuffle.
+    const int wps = d.Wf <= 1 ? 0 : d.Wf <= 2 ? 1 : d.Wf <= 4 ? 2 : 3; // wp = 1 << wps
+    const int dr_f = lane & ((1 << wps) - 1), dr_h = (lane >> wps) & 1, dr_t = (lane >> (wps + 1)) & 3, dr_e = lane >> (wps + 3);
+    const uint32_t thr_nibble_n = NARROW ? ~(d.thr >> (4 * dr_t)) : 0u; // complement of the four thr bits of this lane's block
+    const uint32_t dr_ctr = 4u * (uint32_t)(dr_f + dr_h * d.Wf) + (uint32_t)dr_t;
+    const int dr_src = ((lane >> 3) & 1) * (1 << wps) + (lane & ((1 << wps) - 1)); // draw lane (event 0) of this state lane
+    uint32_t ge_ahead = 0u;
+    int n_ahead = 0; // events drawn ahead and not used yet; they are consecutive Type I events of the round
+    auto narrow_draw = [&](uint64_t t1, int iv) { // t1: Type I events of the round still to come, iv: example of each gate lane
+        if constexpr (NARROW) {
+            const int per_call = 8 >> wps;
+            uint32_t ii = 0u;
+            for (n_ahead = 0; n_ahead < per_call && t1; ++n_ahead) {
+                const uint32_t id = readlane((uint32_t)iv, __builtin_ctzll(t1));
+                t1 &= t1 - 1;
+                ii = dr_e == n_ahead ? id : ii;
+            }
+            // Over the four planes of one block the comparison is "the value that went in if the four bits
+            // equal those of thr, else decided": two runs of the chain, from 0 and from 1, give what is
+            // decided (d0) and where the input passes (d0 ^ d1).
+            const U4 R = draw(d.key, STREAM_TYPE1, dr_ctr, (uint32_t)g, (uint64_t)ii, a.epoch);
+            const uint32_t w[4] = {R.x, R.y, R.z, R.w};
+            uint32_t d0 = 0u, d1 = ~0u;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t K = (uint32_t)__builtin_amdgcn_sbfe((int)thr_nibble_n, j, 1); // thr bit 1: 0, 0: ~0
+                d0 = majority3(w[j], d0, K);
+                d1 = majority3(w[j], d1, K);
+            }
+            const uint32_t pass = d0 ^ d1;
+            ge_ahead = ge_init;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) { // least significant block first
+                const int src = (lane & ~(3 << (wps + 1))) | (t << (wps + 1));
+                const uint32_t dt = (uint32_t)__shfl((int)d0, src, 64), pt = (uint32_t)__shfl((int)pass, src, 64);
+                ge_ahead = dt | (pt & ge_ahead);
+            }
+        }
+    };
+    int n_used = 0; // of the events drawn ahead
 
     // per-wavefront event counts of one launch fit 32 bits (at most 2^30 examples per launch)
     uint32_t n_fired = 0, n_type1 = 0, n_changes = 0, n_type2 = 0, n_eval = 0, n_draw = 0, n_listed_blocks = 0;
@@ -322,9 +421,28 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
             n_changes += __builtin_popcountll(diff);
         }
     };
+    // Narrow clauses: the refresh of a closed block is held back until the next gate entries have arrived.  Loads
+    // and atomics of a wavefront complete in order, and where all clauses correct the same few tallies at the same
+    // time an atomic takes microseconds: a load issued behind it would wait for it.
+    int held_block = -1;
+    uint64_t held_ob = 0, held_os = 0, held_rm = 0;
+    auto refresh_held = [&]() {
+        if (NARROW && held_block >= 0) {
+            refresh_block(held_block, held_ob, held_os, held_rm);
+            held_block = -1;
+        }
+    };
     // ... followed by the bookkeeping of which stored outputs may be outdated
     auto close_block = [&](int b, uint64_t ob, uint64_t os, uint64_t rm, bool changed) {
-        refresh_block(b, ob, os, rm);
+        if constexpr (NARROW) {
+            refresh_held();
+            held_block = b;
+            held_ob = ob;
+            held_os = os;
+            held_rm = rm;
+        } else {
+            refresh_block(b, ob, os, rm);
+        }
         const int b0 = b << 6, b1 = b0 + 64;
         const bool whole = b0 >= i_begin && (b1 <= i_end || i_end == q);
         if (whole) { // this block is up to date again
@@ -430,7 +548,7 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
         if (WPL <= 4 && n_blocks >= (n_listed < 0 ? 8 : 3)) {
             if (n_listed < 0) {
                 n_listed = count_literals<WPL>(p);
-                if (n_listed <= TRAIN_LIT_MAX) build_literals<WPL>(p, llist, lane, d.Wf, d.o, (uint32_t)a.QW * 4u);
+                if (n_listed <= TRAIN_LIT_MAX) build_literals<WPL, NARROW>(p, llist, lane, d.Wf, d.o, (uint32_t)a.QW * 4u);
             }
             if (n_listed <= TRAIN_LIT_MAX) {
                 if (s1 < e1) sweep_listed(s1, e1);
@@ -441,7 +559,14 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
         for (int b = next_stale(from); b < to; b = next_stale(b + 1)) { // closing b does not change which later blocks are outdated
             const uint32_t *op = ostar_row + (b << 1);
             const uint32_t o0 = op[0], o1 = op[1];
-            const uint64_t ob = eval64(eoff, emask, nent, XT + (b << 6), lane);
+            uint64_t ob;
+            if constexpr (NARROW) {
+                uint32_t x[8];
+                narrow_load(b, x);
+                ob = narrow_eval(x);
+            } else {
+                ob = eval64(eoff, emask, nent, XT + (b << 6), lane);
+            }
             close_block(b, ob, pack64(o0, o1), range_mask(b << 6), false);
             ++n_eval;
         }
@@ -472,6 +597,7 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
     constexpr bool HOLD_VALID = PAIRED && WPL <= 16;
     uint32_t word_valid[HOLD_VALID ? NX : 1];
     const int last_pair = (d.Wf - 1) >> 6;
+    const uint32_t narrow_valid = Map::held(0, lane, d.Wf) ? ((lane & 7) == d.Wf - 1 ? d.tailmask : ~0u) : 0u;
     if constexpr (PAIRED) {
 #pragma unroll
         for (int k = 0; k < (HOLD_VALID ? NX : 1); ++k) {
@@ -494,6 +620,11 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
             v_cur = load_v(ent_cur);
             y_cur = load_y(ent_cur);
             ent_nxt = load_ent(k0 + 128);
+            if constexpr (NARROW) { // everything requested so far arrives here, ahead of the atomics
+                asm volatile("" : "+v"(bw_next[0]), "+v"(bw_next[1]), "+v"(bw_next[2]), "+v"(bw_next[3]), "+v"(bw_next[4]),
+                             "+v"(bw_next[5]), "+v"(bw_next[6]), "+v"(bw_next[7]), "+v"(os_next0), "+v"(os_next1));
+            }
+            refresh_held();
             const bool valid = ent >= 0;
             iv = ent >> 1;
             bool target = (ent & 1) != 0;
@@ -544,7 +675,8 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
         };
         // the row of the next fired example is requested while the current one is processed
         uint32_t xnext[NX];
-        if (fmask) load_row(__builtin_amdgcn_readlane(iv, __builtin_ctzll(fmask)), xnext);
+        if (!NARROW && fmask) load_row(__builtin_amdgcn_readlane(iv, __builtin_ctzll(fmask)), xnext);
+        n_ahead = n_used = 0;
 
         for (;;) {
             // next event: a fired candidate, or (after the last candidate) the end of the range
@@ -563,6 +695,16 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
 
             // bring block B up: close the open block, refresh the outdated blocks in between
             if (cb != B) {
+                uint32_t os_b0 = 0u, os_b1 = 0u;
+                const bool ahead = NARROW && B == block_next;
+                if constexpr (NARROW) {
+                    if (ahead) {
+#pragma unroll
+                        for (int f = 0; f < 8; ++f) bw[f] = bw_next[f];
+                        os_b0 = os_next0;
+                        os_b1 = os_next1;
+                    }
+                }
                 if (cb >= 0) {
                     close_block(cb, obits, ost, rmask, mask_changed);
                     next_block = cb + 1;
@@ -575,11 +717,29 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
                     // open block B: previous outputs, range mask, evaluation with the current masks
                     cb = B;
                     const int b0 = B << 6;
-                    const uint32_t *op = a.ostar + (int64_t)g * a.Qw + (b0 >> 5);
-                    const uint32_t o0 = op[0], o1 = op[1];
                     rmask = range_mask(b0);
-                    obits = eval64(eoff, emask, nent, XT + b0, lane);
-                    ost = pack64(o0, o1);
+                    if constexpr (NARROW) {
+                        if (!ahead) {
+                            narrow_load(B, bw);
+                            os_b0 = ostar_row[B << 1];
+                            os_b1 = ostar_row[(B << 1) + 1];
+                        }
+                        narrow_keep();
+                        obits = narrow_eval(bw);
+                        ost = pack64(os_b0, os_b1);
+                        block_next = -1;
+                        if (B + 1 < end_block) { // nothing but the wavefront itself writes the stored outputs, and those of a
+                            block_next = B + 1;  // later block only when it gets there
+                            narrow_load(B + 1, bw_next);
+                            os_next0 = ostar_row[(B << 1) + 2];
+                            os_next1 = ostar_row[(B << 1) + 3];
+                        }
+                    } else {
+                        const uint32_t *op = a.ostar + (int64_t)g * a.Qw + (b0 >> 5);
+                        const uint32_t o0 = op[0], o1 = op[1];
+                        obits = eval64(eoff, emask, nent, XT + b0, lane);
+                        ost = pack64(o0, o1);
+                    }
                     mask_changed = false;
                     ++n_eval;
                 }
@@ -594,10 +754,13 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
             uint32_t changed = 0;
             uint32_t xw[NX];
 #pragma unroll
-            for (int r = 0; r < NX; ++r) xw[r] = xnext[r];
-            if (fmask) load_row(__builtin_amdgcn_readlane(iv, __builtin_ctzll(fmask)), xnext);
+            for (int r = 0; r < NX; ++r) xw[r] = NARROW ? 0u : xnext[r];
+            if (!NARROW && fmask) load_row(__builtin_amdgcn_readlane(iv, __builtin_ctzll(fmask)), xnext);
             auto literal = [&](int r, uint32_t lw, uint32_t &valid) { // 0 on padding bits and idle lanes
-                if constexpr (PAIRED) {
+                if constexpr (NARROW) {
+                    valid = narrow_valid;
+                    return (xw[0] ^ (lane & 8 ? ~0u : 0u)) & valid;
+                } else if constexpr (PAIRED) {
                     if constexpr (HOLD_VALID) {
                         valid = word_valid[r / 2];
                     } else {
@@ -617,6 +780,13 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
             if (!type1 && !Cout) continue; // Type II feedback to a clause whose output is 0 changes nothing (Table 2)
             if (type1) ++n_type1;
             else ++n_type2;
+            if constexpr (NARROW) {
+                xw[0] = narrow_row(bl);
+                if (type1 && n_used == n_ahead) {
+                    narrow_draw((fmask | (1ull << l)) & (pos ? tmask : ~tmask), iv);
+                    n_used = 0;
+                }
+            }
             {
 #pragma unroll
                 for (int r = 0; r < WPL; ++r) {
@@ -627,7 +797,7 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
                     // The literal-word index is laundered through an empty asm so that the
                     // compiler does not hoist the example-independent first Philox round of
                     // every slot and block out of the example loop (dozens of live VGPRs per slot).
-                    uint32_t lw = (uint32_t)SlotMap<WPL>::word(r, lane, d.Wf);
+                    uint32_t lw = (uint32_t)Map::word(r, lane, d.Wf);
                     asm volatile("" : "+v"(lw));
                     uint32_t valid;
                     const uint32_t lit = literal(r, lw, valid);
@@ -640,26 +810,8 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
                     uint32_t thr = d.thr;
                     if (WPL <= 2) asm volatile("" : "+s"(key.seed_lo), "+s"(key.seed_hi), "+s"(thr));
                     if constexpr (NARROW) {
-                        // Over the four planes of one block the comparison is "the value that went in if
-                        // the four bits equal those of thr, else decided": two runs of the chain, from 0
-                        // and from 1, give what is decided (d0) and where the input passes (d0 ^ d1).
-                        const U4 R = draw(key, STREAM_TYPE1, 4u * (uint32_t)(lane & 15) + (uint32_t)(lane >> 4), (uint32_t)g,
-                                          (uint64_t)(uint32_t)ii, a.epoch);
-                        const uint32_t w[4] = {R.x, R.y, R.z, R.w};
-                        uint32_t d0 = 0u, d1 = ~0u;
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) {
-                            const uint32_t K = (uint32_t)__builtin_amdgcn_sbfe((int)thr_nibble_n, k, 1); // thr bit 1: 0, 0: ~0
-                            d0 = majority3(w[k], d0, K);
-                            d1 = majority3(w[k], d1, K);
-                        }
-                        const uint32_t pass = d0 ^ d1;
-#pragma unroll
-                        for (int t = 0; t < 4; ++t) { // least significant block first; lanes 16.. compute nothing that is used
-                            const int src = (lane & 15) + 16 * t;
-                            const uint32_t dt = (uint32_t)__shfl((int)d0, src, 64), pt = (uint32_t)__shfl((int)pass, src, 64);
-                            ge = dt | (pt & ge);
-                        }
+                        ge = (uint32_t)__shfl((int)ge_ahead, dr_src + (n_used << (wps + 3)), 64);
+                        ++n_used;
                     } else {
 #pragma unroll
                         for (int t = 0; t < 4; ++t) {
@@ -706,22 +858,28 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
             if (ballot(changed != 0u)) { // the conjunction changed: re-evaluate this and the later examples of the block
                 mask_changed = true;
                 n_listed = -1;
-                nent = build_entries<WPL>(p, lmask, eoff, emask, lane, d.Wf, d.W, row_bytes);
-                const uint64_t nb = eval64(eoff, emask, nent, XT + (cb << 6), lane);
+                uint64_t nb;
+                if constexpr (NARROW) {
+                    nb = narrow_eval(bw);
+                } else {
+                    nent = build_entries<WPL>(p, lmask, eoff, emask, lane, d.Wf, d.W, row_bytes);
+                    nb = eval64(eoff, emask, nent, XT + (cb << 6), lane);
+                }
                 const uint64_t keep = (1ull << bl) - 1ull;
                 obits = (obits & keep) | (nb & ~keep);
             }
         }
         if (last) break;
     }
+    refresh_held();
     if (plo >= phi) plo = phi = 0;
     if (lane == 0) *reinterpret_cast<int4 *>(a.fresh + (int64_t)g * 4) = make_int4(plo, phi, slo, 0);
 
     if (!LAZY || have_planes) { // a gate fired: the automata may have moved
 #pragma unroll
         for (int r = 0; r < WPL; ++r) {
-            const int lw = SlotMap<WPL>::word(r, lane, d.Wf);
-            if (SlotMap<WPL>::held(r, lane, d.Wf)) {
+            const int lw = Map::word(r, lane, d.Wf);
+            if (Map::held(r, lane, d.Wf)) {
                 uint4 *dst = reinterpret_cast<uint4 *>(a.planes + ((int64_t)g * d.W + lw) * 8);
                 const u32x8 t = p[r];
                 dst[0] = make_uint4(t[0], t[1], t[2], t[3]);

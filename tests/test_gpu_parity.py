@@ -283,6 +283,15 @@ def test_feedback_step_at_slot_pair_edges(o, N, s, regression, device):
     test_feedback_step_in_every_kernel_width(o, N, s, regression, device)
 
 
+# narrow clauses: every rounding of the words per half (1, 2, 3 -> 4, 5 -> 8, 8), one and several Philox blocks of the
+# threshold that matter, and the two thresholds (s = 1, s beyond 16 bits) that stay with the general version
+@pytest.mark.parametrize("o,N,s,regression", [(31, 128, 3.9, False), (64, 100, 2.0, False), (90, 128, 7.0, False), (129, 128, 1.5, True),
+                                              (160, 128, 3.9, False), (256, 64, 25.0, False), (256, 128, 1.0, False),
+                                              (40, 128, 200000.0, True)])
+def test_feedback_step_narrow_clauses(o, N, s, regression, device):
+    test_feedback_step_in_every_kernel_width(o, N, s, regression, device)
+
+
 
 @pytest.mark.parametrize("s", [1.0, 2.0, 4.0, 3.9, 25.0])
 @pytest.mark.parametrize("N", [3, 100, 128])
