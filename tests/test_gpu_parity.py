@@ -609,3 +609,33 @@ def test_error_codes(device):
     empty = torch.empty((0, 1), dtype=torch.int32, device=gpu.dev)
     assert gpu.class_sums(empty).shape == (0, 3)
     torch.cuda.synchronize()
+
+
+# calls of a few examples take a path of their own up to 32 of them: remainders of the groups of four examples and of
+# the shares of 32 clauses, more than 64 literal words, more classes than wavefronts, ties between classes
+@pytest.mark.parametrize("m,n,o,regression", [(2, 2, 12, False), (7, 34, 784, False), (3, 70, 4200, False), (1, 40, 90, True)])
+@pytest.mark.parametrize("q", [1, 2, 5, 32, 33])
+def test_predictions_of_few_examples(m, n, o, regression, q, device):
+    print("few examples", m, n, o, regression, q, flush=True)
+    rng = np.random.default_rng(o + q)
+    T = 5 if not regression else 30
+    ora = O.Oracle(m, n, o, 128, T, 3.0, 5, regression=regression)
+    gpu = B.TsetlinMachine(m, n, o, 128, T, 3.0, 5, regression=regression)
+    ora.state[:] = sparse_random_state(rng, ora.C, ora.L, 128, 2.0 / ora.L)
+    push_state(gpu, ora.state)
+    X = (rng.random((q, o)) < 0.5).astype(np.uint8)
+    Xd = dev_bits(gpu, X)
+    ws = torch.empty(B.tm_infer_ws_bytes(gpu.cfg, q), dtype=torch.uint8, device=gpu.dev)
+    sums = torch.full((q, m), -99, dtype=torch.int32, device=gpu.dev)
+    pred = torch.full((q,), -99, dtype=torch.int32, device=gpu.dev)
+    with torch.cuda.device(gpu.dev):
+        B.tm_predict_ws(gpu.h, Xd, pred, sums, ws)
+        assert np.array_equal(sums.cpu().numpy(), ora.class_sums(X))
+        assert np.array_equal(pred.cpu().numpy(), ora.predict(X))
+        sums.fill_(-99)
+        B.tm_class_sums_ws(gpu.h, Xd, sums, ws)
+        assert np.array_equal(sums.cpu().numpy(), ora.class_sums(X))
+        pred.fill_(-99)
+        B.tm_predict_static(gpu.h, Xd, pred)
+        assert np.array_equal(pred.cpu().numpy(), ora.predict(X))
+    gpu.close()
