@@ -57,6 +57,7 @@ struct Dims {
 #include "tm_kernels_util.hpp"
 #include "tm_kernels_prep.hpp"
 #include "tm_kernels_eval_masks.hpp"
+#include "tm_kernels_eval_bits.hpp"
 #include "tm_kernels_eval_lists.hpp"
 #include "tm_kernels_eval_few.hpp"
 #include "tm_kernels_train.hpp"
@@ -308,6 +309,25 @@ void launch_eval_resident(const EvalPtrs &p, const EvalArgs &a, dim3 grid, hipSt
         hipLaunchKernelGGL((k_eval_resident<CH, false, true>), grid, dim3(64), 0, st, p.inc, p.X, p.bits, p.acc, a);
 }
 
+template <int RW, int WF>
+int launch_eval_bits_t(tm_handle *h, const EvalPtrs &p, const EvalArgs &a, hipStream_t st)
+{
+    // one workgroup fits a CU by its LDS: about 256 of them, in up to four rounds so that the last is not
+    // left nearly empty; at least one clause per wavefront
+    const int64_t ranges = (a.q + RW * 32 - 1) / (RW * 32);
+    int64_t shares = 1;
+    for (int64_t rounds = 1; rounds <= 4; ++rounds) {
+        shares = std::max<int64_t>(1, 256 * rounds / ranges);
+        if (shares * ranges * 10 >= 256 * rounds * 9) break;
+    }
+    shares = std::min<int64_t>(shares, (a.C + BITS_WAVES - 1) / BITS_WAVES);
+    const int share = (int)((a.C + shares - 1) / shares);
+    hipLaunchKernelGGL((k_eval_bits<RW, WF>), dim3((unsigned)ranges, (unsigned)((a.C + share - 1) / share)),
+                       dim3(64 * BITS_WAVES), 0, st, p.inc, p.X, p.bits, a, share);
+    TM_HIP(h, hipGetLastError());
+    return TM_OK;
+}
+
 // Evaluation of all clauses on q examples; writes bits and/or accumulates sums.
 int launch_eval(tm_handle *h, const uint32_t *X, int64_t q, uint32_t *bits, int64_t bits_stride, int32_t *acc,
                 int64_t acc_si, int64_t acc_sc, hipStream_t st)
@@ -319,6 +339,17 @@ int launch_eval(tm_handle *h, const uint32_t *X, int64_t q, uint32_t *bits, int6
     a.q = q; a.Wf = d.Wf; a.W = d.W; a.C = d.C; a.n = d.n; a.m = d.m;
     a.posmask = d.regr ? ~0ull : 0xAAAAAAAAAAAAAAAAull;
     a.bits_stride = bits_stride; a.acc_si = acc_si; a.acc_sc = acc_sc;
+    // Outputs of the clauses from literal rows in LDS.  us with the lane = clause kernels / with the rows, 20 random
+    // literals per clause, 20,000 clauses: 784 features, 256 examples 46 / 22, 1,024 examples 70 / 24, 60,000 examples
+    // 1,375 / 477 (dense untrained clauses 1,381 / 689); 2,400 features, 10,000 examples 1,600 / 254.  Below 128 examples
+    // the transposition is most of it (64 examples 14 / 19, one 7 / 16); up to 16 feature words the few operations per
+    // example are as cheap (128 features, 10,000 examples 92 / 138; 256 features, 1,280 clauses 26 / 14 to 17); above
+    // 76 feature words the rows do not fit.
+    if (bits && !acc && q >= 128 && d.Wf > 16 && d.Wf <= 76) {
+        if (d.Wf <= 26) return launch_eval_bits_t<32, 26>(h, p, a, st);
+        if (d.Wf <= 38) return launch_eval_bits_t<32, 38>(h, p, a, st);
+        return launch_eval_bits_t<16, 76>(h, p, a, st);
+    }
     // a wavefront takes one tile of 64 clauses and a range of examples (a multiple of 256);
     // ranges are sized so that the launch has a few thousand wavefronts per XCD
     const int64_t tiles = (d.C + 63) / 64;

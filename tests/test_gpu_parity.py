@@ -639,3 +639,30 @@ def test_predictions_of_few_examples(m, n, o, regression, q, device):
         B.tm_predict_static(gpu.h, Xd, pred)
         assert np.array_equal(pred.cpu().numpy(), ora.predict(X))
     gpu.close()
+
+
+# clause outputs take the literal rows of a range of examples from LDS for 17 to 76 feature words and 128 examples or more: edges of the widths that
+# the kernel is compiled for, of its ranges of 1,024 (512) examples and of the words of 32, empty and dense clauses
+@pytest.mark.parametrize("o", [512, 513, 832, 833, 1216, 1217, 2432, 2433])
+@pytest.mark.parametrize("q", [127, 128, 512, 1057])
+def test_clause_outputs_over_widths(o, q, device):
+    print("clause outputs", o, q, flush=True)
+    rng = np.random.default_rng(o + q)
+    ora = O.Oracle(3, 38, o, 128, 9, 3.0, 5)
+    gpu = B.TsetlinMachine(3, 38, o, 128, 9, 3.0, 5)
+    X = (rng.random((q, o)) < 0.5).astype(np.uint8)
+    X[:, : o // 4], X[:, o // 4 : o // 3] = 0, 1  # literals that are true (or false) on every example
+    X[q // 2, 5] = 1                               # and one that is not, on a single example
+    lit = np.concatenate([X[0], 1 - X[0]])  # literals true for example 0
+    ora.state[:] = sparse_random_state(rng, ora.C, ora.L, 128, 2.0 / ora.L)
+    flat = ora.state.reshape(ora.C, ora.L)
+    flat[5] = np.where(lit, 129, 128)       # a whole example: true for its copies only
+    flat[6] = np.where(lit & (rng.random(ora.L) < 0.02), 129, 128)
+    flat[7] = 200                           # every literal: never true
+    flat[8] = 1                             # none: always true
+    X[q - 1] = X[0]
+    push_state(gpu, ora.state)
+    got = bits_to_u8(gpu.clause_outputs(dev_bits(gpu, X)), q)
+    assert np.array_equal(got, ora.clause_outputs(X).T)
+    assert got[5].any() and not got[7].any() and got[8].all()
+    gpu.close()
