@@ -384,7 +384,7 @@ struct TrainPtrs {
     const int32_t *gate, *ngate;
 };
 
-template <int WPL, bool NARROW = false>
+template <int WPL, bool ROOMY, bool NARROW = false>
 void launch_train_t(const TrainPtrs &p, const TrainArgs &a, bool full, hipStream_t st)
 {
     // Clauses (wavefronts) per workgroup; the wavefronts of a workgroup do not interact.  Two are best once
@@ -396,10 +396,10 @@ void launch_train_t(const TrainPtrs &p, const TrainArgs &a, bool full, hipStream
     const size_t lds = (size_t)a.lds_wave_words * tw * 4;
     const dim3 grid((unsigned)((a.slot_hi - a.slot_lo + tw - 1) / tw)), block(64 * tw);
     const bool regr = a.y_regr != nullptr;
-    if (full && !regr) hipLaunchKernelGGL((k_train<WPL, true, false, NARROW>), grid, block, lds, st, p.X, p.XT, p.XB, p.gate, p.ngate, a);
-    else if (!regr) hipLaunchKernelGGL((k_train<WPL, false, false, NARROW>), grid, block, lds, st, p.X, p.XT, p.XB, p.gate, p.ngate, a);
-    else if (full) hipLaunchKernelGGL((k_train<WPL, true, true, NARROW>), grid, block, lds, st, p.X, p.XT, p.XB, p.gate, p.ngate, a);
-    else hipLaunchKernelGGL((k_train<WPL, false, true, NARROW>), grid, block, lds, st, p.X, p.XT, p.XB, p.gate, p.ngate, a);
+    if (full && !regr) hipLaunchKernelGGL((k_train<WPL, true, false, ROOMY, NARROW>), grid, block, lds, st, p.X, p.XT, p.XB, p.gate, p.ngate, a);
+    else if (!regr) hipLaunchKernelGGL((k_train<WPL, false, false, ROOMY, NARROW>), grid, block, lds, st, p.X, p.XT, p.XB, p.gate, p.ngate, a);
+    else if (full) hipLaunchKernelGGL((k_train<WPL, true, true, ROOMY, NARROW>), grid, block, lds, st, p.X, p.XT, p.XB, p.gate, p.ngate, a);
+    else hipLaunchKernelGGL((k_train<WPL, false, true, ROOMY, NARROW>), grid, block, lds, st, p.X, p.XT, p.XB, p.gate, p.ngate, a);
 }
 
 // XB (rows of bits over the examples, and the all-ones row) of q examples given row-major.
@@ -561,17 +561,25 @@ int launch_train(tm_handle *h, const int32_t *vhat, int64_t i_begin, int64_t i_e
         TM_HIP(h, hipGetLastError());
         int rc = timing_mark(h, TIMED_TRAIN, true, st);
         if (rc) return rc;
-        if (wpl <= 1 && narrow) launch_train_t<1, true>(p, a, full, st);
-        else if (wpl <= 1) launch_train_t<1>(p, a, full, st);
-        else if (wpl <= 2) launch_train_t<2>(p, a, full, st);
-        else if (wpl <= 3) launch_train_t<3>(p, a, full, st);
-        else if (wpl <= 4) launch_train_t<4>(p, a, full, st);
-        else if (wpl <= 6) launch_train_t<6>(p, a, full, st);
-        else if (wpl <= 8) launch_train_t<8>(p, a, full, st);
-        else if (wpl <= 10) launch_train_t<10>(p, a, full, st);
-        else if (wpl <= 12) launch_train_t<12>(p, a, full, st);
-        else if (wpl <= 16) launch_train_t<16>(p, a, full, st);
-        else if (wpl <= 20) launch_train_t<20>(p, a, full, st);
+        // which form of the kernel (train_split): by whether its wavefronts are resident all at once, 1,024 SIMDs
+        const int clauses = a.slot_hi - a.slot_lo;
+        const bool roomy1 = d.regr || d.thr == 0 || __builtin_ctz(d.thr) >= 12, roomy3 = clauses <= 3 * 1024, roomy2 = clauses <= 2 * 1024;
+        if (wpl <= 1 && narrow) launch_train_t<1, false, true>(p, a, full, st);
+        else if (wpl <= 1 && roomy1) launch_train_t<1, true>(p, a, full, st);
+        else if (wpl <= 1) launch_train_t<1, false>(p, a, full, st);
+        else if (wpl <= 2) launch_train_t<2, false>(p, a, full, st);
+        else if (wpl <= 3) launch_train_t<3, true>(p, a, full, st);
+        else if (wpl <= 4 && roomy3) launch_train_t<4, true>(p, a, full, st);
+        else if (wpl <= 4) launch_train_t<4, false>(p, a, full, st);
+        else if (wpl <= 6 && roomy3) launch_train_t<6, true>(p, a, full, st);
+        else if (wpl <= 6) launch_train_t<6, false>(p, a, full, st);
+        else if (wpl <= 8 && roomy2) launch_train_t<8, true>(p, a, full, st);
+        else if (wpl <= 8) launch_train_t<8, false>(p, a, full, st);
+        else if (wpl <= 10 && roomy2) launch_train_t<10, true>(p, a, full, st);
+        else if (wpl <= 10) launch_train_t<10, false>(p, a, full, st);
+        else if (wpl <= 12) launch_train_t<12, false>(p, a, full, st);
+        else if (wpl <= 16) launch_train_t<16, false>(p, a, full, st);
+        else if (wpl <= 20) launch_train_t<20, false>(p, a, full, st);
         else return TM_ELIMIT;
         TM_HIP(h, hipGetLastError());
         rc = timing_mark(h, TIMED_TRAIN, false, st);

@@ -139,6 +139,23 @@ __device__ __forceinline__ uint64_t eval64(const uint32_t *eoff, const uint2 *em
     return ballot(viol == 0u);
 }
 
+// The feedback update comes in two forms.  ROOMY: a loop over the slots for Type I events and one for Type II events; what
+// an event costs a wavefront is least, but the registers of the slots are live together.  Otherwise one loop serves
+// both types (a branch per slot, two more steps of latency), which needs the fewest registers.  Fewer registers are more
+// wavefronts per SIMD, so the second form pays as soon as the launch has wavefronts for them, and only then; wavefronts per
+// SIMD of the two forms: 3 and 4 with 6 slots, 2 and 3 with 8 and 10.  Measured, time with the one
+// loop divided by time with two loops, s = 10: 5,000 features (6 slots) 1.16 with 500 clauses, 1.24 with 3,000, 0.97 with
+// 16,000; 10,000 features (10 slots) 1.15 with 1,000 clauses, 0.85 with 3,000, 0.90 with 16,000.
+//   1 slot: five wavefronts either way; two loops are faster where little is drawn (a threshold of one Philox block or
+//     none, s = 2: 0.97) and in regression (0.98), one loop elsewhere (s = 10: 0.98)
+//   2 slots: one loop (1,000 to 16,000 clauses: 0.96 to 0.97 of two)
+//   3 slots: two loops (0.93 to 0.99 of one at every clause count; four wavefronts either way)
+//   4 slots: two loops; for many clauses held to four wavefronts by the launch bound, at 2 to 5 spilled registers (16,000
+//     clauses: 0.90 to 0.97 of the time with three wavefronts, 0.94 to 0.99 of one loop; 3,000 clauses: 1.18 to 1.27)
+//   12 to 20 slots: one loop; two would not leave room for two wavefronts
+__host__ __device__ constexpr bool train_split(int wpl, bool roomy) { return roomy || wpl == 4; }
+__host__ __device__ constexpr int train_min_waves(int wpl, bool roomy) { return wpl > 10 ? 2 : wpl == 4 && !roomy ? 4 : 1; }
+
 // Literals a clause's list in LDS can hold for the sweeps over outdated outputs; clauses
 // with more (untrained ones) are swept block by block with eval64.  Trained clauses of the
 // image-like workload have 17 literals on average, but a few dozen of 20,000 grow past 64 within
@@ -193,6 +210,13 @@ __device__ __forceinline__ int build_literals(const u32x8 (&p)[WPL], uint32_t *l
     return base;
 }
 
+// The planes of a slot are final here: the compiler may not move their update behind this point.
+__device__ __forceinline__ void pin_planes(uint32_t (&sp)[8], uint32_t &changed)
+{
+    asm volatile("" : "+v"(sp[0]), "+v"(sp[1]), "+v"(sp[2]), "+v"(sp[3]), "+v"(sp[4]), "+v"(sp[5]), "+v"(sp[6]),
+                 "+v"(sp[7]), "+v"(changed));
+}
+
 constexpr int TRAIN_WAVES_MAX = 4; // most clauses (wavefronts) per workgroup of the training kernel; the launch chooses
 
 // One wavefront = one clause of class c.  The examples whose gate can open for this
@@ -204,7 +228,7 @@ constexpr int TRAIN_WAVES_MAX = 4; // most clauses (wavefronts) per workgroup of
 // LAZY: the automata (all planes but the include masks) are fetched only when the first feedback
 // is due and written back only if there was one; otherwise they are loaded up front.  The kernel
 // holds both versions of the loop and picks per clause (see k_train).
-template <int WPL, bool FULL, bool REGR, bool LAZY, bool NARROW>
+template <int WPL, bool FULL, bool REGR, bool LAZY, bool NARROW, bool ROOMY>
 __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, const uint32_t *__restrict__ XT,
                                              const uint32_t *__restrict__ XB, const int32_t *__restrict__ gate,
                                              const int k_hi, const TrainArgs &a, uint32_t *lds, const int g,
@@ -787,7 +811,23 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
                     n_used = 0;
                 }
             }
-            {
+            constexpr bool SPLIT = train_split(WPL, ROOMY);
+            if (SPLIT && !type1) { // Type II feedback (Table 2): where the clause is 1 and the literal 0, push Exclude towards Include
+#pragma unroll
+                for (int r = 0; r < WPL; ++r) {
+                    uint32_t lw = (uint32_t)Map::word(r, lane, d.Wf);
+                    asm volatile("" : "+v"(lw));
+                    uint32_t valid;
+                    const uint32_t lit = literal(r, lw, valid);
+                    uint32_t sp[8];
+                    get_slot(p[r], sp);
+                    const uint32_t old7 = sp[7];
+                    ripple_inc(sp, ~lit & ~old7 & valid); // excluded automata (below the top bit) cannot overflow
+                    changed |= sp[7] ^ old7;
+                    if (WPL == 1) pin_planes(sp, changed);
+                    put_slot(p[r], sp);
+                }
+            } else {
 #pragma unroll
                 for (int r = 0; r < WPL; ++r) {
                     uint32_t sp[8];
@@ -801,7 +841,7 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
                     asm volatile("" : "+v"(lw));
                     uint32_t valid;
                     const uint32_t lit = literal(r, lw, valid);
-                    if (type1) { // Type I feedback (Table 1)
+                    if (SPLIT || type1) { // Type I feedback (Table 1)
                     // bit-sliced comparison of 32 16-bit uniforms with thr, least significant bit first:
                     // ge = [u >= thr]; bit b of literal j's uniform is bit j of random word b;
                     // thr bit 1: ge &= w, thr bit 0: ge |= w, i.e. majority(w, ge, ~thr bit)
@@ -838,8 +878,8 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
                     if (Cout) up = lit & (ge | d.boost) & ~at_value<FULL>(sp, a.sat.kmax, true);
                     // weak: everything else moves towards Exclude with probability 1/s
                     wk = (Cout ? ~lit : ~0u) & ~ge & valid & ~at_value<FULL>(sp, a.sat.kmin, false);
-                    } else { // Type II feedback (Table 2): where the clause is 1 and the literal 0, push Exclude towards Include
-                        up = ~lit & ~old7 & valid; // excluded automata (below the top bit) cannot overflow
+                    } else { // Type II feedback, as above
+                        up = ~lit & ~old7 & valid;
                         wk = 0u;
                     }
                     ripple_updown(sp, up, wk);
@@ -847,8 +887,7 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
                     // the planes are final here: without this the compiler moves the updates of all slots behind
                     // the last slot's draw, and old planes, direction masks and carries of every slot stay in
                     // registers until then
-                    asm volatile("" : "+v"(sp[0]), "+v"(sp[1]), "+v"(sp[2]), "+v"(sp[3]), "+v"(sp[4]), "+v"(sp[5]),
-                                 "+v"(sp[6]), "+v"(sp[7]), "+v"(changed));
+                    pin_planes(sp, changed);
                     put_slot(p[r], sp);
                     // keep the slots apart in the instruction schedule: interleaving them
                     // multiplies the live registers by the number of slots
@@ -907,8 +946,8 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
 // clauses get none, and the lazy version saves moving their automata (16 % of a quiet epoch).
 constexpr int TRAIN_EAGER_CANDIDATES = 256;
 
-template <int WPL, bool FULL, bool REGR, bool NARROW = false>
-__global__ __launch_bounds__(64 * TRAIN_WAVES_MAX, WPL > 10 ? 2 : 1) void k_train(const uint32_t *__restrict__ X, const uint32_t *__restrict__ XT,
+template <int WPL, bool FULL, bool REGR, bool ROOMY, bool NARROW = false>
+__global__ __launch_bounds__(64 * TRAIN_WAVES_MAX, train_min_waves(WPL, ROOMY)) void k_train(const uint32_t *__restrict__ X, const uint32_t *__restrict__ XT,
                                                             const uint32_t *__restrict__ XB,
                                                             const int32_t *__restrict__ gate,
                                                             const int32_t *__restrict__ ngate, const TrainArgs a)
@@ -922,8 +961,8 @@ __global__ __launch_bounds__(64 * TRAIN_WAVES_MAX, WPL > 10 ? 2 : 1) void k_trai
     const int k_hi = __builtin_amdgcn_readfirstlane(ngate[g / a.d.n]);
     // wide clauses keep to the one version: the lazy one holds the addresses of all their register slots
     // alive through the loop (36 more registers with 10 slots: one wavefront per SIMD instead of two)
-    if (WPL > 4 || k_hi >= TRAIN_EAGER_CANDIDATES) train_clause<WPL, FULL, REGR, false, NARROW>(X, XT, XB, gate, k_hi, a, lds, g, lane, wave);
-    else train_clause<WPL, FULL, REGR, WPL <= 4, NARROW>(X, XT, XB, gate, k_hi, a, lds, g, lane, wave);
+    if (WPL > 4 || k_hi >= TRAIN_EAGER_CANDIDATES) train_clause<WPL, FULL, REGR, false, NARROW, ROOMY>(X, XT, XB, gate, k_hi, a, lds, g, lane, wave);
+    else train_clause<WPL, FULL, REGR, WPL <= 4, NARROW, ROOMY>(X, XT, XB, gate, k_hi, a, lds, g, lane, wave);
 }
 
 } // namespace tsetlin

@@ -292,6 +292,39 @@ def test_feedback_step_narrow_clauses(o, N, s, regression, device):
     test_feedback_step_in_every_kernel_width(o, N, s, regression, device)
 
 
+# the widths of 4, 6, 8 and 10 register slots have a second form of the update, for launches of more clauses than the
+# first form keeps resident (3,072 with 4 and 6 slots, 2,048 with 8 and 10); one slot has one for thresholds of a single
+# Philox block (s = 2) and for regression.  Examples few enough for the oracle, blocks of 64 crossed by the ranges.
+@pytest.mark.parametrize("m,n,o,N,s,regression", [(2, 1538, 4001, 128, 5.0, False), (2, 1538, 3100, 100, 2.0, False),
+                                                  (1, 3074, 4001, 128, 1.5, True), (2, 1538, 5003, 64, 3.0, False),
+                                                  (2, 1026, 7001, 128, 10.0, False), (2, 1026, 9001, 128, 4.0, False),
+                                                  (2, 1024, 9001, 128, 4.0, False), (3, 20, 300, 128, 2.0, False),
+                                                  (3, 20, 300, 100, 4.0, False), (1, 40, 300, 100, 3.0, True)])
+def test_feedback_step_in_both_forms_of_a_width(m, n, o, N, s, regression, device):
+    print("feedback, forms", m, n, o, N, s, regression, flush=True)
+    T, q = n, 70
+    rng = np.random.default_rng(o + n)
+    ora = O.Oracle(m, n, o, N, T, s, 23, regression=regression)
+    gpu = B.TsetlinMachine(m, n, o, N, T, s, 23, regression=regression)
+    # clauses of few literals: outputs of both kinds, so feedback of both types
+    ora.state[:] = sparse_random_state(rng, ora.C, ora.L, N, 1.0 / ora.L)
+    push_state(gpu, ora.state)
+    X = (rng.random((q, o)) < 0.3).astype(np.uint8)
+    y = rng.integers(0, (T + 1) if regression else m, size=q).astype(np.int32)
+    gpu.bind_train(dev_bits(gpu, X), dev_i32(gpu, y))
+    tally, ostar = ora.sync_tallies(X)
+    gpu.counters()
+    for step, (i0, cnt) in enumerate([(60, 10), (0, 12)]):
+        B.tm_set_epoch(gpu.h, step)
+        run_frozen(ora, gpu, X, y, step, i0, cnt, tally, ostar)
+        assert np.array_equal(gpu_state_as_oracle(gpu), ora.state), step
+        assert np.array_equal(gpu.tallies().cpu().numpy(), tally), step
+        assert np.array_equal(bits_to_u8(gpu.prev_outputs(), q), ostar), step
+    c = gpu.counters()
+    assert c["type1"] > 20 and c["type2_active"] > 20
+    gpu.close()
+
+
 
 @pytest.mark.parametrize("s", [1.0, 2.0, 4.0, 3.9, 25.0])
 @pytest.mark.parametrize("N", [3, 100, 128])
