@@ -379,6 +379,8 @@ int launch_eval(tm_handle *h, const uint32_t *X, int64_t q, uint32_t *bits, int6
     return TM_OK;
 }
 
+constexpr int ONE_PER_SIMD = 1536; // most clauses for which "about one per SIMD" holds (256 CUs of four)
+
 struct TrainPtrs {
     const uint32_t *X, *XT, *XB;
     const int32_t *gate, *ngate;
@@ -392,7 +394,7 @@ void launch_train_t(const TrainPtrs &p, const TrainArgs &a, bool full, hipStream
     // 0.14 ms with four; a workgroup's slots are handed on only when its slowest clause is done).  With about
     // one clause per SIMD four are better: they land on the four SIMDs of a CU, while two workgroups of two
     // may share a pair of SIMDs (1,000 clauses: 4.0 ms per epoch against 5.0 ms).
-    const int tw = a.d.C <= 1536 ? TRAIN_WAVES_MAX : 2;
+    const int tw = a.d.C <= ONE_PER_SIMD ? TRAIN_WAVES_MAX : 2;
     const size_t lds = (size_t)a.lds_wave_words * tw * 4;
     const dim3 grid((unsigned)((a.slot_hi - a.slot_lo + tw - 1) / tw)), block(64 * tw);
     const bool regr = a.y_regr != nullptr;
@@ -531,9 +533,14 @@ int launch_train(tm_handle *h, const int32_t *vhat, int64_t i_begin, int64_t i_e
     a.lds_mask_words = (d.W + 3) & ~3;
     a.lds_off_words = (d.Wf + EVAL_PAD + 3) & ~3;
     a.lds_wave_words = a.lds_mask_words + a.lds_off_words + 2 * ((d.Wf + EVAL_PAD + 1) & ~1) + TRAIN_LIT_MAX + 8;
-    // at most 16 literal words: the version whose feedback events touch neither memory nor LDS lists (its
-    // comparison needs a threshold of 1 .. 65535; 0 and 65536, where nothing is drawn, keep to the general one)
-    const bool narrow = d.W <= 16 && d.thr != 0 && d.thr < 65536u;
+    // at most 16 literal words: the version whose feedback events touch neither memory nor LDS lists.  With more than four
+    // feature words its draws go one event at a time, which pays only if a comparison needs several Philox blocks (the
+    // threshold has a bit below 12 set).  Where no draw is needed at all (s = 1) it draws all the same, which is free only
+    // with about one clause per SIMD.  Time of the general version / this one, 1,000 clauses: 12 features s = 3.9 1.43, s = 2
+    // 1.33, s = 1 1.05 (20,000 clauses 0.95); 100 features 1.22, 1.14, 1.04; 256 features s = 3.9 1.05, s = 4 1.00, s = 2
+    // 0.97 (20,000 clauses 0.95)
+    const bool several = d.thr != 0 && __builtin_ctz(d.thr) < 12, drawn = d.thr != 0 && d.thr < 65536u;
+    const bool narrow = d.W <= 16 && (several || (d.Wf <= 4 && (drawn || d.C <= ONE_PER_SIMD)));
     if (narrow) a.lds_wave_words = 8 * 64 + TRAIN_LIT_MAX + 8; // the words of the open block and the list for the sweeps
     a.QW = (int)xb_row_words(h->q);
     const bool full = (d.N == 128);

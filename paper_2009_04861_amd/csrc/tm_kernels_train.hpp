@@ -350,7 +350,8 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
     // comparisons of a word are folded at once for all events; an event takes its lanes with one shuffle.
     const int wps = d.Wf <= 1 ? 0 : d.Wf <= 2 ? 1 : d.Wf <= 4 ? 2 : 3; // wp = 1 << wps
     const int dr_f = lane & ((1 << wps) - 1), dr_h = (lane >> wps) & 1, dr_t = (lane >> (wps + 1)) & 3, dr_e = lane >> (wps + 3);
-    const uint32_t thr_nibble_n = NARROW ? ~(d.thr >> (4 * dr_t)) : 0u; // complement of the four thr bits of this lane's block
+    // complement of the four thr bits of this lane's block; 65536 (s = 1) as 65535: with ge_init = 0 nothing stays "at least"
+    const uint32_t thr_nibble_n = NARROW ? ~(min(d.thr, 65535u) >> (4 * dr_t)) : 0u;
     const uint32_t dr_ctr = 4u * (uint32_t)(dr_f + dr_h * d.Wf) + (uint32_t)dr_t;
     const int dr_src = ((lane >> 3) & 1) * (1 << wps) + (lane & ((1 << wps) - 1)); // draw lane (event 0) of this state lane
     uint32_t ge_ahead = 0u;

@@ -284,10 +284,12 @@ def test_feedback_step_at_slot_pair_edges(o, N, s, regression, device):
 
 
 # narrow clauses: every rounding of the words per half (1, 2, 3 -> 4, 5 -> 8, 8), one and several Philox blocks of the
-# threshold that matter, and the two thresholds (s = 1, s beyond 16 bits) that stay with the general version
+# threshold that matter, and the two thresholds (s = 1, s beyond 16 bits) with one outcome for every literal; five words and more
+# with a threshold of one block or none stay with the general version
 @pytest.mark.parametrize("o,N,s,regression", [(31, 128, 3.9, False), (64, 100, 2.0, False), (90, 128, 7.0, False), (129, 128, 1.5, True),
                                               (160, 128, 3.9, False), (256, 64, 25.0, False), (256, 128, 1.0, False),
-                                              (40, 128, 200000.0, True)])
+                                              (40, 128, 200000.0, True), (12, 100, 1.0, False), (128, 128, 1.0, True),
+                                              (60, 64, 200000.0, False), (129, 100, 4.0, False), (256, 128, 2.0, False)])
 def test_feedback_step_narrow_clauses(o, N, s, regression, device):
     test_feedback_step_in_every_kernel_width(o, N, s, regression, device)
 
@@ -298,7 +300,8 @@ def test_feedback_step_narrow_clauses(o, N, s, regression, device):
 @pytest.mark.parametrize("m,n,o,N,s,regression", [(2, 1538, 4001, 128, 5.0, False), (2, 1538, 3100, 100, 2.0, False),
                                                   (1, 3074, 4001, 128, 1.5, True), (2, 1538, 5003, 64, 3.0, False),
                                                   (2, 1026, 7001, 128, 10.0, False), (2, 1026, 9001, 128, 4.0, False),
-                                                  (2, 1024, 9001, 128, 4.0, False), (3, 20, 300, 128, 2.0, False),
+                                                  (2, 1024, 9001, 128, 4.0, False), (2, 770, 90, 128, 1.0, False),
+                                                  (3, 20, 300, 128, 2.0, False),
                                                   (3, 20, 300, 100, 4.0, False), (1, 40, 300, 100, 3.0, True)])
 def test_feedback_step_in_both_forms_of_a_width(m, n, o, N, s, regression, device):
     print("feedback, forms", m, n, o, N, s, regression, flush=True)
