@@ -494,14 +494,21 @@ int launch_eval_few(tm_handle *h, const uint32_t *X, int64_t q, int32_t *partial
     a.all_pos = d.regr; a.Tlo = d.regr ? 0 : -d.T; a.T = d.T;
     int rc = timing_mark(h, timed_kind, true, st);
     if (rc) return rc;
-    const unsigned wgs = (unsigned)(d.m * a.S);
-    if (q == 1) hipLaunchKernelGGL(k_eval_few<1>, dim3(wgs), dim3(64 * FEW_WAVES), 0, st, h->inc, X, partial, a);
-    else hipLaunchKernelGGL(k_eval_few<FEW_E>, dim3(wgs, (unsigned)((q + FEW_E - 1) / FEW_E)), dim3(64 * FEW_WAVES), 0, st,
-                            h->inc, X, partial, a);
+    const int64_t rows = ((int64_t)d.m * a.S + 7) / 8, rows_z = (rows + 65534) / 65535;
+    // examples per workgroup: eight read the masks half as often as four but are half the workgroups, which pays from
+    // about four workgroups per CU on.  us with four / eight: 20,000 clauses of 10,000 features, 8 examples 20 / 21, 16
+    // examples 30 / 25; 65,536 of 20,000 features 116 / 96, 179 / 141; 200,000 of 784 features 49 / 43, 82 / 67
+    const int E = q == 1 ? 1 : q <= 4 || 8 * rows * ((q + FEW_E - 1) / FEW_E) < 1024 ? 4 : FEW_E;
+    const dim3 grid((unsigned)(8 * ((q + E - 1) / E)), (unsigned)((rows + rows_z - 1) / rows_z), (unsigned)rows_z);
+    if (E == 1) hipLaunchKernelGGL(k_eval_few<1>, grid, dim3(64 * FEW_WAVES), 0, st, h->inc, X, partial, a);
+    else if (E == 4) hipLaunchKernelGGL(k_eval_few<4>, grid, dim3(64 * FEW_WAVES), 0, st, h->inc, X, partial, a);
+    else hipLaunchKernelGGL(k_eval_few<FEW_E>, grid, dim3(64 * FEW_WAVES), 0, st, h->inc, X, partial, a);
     TM_HIP(h, hipGetLastError());
     rc = timing_mark(h, timed_kind, false, st);
     if (rc) return rc;
-    hipLaunchKernelGGL(k_few_finish, dim3((unsigned)q), dim3(256), 0, st, partial, sums, pred, a);
+    int per = 1; // lanes per class
+    while (per < a.S && per < 64) per *= 2;
+    hipLaunchKernelGGL(k_few_finish, dim3((unsigned)q), dim3(256), 0, st, partial, sums, pred, a, per);
     TM_HIP(h, hipGetLastError());
     return TM_OK;
 }
@@ -832,8 +839,9 @@ static int infer_ws(tm_handle *h, const uint32_t *X, int64_t q, int32_t *sums, i
     uint32_t *lits = (uint32_t *)(base + align256(xb_bytes(d, q)));
     int32_t *nlit = (int32_t *)(base + align256(xb_bytes(d, q)) + align256(lits_bytes(d, q)));
     // a few examples: from the masks, without lists and bit rows.  Both paths measured per call, us (masks / lists): 20,000
-    // clauses of 784 features, 1 example 10.6 / 33.8, 32 examples 19.3 / 33.8; 20,000 of 10,000 features 14.4 / 80, 64 / 80;
-    // 16,384 of 20,000 features 23 / 86, 78 / 86; 70,000 of 784 features 11.5 / 58, 54 / 58; 20 of 12 features 9.6 / 12.4
+    // clauses of 784 features, 1 example 11 / 31, 32 examples 19 / 35; 20,000 of 10,000 features 16 / 81, 40 / 88; 65,536 of
+    // 20,000 features 64 / 337, 235 / 347; 200,000 of 784 features 24 / 114, 119 / 123; 1,000,000 of 64 features 118 / 595,
+    // 593 / 628; 3,000 classes of 2 clauses 11 / 305, 28 / 418; 20 clauses of 12 features 11 / 14, 11 / 14
     if (q <= FEW_EXAMPLES) return launch_eval_few(h, X, q, (int32_t *)ws, sums, pred, timed_kind, st);
     // the bit rows of the examples and the literal lists are built by one launch
     return launch_eval_sparse(h, XB, q, lits, nlit, nullptr, 0, sums, d.m, 1, d.T, pred, nullptr, timed_kind, st, X);

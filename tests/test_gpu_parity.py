@@ -677,6 +677,35 @@ def test_predictions_of_few_examples(m, n, o, regression, q, device):
     gpu.close()
 
 
+# the same calls where the kernels go round their loops: more than 64 shares of 32 clauses in a class (n > 2,048) with a
+# ragged last one, four and eight examples per workgroup, more classes than a workgroup takes at once with equal sums
+@pytest.mark.parametrize("m,n,o,q", [(2, 2102, 300, 1), (2, 2102, 300, 8), (2, 2102, 300, 32), (1, 33000, 40, 20), (600, 6, 70, 1),
+                                     (300, 40, 70, 32), (500, 34, 40, 9)])
+def test_predictions_of_few_examples_on_large_machines(m, n, o, q, device):
+    test_predictions_of_few_examples(m, n, o, m == 1, q, device)
+
+
+def test_prediction_of_one_example_over_half_a_million_classes(device):
+    """More shares than two grid dimensions hold: sums and the lowest of many equal best classes, in closed form."""
+    m, n, o, N = 524300, 2, 12, 128
+    gpu = B.TsetlinMachine(m, n, o, N, 9, 3.0, 5)
+    st = torch.zeros((gpu.C, gpu.L), dtype=torch.uint8, device=gpu.dev)
+    st[0::2, 0] = 255                     # negative clauses: x0
+    st[1::2, 1] = 255                     # positive clauses: x1, except
+    st[524290 * 2 + 1::2, 1] = 0
+    st[524290 * 2 + 1::2, 2] = 255        # those of the last ten classes: x2
+    gpu.set_ta_state(st)
+    ws = torch.empty(B.tm_infer_ws_bytes(gpu.cfg, 1), dtype=torch.uint8, device=gpu.dev)
+    sums = torch.full((1, m), -99, dtype=torch.int32, device=gpu.dev)
+    pred = torch.full((1,), -99, dtype=torch.int32, device=gpu.dev)
+    with torch.cuda.device(gpu.dev):
+        for x, head, tail, best in [(0b100, 0, 1, 524290), (0b010, 1, 0, 0), (0b101, -1, 0, 524290)]:
+            B.tm_predict_ws(gpu.h, torch.tensor([[x]], dtype=torch.int32, device=gpu.dev), pred, sums, ws)
+            assert bool((sums[0, :524290] == head).all()) and bool((sums[0, 524290:] == tail).all())
+            assert int(pred[0]) == best
+    gpu.close()
+
+
 # clause outputs take the literal rows of a range of examples from LDS for 17 to 76 feature words and 128 examples or more: edges of the widths that
 # the kernel is compiled for, of its ranges of 1,024 (512) examples and of the words of 32, empty and dense clauses
 @pytest.mark.parametrize("o", [512, 513, 832, 833, 1216, 1217, 2432, 2433])
