@@ -708,7 +708,7 @@ def test_prediction_of_one_example_over_half_a_million_classes(device):
 
 # clause outputs take the literal rows of a range of examples from LDS for 17 to 76 feature words and 128 examples or more: edges of the widths that
 # the kernel is compiled for, of its ranges of 1,024 (512) examples and of the words of 32, empty and dense clauses
-@pytest.mark.parametrize("o", [512, 513, 832, 833, 1216, 1217, 2432, 2433])
+@pytest.mark.parametrize("o", [512, 513, 832, 833, 1024, 1025, 1216, 1217, 2432, 2433])
 @pytest.mark.parametrize("q", [127, 128, 512, 1057])
 def test_clause_outputs_over_widths(o, q, device):
     print("clause outputs", o, q, flush=True)
@@ -730,4 +730,44 @@ def test_clause_outputs_over_widths(o, q, device):
     got = bits_to_u8(gpu.clause_outputs(dev_bits(gpu, X)), q)
     assert np.array_equal(got, ora.clause_outputs(X).T)
     assert got[5].any() and not got[7].any() and got[8].all()
+    gpu.close()
+
+
+# the same kernel with several clauses per wavefront: an early stop followed by a live clause, clauses whose many literals
+# are almost always true (put aside and evaluated from the feature words, in fours with a remainder), a ragged last
+# share; the last machine has more clauses per share than the chunk of 2,048 after which the put-aside ones are visited
+@pytest.mark.parametrize("m,n,o,q", [(3, 702, 520, 2500), (3, 702, 1000, 1100), (2, 402, 1216, 130), (2, 402, 2432, 1500),
+                                     (2, 1060, 1217, 131137)])
+def test_clause_outputs_with_many_clauses_per_wavefront(m, n, o, q, device):
+    print("clause outputs, many clauses", m, n, o, q, flush=True)
+    rng = np.random.default_rng(o + q)
+    gpu = B.TsetlinMachine(m, n, o, 128, 9, 3.0, 5)
+    X = (rng.random((q, o)) < 0.001).astype(np.uint8)
+    X[:, : o // 8] = rng.random((q, o // 8)) < 0.5
+    st = np.full((gpu.C, gpu.L), 100, dtype=np.uint8)
+    kind = np.arange(gpu.C) % 7
+    for g in range(gpu.C):
+        if kind[g] == 1:    # a few literals
+            st[g, rng.integers(0, o // 8, 3)] = 200
+        elif kind[g] == 2:  # never true from the first literals on
+            st[g] = 200
+        elif kind[g] == 3:  # hundreds of negated rare features
+            st[g, o + o // 8:] = np.where(rng.random(o - o // 8) < 0.3, 200, 100)
+        elif kind[g] == 4:  # all of them, and two that decide half of the examples each
+            st[g, o + o // 8:] = 200
+            st[g, [g % (o // 8), o + (g + 1) % (o // 8)]] = 200
+        elif kind[g] == 5:  # ten literals in one word
+            st[g, o + o // 32 * 32 - 32:o + o // 32 * 32 - 22] = 200
+    gpu.set_ta_state(torch.from_numpy(st).to(gpu.dev))
+    got = bits_to_u8(gpu.clause_outputs(dev_bits(gpu, X)), q)
+    ids = np.arange(gpu.C) if gpu.C * q < 10 ** 7 else np.concatenate([np.arange(14), np.arange(2040, 2062), np.arange(gpu.C - 7, gpu.C)])
+    for g in ids:
+        pos, neg = np.flatnonzero(st[g, :o] > 127), np.flatnonzero(st[g, o:] > 127)
+        if kind[g] == 2:
+            want = np.zeros(q, dtype=bool)
+        else:
+            want = X[:, pos].all(1) & ~X[:, neg].any(1)
+        assert np.array_equal(got[g].astype(bool), want), (g, kind[g])
+    heavy = got[kind == 3].mean()
+    assert 0.1 < heavy < 1.0 and got[kind == 0].all()
     gpu.close()
