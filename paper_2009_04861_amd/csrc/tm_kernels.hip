@@ -344,9 +344,12 @@ int launch_eval(tm_handle *h, const uint32_t *X, int64_t q, uint32_t *bits, int6
     // 1,375 / 477 (dense untrained clauses 1,381 / 689); 2,400 features, 10,000 examples 1,600 / 254.  Below 128 examples
     // the transposition is most of it (64 examples 14 / 19, one 7 / 16); up to 16 feature words the few operations per
     // example are as cheap (128 features, 10,000 examples 92 / 138; 256 features, 1,280 clauses 26 / 14 to 17); above
-    // 76 feature words the rows do not fit.
+    // 76 feature words the rows do not fit.  What the rule cannot see is the number of literals that are true on almost,
+    // but not quite, every example; 20,000 clauses of 784 features, 10,000 examples: 50 of them 250 / 165, 100 249 / 257,
+    // 300 250 / 582 (2,400 features, 300: 1,600 / 920).  Up to 32 words a lane holds one mask word and the rows of 1,024
+    // examples leave one workgroup per CU either way (1,000 features with one mask word instead of two: 103 -> 98).
     if (bits && !acc && q >= 128 && d.Wf > 16 && d.Wf <= 76) {
-        if (d.Wf <= 26) return launch_eval_bits_t<32, 26>(h, p, a, st);
+        if (d.Wf <= 32) return launch_eval_bits_t<32, 32>(h, p, a, st);
         if (d.Wf <= 38) return launch_eval_bits_t<32, 38>(h, p, a, st);
         return launch_eval_bits_t<16, 76>(h, p, a, st);
     }
