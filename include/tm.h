@@ -160,7 +160,8 @@ int tm_infer_ws_bytes(const tm_config *cfg, int64_t q, size_t *out);
  * from the list of its included literals instead of from its 2o mask bits; on a
  * trained machine that is a few dozen literals per clause (the lists hold
  * 128 to 1,024 literals depending on o; longer clauses are finished from
- * their masks).  TM_ELIMIT when
+ * their masks).  Calls of up to 32 examples do without lists: one pass over
+ * the masks costs less than building them.  TM_ELIMIT when
  * (2o + 1) * 64 * ceil(q / 2048) * 4 bytes reach 4 GiB: split q. */
 int tm_class_sums_ws(tm_handle *h, const uint32_t *X, int64_t q, int32_t *sums, void *ws, void *stream);
 int tm_predict_ws(tm_handle *h, const uint32_t *X, int64_t q, int32_t *pred, int32_t *sums_scratch, void *ws,
@@ -268,7 +269,8 @@ int tm_read_counters(tm_handle *h, uint64_t *out, void *stream);
  * every launch of the training kernel is bracketed by two events on its stream,
  * with bit 1 every launch of the literal-list evaluation kernel in the tally
  * pre-calculation, with bit 2 every such launch in tm_class_sums_ws /
- * tm_predict_ws; 0 switches timing off, 7 times all three (an event between
+ * tm_predict_ws (up to 32 examples: of the kernel that evaluates them from the
+ * masks, without the one that adds up its sums); 0 switches timing off, 7 times all three (an event between
  * two kernels costs the stream a few microseconds, so a caller that times a
  * whole step asks only for the kernel it wants).  tm_read_kernel_timing waits
  * for the recorded events and returns, per kind, the summed kernel time in

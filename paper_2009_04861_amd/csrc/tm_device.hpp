@@ -162,16 +162,4 @@ __device__ __forceinline__ void ripple_updown(uint32_t (&p)[8], uint32_t up, uin
     }
 }
 
-// -1 on the automata selected by m (none of them at the bottom)
-__device__ __forceinline__ void ripple_dec(uint32_t (&p)[8], uint32_t m)
-{
-    uint32_t borrow = m;
-#pragma unroll
-    for (int b = 0; b < 8; ++b) {
-        const uint32_t t = ~p[b] & borrow;
-        p[b] ^= borrow;
-        borrow = t;
-    }
-}
-
 } // namespace tsetlin

@@ -18,13 +18,17 @@
 //                  counters uint64 [64][16] interleaved event counters, flag int32
 //   literal word lw < Wf holds x_(32 lw + j), literal word Wf + fw holds NOT x_(32 fw + j).
 //
-// Three evaluation layouts are used:
+// Five evaluation layouts are used:
 //   k_eval_sparse lane = 32 examples : one clause per wavefront at a time, one word of XB
 //            per included literal; votes counted bit-sliced (tally pre-calculation and
 //            inference with a workspace).
-//   k_eval_* lane = clause : include masks in VGPRs, example words arrive through
-//            scalar loads, one bit-select per feature word and pair; clause votes are
-//            summed with wave ballot + popcount (inference, tally pre-calculation).
+//   k_eval_few lane = literal word : a few examples straight from the include masks
+//            (inference with a workspace, up to 32 examples).
+//   k_eval_bits lane = 64 examples : literal rows of a range of examples in LDS, one row per
+//            included literal (clause outputs of 17 to 76 feature words).
+//   k_eval_resident, k_eval_stream lane = clause : include masks in VGPRs, example words arrive
+//            through scalar loads, one bit-select per feature word and pair; clause votes are
+//            summed with wave ballot + popcount (inference without a workspace, other clause outputs).
 //   k_train  one wavefront = one clause (Algorithm 1 gives every clause its own
 //            thread); lane = gate-list entry for the gates, lane = literal word for
 //            feedback, lane = example for the evaluation of a block of 64 examples.
@@ -498,20 +502,21 @@ int launch_eval_few(tm_handle *h, const uint32_t *X, int64_t q, int32_t *partial
     int rc = timing_mark(h, timed_kind, true, st);
     if (rc) return rc;
     const int64_t rows = ((int64_t)d.m * a.S + 7) / 8, rows_z = (rows + 65534) / 65535;
+    a.rows_y = (int)((rows + rows_z - 1) / rows_z);
     // examples per workgroup: eight read the masks half as often as four but are half the workgroups, which pays from
     // about four workgroups per CU on.  us with four / eight: 20,000 clauses of 10,000 features, 8 examples 20 / 21, 16
     // examples 30 / 25; 65,536 of 20,000 features 116 / 96, 179 / 141; 200,000 of 784 features 49 / 43, 82 / 67
     const int E = q == 1 ? 1 : q <= 4 || 8 * rows * ((q + FEW_E - 1) / FEW_E) < 1024 ? 4 : FEW_E;
-    const dim3 grid((unsigned)(8 * ((q + E - 1) / E)), (unsigned)((rows + rows_z - 1) / rows_z), (unsigned)rows_z);
+    const dim3 grid((unsigned)(8 * ((q + E - 1) / E)), (unsigned)a.rows_y, (unsigned)rows_z);
     if (E == 1) hipLaunchKernelGGL(k_eval_few<1>, grid, dim3(64 * FEW_WAVES), 0, st, h->inc, X, partial, a);
     else if (E == 4) hipLaunchKernelGGL(k_eval_few<4>, grid, dim3(64 * FEW_WAVES), 0, st, h->inc, X, partial, a);
     else hipLaunchKernelGGL(k_eval_few<FEW_E>, grid, dim3(64 * FEW_WAVES), 0, st, h->inc, X, partial, a);
     TM_HIP(h, hipGetLastError());
     rc = timing_mark(h, timed_kind, false, st);
     if (rc) return rc;
-    int per = 1; // lanes per class
-    while (per < a.S && per < 64) per *= 2;
-    hipLaunchKernelGGL(k_few_finish, dim3((unsigned)q), dim3(256), 0, st, partial, sums, pred, a, per);
+    int per_log = 0; // lanes per class
+    while ((1 << per_log) < a.S && per_log < 6) ++per_log;
+    hipLaunchKernelGGL(k_few_finish, dim3((unsigned)q), dim3(256), 0, st, partial, sums, pred, a, per_log);
     TM_HIP(h, hipGetLastError());
     return TM_OK;
 }
@@ -877,9 +882,10 @@ int tm_predict_static(tm_handle *h, const uint32_t *X, int64_t q, int32_t *pred,
     hipError_t e;
     char *base = (char *)static_scratch_of(h->cfg.device, &e); // looked up in tm_create: no HIP call here
     if (!base) return hip_fail(h, e);
-    // every word the kernels read is written first by this call (literal rows, lists, lengths; partial sums
-    // are cleared by the list kernel), so what an earlier call left in the array does not matter; the
-    // kernels are not timed here because recording a new event would allocate
+    // every word the kernels read is written first by this call (literal rows, lists, lengths; sums that several
+    // workgroups add up to are cleared by the list kernel, partial sums of a few examples written whole), so what an
+    // earlier call left in the array does not matter; the kernels are not timed here because recording a new event
+    // would allocate
     return infer_ws(h, X, q, (int32_t *)(base + align256(ws_bytes)), pred, base, stream, -1);
 }
 

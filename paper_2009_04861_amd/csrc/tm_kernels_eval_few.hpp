@@ -31,6 +31,7 @@ struct FewArgs {
     int q, Wf, W, n, m, S; // S = shares of FEW_CHUNK clauses per class
     int all_pos;           // regression mode: every clause votes +1
     int Tlo, T;
+    int rows_y;            // grid dimension y of k_eval_few
 };
 
 // partial[(c * S + s) * q + i] = votes of the clauses of share s of class c for example i.  Grid: x = 8 * groups of E
@@ -42,7 +43,7 @@ __global__ __launch_bounds__(64 * FEW_WAVES) void k_eval_few(const uint32_t *__r
     __shared__ int32_t votes[FEW_WAVES][E];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int share = (int)((blockIdx.z * gridDim.y + blockIdx.y) * 8 + (blockIdx.x & 7)); // at most half the 2^30 clauses
+    const int share = (int)((blockIdx.z * (unsigned)a.rows_y + blockIdx.y) * 8 + (blockIdx.x & 7)); // at most half the 2^30 clauses
     if (share >= a.m * a.S) return; // the whole workgroup
     const int c = share / a.S, s = share - c * a.S;
     const int i0 = (int)(blockIdx.x >> 3) * E;
@@ -98,18 +99,18 @@ __global__ __launch_bounds__(64 * FEW_WAVES) void k_eval_few(const uint32_t *__r
 }
 
 // One workgroup per example: sums[i][c] = clamped sum of the partial sums, pred[i] (if wanted) = lowest class index
-// with the largest of them, in regression mode the clamped sum itself.  `per` lanes add up the shares of a class (a power
-// of two, S rounded up, at most 64), so that a wavefront takes 64 / per classes at once: with one class at a time 3,000
+// with the largest of them, in regression mode the clamped sum itself.  2^per_log lanes add up the shares of a class (S
+// rounded up to a power of two, at most 64), so that a wavefront takes several classes at once: with one class at a time 3,000
 // classes of two clauses took 264 us per call instead of 11.
 __global__ __launch_bounds__(256) void k_few_finish(const int32_t *__restrict__ partial, int32_t *sums, int32_t *pred,
-                                                    const FewArgs a, int per)
+                                                    const FewArgs a, int per_log)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int i = blockIdx.x;
     int best = 0x7fffffff, bv = (int)0x80000000; // no class yet
-    const int step = 256 / per;
+    const int per = 1 << per_log, step = 256 >> per_log;
     for (int c0 = 0; c0 < a.m; c0 += step) { // every lane takes part in the shuffles of every round
-        const int c = c0 + (int)threadIdx.x / per;
+        const int c = c0 + ((int)threadIdx.x >> per_log);
         int v = 0;
         if (c < a.m)
             for (int s = lane & (per - 1); s < a.S; s += per) v += partial[((int64_t)c * a.S + s) * a.q + i];

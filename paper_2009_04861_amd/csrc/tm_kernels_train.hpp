@@ -38,7 +38,7 @@ struct TrainArgs {
 // What bounds a wide clause is the register file, i.e. how many wavefronts a SIMD holds to hide the latency
 // of each other's multiplies, LDS trips and scalar loads.  With paired slots and the planes of a slot finished in
 // its turn (see the feedback loop) 10 slots take 161 instead of 235 registers (three wavefronts per SIMD instead
-// of two) and 20 slots 256 instead of 462 (two instead of one).  Measured: a batch of 3,328 documents on 20,000
+// of two) and 20 slots 256 and 12 spilled ones instead of 462 (two instead of one).  Measured: a batch of 3,328 documents on 20,000
 // clauses of 10,000 features 45.2 -> 32.2 ms, 832 examples on 16,384 clauses of 20,000 features 50.8 -> 28.2 ms.
 // Narrow clauses (at most 16 literal words, one slot): lane f holds the plain literals of feature word f, lane 8 + f
 // the negated ones, so that the masks of a feature word sit at fixed lanes.
@@ -961,7 +961,7 @@ __global__ __launch_bounds__(64 * TRAIN_WAVES_MAX, train_min_waves(WPL, ROOMY)) 
     const int g = __builtin_amdgcn_readfirstlane(a.order[slot]);
     const int k_hi = __builtin_amdgcn_readfirstlane(ngate[g / a.d.n]);
     // wide clauses keep to the one version: the lazy one holds the addresses of all their register slots
-    // alive through the loop (36 more registers with 10 slots: one wavefront per SIMD instead of two)
+    // alive through the loop (10 slots: 201 registers instead of 161, two wavefronts per SIMD instead of three)
     if (WPL > 4 || k_hi >= TRAIN_EAGER_CANDIDATES) train_clause<WPL, FULL, REGR, false, NARROW, ROOMY>(X, XT, XB, gate, k_hi, a, lds, g, lane, wave);
     else train_clause<WPL, FULL, REGR, WPL <= 4, NARROW, ROOMY>(X, XT, XB, gate, k_hi, a, lds, g, lane, wave);
 }

@@ -40,6 +40,7 @@ LIVE_SHAPES = [
     (2, 6, 2500, 128, 4, 10.0, 400, 0.3),
     (5, 2, 4200, 64, 3, 4.0, 4500, 0.2),
     (2, 4, 10000, 128, 3, 2.0, 1800, 0.1),
+    (3, 6, 200, 100, 5, 3.9, 700, 0.3),  # seven feature words: narrow, one event per draw, corrections held back
 ]
 
 
