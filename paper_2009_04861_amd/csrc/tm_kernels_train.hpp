@@ -286,7 +286,7 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
     // changes, and costs their latency and nothing else.  So the words of the open block of 64 examples stay in
     // registers (lane = example, at most eight words), the next block's are requested a block ahead, and an event
     // touches neither LDS lists nor memory.  Measured per epoch: noisy XOR (20 clauses of 2 literal words, 5,000
-    // examples) 1.27 -> 1.00 ms, regression (1,280 clauses of 16 words, 13,911 examples) 0.673 -> 0.657 ms.
+    // examples) 1.27 -> 0.96 ms, regression (1,280 clauses of 16 words, 13,911 examples) 0.673 -> 0.654 ms.
     uint32_t bw[NARROW ? 8 : 1] = {}, bw_next[NARROW ? 8 : 1] = {}, os_next0 = 0u, os_next1 = 0u;
     int block_next = -1; // block that bw_next holds
     auto narrow_load = [&](int b, uint32_t (&dst)[NARROW ? 8 : 1]) {
