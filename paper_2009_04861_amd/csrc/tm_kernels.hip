@@ -1,6 +1,7 @@
 // HIP kernels and C boundary of the asynchronous Tsetlin machine (gfx950).
-// One translation unit: the kernels live in tm_kernels_*.hpp (included below), the device
-// helpers (Philox, bit-sliced automata) in tm_device.hpp, the host half of the boundary here.
+// The kernels live in tm_kernels_*.hpp (included below), the device helpers (Philox, bit-sliced
+// automata) in tm_device.hpp, the host half of the boundary here; the forms of the training kernel are compiled
+// in tm_train_part.hip.
 //
 // Memory layout (all device memory is caller-owned):
 //   state buffer   planes uint32 [C][W][8]  bit-sliced TA counters, W = 2*Wf literal words
@@ -44,27 +45,14 @@
 #include "../../include/tm.h"
 #include "tm_device.hpp"
 
-namespace tsetlin {
-
-struct Dims {
-    int m, n, o, N, T, C, Wf, W;
-    uint32_t thr;      // 16-bit threshold: P(u < thr) = 1/s
-    uint32_t boost;    // ~0 if true positives are boosted (strong Type I event certain), else 0
-    int regr;          // 1: regression mode (one bank of clauses that all vote +1, targets 0..T)
-    uint32_t tailmask; // valid bits of the last feature word
-    RngKey key;
-};
-
-
-} // namespace tsetlin
-
+#include "tm_dims.hpp"
 #include "tm_kernels_util.hpp"
 #include "tm_kernels_prep.hpp"
 #include "tm_kernels_eval_masks.hpp"
 #include "tm_kernels_eval_bits.hpp"
 #include "tm_kernels_eval_lists.hpp"
 #include "tm_kernels_eval_few.hpp"
-#include "tm_kernels_train.hpp"
+#include "tm_train_launch.hpp"
 
 // ------------------------------------------------------------------------
 // host side: handle, validation, launches
@@ -386,29 +374,71 @@ int launch_eval(tm_handle *h, const uint32_t *X, int64_t q, uint32_t *bits, int6
     return TM_OK;
 }
 
-constexpr int ONE_PER_SIMD = 1536; // most clauses for which "about one per SIMD" holds (256 CUs of four)
+#define TM_EXTERN(part, wpl, roomy, deep, narrow) \
+    extern template void tsetlin::launch_train_form<wpl, roomy, deep, narrow>(const TrainPtrs &, TrainArgs, bool, hipStream_t);
+} // namespace
+TM_TRAIN_FORMS(TM_EXTERN)
+namespace {
 
-struct TrainPtrs {
-    const uint32_t *X, *XT, *XB;
-    const int32_t *gate, *ngate;
-};
-
-template <int WPL, bool ROOMY, bool NARROW = false>
-void launch_train_t(const TrainPtrs &p, const TrainArgs &a, bool full, hipStream_t st)
+// Launches the form for clauses of wpl register slots; false if there is none.  Roomy where a form has it: about one
+// wavefront per SIMD, or none to gain (train_split).
+bool launch_train_slots(int wpl, bool narrow, bool deep, int clauses, const TrainPtrs &p, const TrainArgs &a, bool full,
+                        hipStream_t st)
 {
-    // Clauses (wavefronts) per workgroup; the wavefronts of a workgroup do not interact.  Two are best once
-    // every SIMD holds several wavefronts (steady epochs of 20,000 clauses: 0.11 ms per launch against
-    // 0.14 ms with four; a workgroup's slots are handed on only when its slowest clause is done).  With about
-    // one clause per SIMD four are better: they land on the four SIMDs of a CU, while two workgroups of two
-    // may share a pair of SIMDs (1,000 clauses: 4.0 ms per epoch against 5.0 ms).
-    const int tw = a.d.C <= ONE_PER_SIMD ? TRAIN_WAVES_MAX : 2;
-    const size_t lds = (size_t)a.lds_wave_words * tw * 4;
-    const dim3 grid((unsigned)((a.slot_hi - a.slot_lo + tw - 1) / tw)), block(64 * tw);
-    const bool regr = a.y_regr != nullptr;
-    if (full && !regr) hipLaunchKernelGGL((k_train<WPL, true, false, ROOMY, NARROW>), grid, block, lds, st, p.X, p.XT, p.XB, p.gate, p.ngate, a);
-    else if (!regr) hipLaunchKernelGGL((k_train<WPL, false, false, ROOMY, NARROW>), grid, block, lds, st, p.X, p.XT, p.XB, p.gate, p.ngate, a);
-    else if (full) hipLaunchKernelGGL((k_train<WPL, true, true, ROOMY, NARROW>), grid, block, lds, st, p.X, p.XT, p.XB, p.gate, p.ngate, a);
-    else hipLaunchKernelGGL((k_train<WPL, false, true, ROOMY, NARROW>), grid, block, lds, st, p.X, p.XT, p.XB, p.gate, p.ngate, a);
+    if (narrow) return launch_train_form<1, false, false, true>(p, a, full, st), true;
+    const bool alone = clauses <= 1024, few = clauses <= 2 * 1024, some = clauses <= 3 * 1024;
+#define TM_TAKE(most, wpl_, roomy, deep_) \
+    if (wpl <= most) return launch_train_form<wpl_, roomy, deep_, false>(p, a, full, st), true
+    if (deep) {
+        if (alone) {
+            TM_TAKE(1, 1, true, true);
+            TM_TAKE(2, 2, true, true);
+            TM_TAKE(3, 3, true, true);
+            TM_TAKE(4, 4, false, true);
+            TM_TAKE(6, 6, true, true);
+            TM_TAKE(8, 8, true, true);
+            TM_TAKE(10, 10, true, true);
+        }
+        TM_TAKE(1, 1, false, true);
+        TM_TAKE(2, 2, false, true);
+        TM_TAKE(3, 3, false, true);
+        TM_TAKE(4, 4, false, true);
+        TM_TAKE(6, 6, false, true);
+        TM_TAKE(8, 8, false, true);
+        TM_TAKE(10, 10, false, true);
+        TM_TAKE(12, 12, false, true);
+        TM_TAKE(16, 16, false, true);
+        TM_TAKE(20, 20, false, true);
+        return false;
+    }
+    if (alone) {
+        TM_TAKE(1, 1, true, false);
+        TM_TAKE(2, 2, false, false);
+        TM_TAKE(3, 3, true, false);
+    }
+    if (some) {
+        TM_TAKE(1, 1, false, false);
+        TM_TAKE(2, 2, false, false);
+        TM_TAKE(3, 3, false, false);
+        TM_TAKE(4, 4, true, false);
+        TM_TAKE(6, 6, true, false);
+    }
+    if (few) {
+        TM_TAKE(8, 8, true, false);
+        TM_TAKE(10, 10, true, false);
+    }
+    TM_TAKE(1, 1, false, false);
+    TM_TAKE(2, 2, false, false);
+    TM_TAKE(3, 3, false, false);
+    TM_TAKE(4, 4, false, false);
+    TM_TAKE(6, 6, false, false);
+    TM_TAKE(8, 8, false, false);
+    TM_TAKE(10, 10, false, false);
+    TM_TAKE(12, 12, false, false);
+    TM_TAKE(16, 16, false, false);
+    TM_TAKE(20, 20, false, false);
+#undef TM_TAKE
+    return false;
 }
 
 // XB (rows of bits over the examples, and the all-ones row) of q examples given row-major.
@@ -583,26 +613,8 @@ int launch_train(tm_handle *h, const int32_t *vhat, int64_t i_begin, int64_t i_e
         TM_HIP(h, hipGetLastError());
         int rc = timing_mark(h, TIMED_TRAIN, true, st);
         if (rc) return rc;
-        // which form of the kernel (train_split): by whether its wavefronts are resident all at once, 1,024 SIMDs
-        const int clauses = a.slot_hi - a.slot_lo;
-        const bool roomy1 = d.regr || d.thr == 0 || __builtin_ctz(d.thr) >= 12, roomy3 = clauses <= 3 * 1024, roomy2 = clauses <= 2 * 1024;
-        if (wpl <= 1 && narrow) launch_train_t<1, false, true>(p, a, full, st);
-        else if (wpl <= 1 && roomy1) launch_train_t<1, true>(p, a, full, st);
-        else if (wpl <= 1) launch_train_t<1, false>(p, a, full, st);
-        else if (wpl <= 2) launch_train_t<2, false>(p, a, full, st);
-        else if (wpl <= 3) launch_train_t<3, true>(p, a, full, st);
-        else if (wpl <= 4 && roomy3) launch_train_t<4, true>(p, a, full, st);
-        else if (wpl <= 4) launch_train_t<4, false>(p, a, full, st);
-        else if (wpl <= 6 && roomy3) launch_train_t<6, true>(p, a, full, st);
-        else if (wpl <= 6) launch_train_t<6, false>(p, a, full, st);
-        else if (wpl <= 8 && roomy2) launch_train_t<8, true>(p, a, full, st);
-        else if (wpl <= 8) launch_train_t<8, false>(p, a, full, st);
-        else if (wpl <= 10 && roomy2) launch_train_t<10, true>(p, a, full, st);
-        else if (wpl <= 10) launch_train_t<10, false>(p, a, full, st);
-        else if (wpl <= 12) launch_train_t<12, false>(p, a, full, st);
-        else if (wpl <= 16) launch_train_t<16, false>(p, a, full, st);
-        else if (wpl <= 20) launch_train_t<20, false>(p, a, full, st);
-        else return TM_ELIMIT;
+        const bool deep = d.thr != 0 && __builtin_ctz(d.thr) < 8; // the Type I comparison needs more than two Philox blocks
+        if (!launch_train_slots(wpl, narrow, deep, a.slot_hi - a.slot_lo, p, a, full, st)) return TM_ELIMIT;
         TM_HIP(h, hipGetLastError());
         rc = timing_mark(h, TIMED_TRAIN, false, st);
         if (rc) return rc;

@@ -1,0 +1,57 @@
+// Launch of the training kernel: one function per form of it.  The forms are compiled in several translation units
+// (tm_train_part.hip), because together they take minutes.
+#ifndef TM_TRAIN_LAUNCH_HPP_
+#define TM_TRAIN_LAUNCH_HPP_
+#include "tm_dims.hpp"
+#include "tm_kernels_prep.hpp"
+#include "tm_kernels_train.hpp"
+
+namespace tsetlin {
+
+constexpr int ONE_PER_SIMD = 1536; // most clauses for which "about one per SIMD" holds (256 CUs of four)
+
+struct TrainPtrs {
+    const uint32_t *X, *XT, *XB;
+    const int32_t *gate, *ngate;
+};
+
+template <int WPL, bool ROOMY, bool DEEP, bool NARROW>
+void launch_train_form(const TrainPtrs &p, TrainArgs a, bool full, hipStream_t st)
+{
+    if (!NARROW) {
+        if (SlotMap<WPL>::PAIRED) a.lds_mask_words = 0; // the masks come out of the slots
+        a.lds_draw_off = (a.lds_mask_words + a.lds_off_words + 2 * (a.d.Wf + EVAL_PAD) + 3) & ~3;
+        a.lds_wave_words = a.lds_draw_off + (DEEP ? train_draw_words(WPL) : 0) + (WPL <= 4 ? TRAIN_LIT_MAX + 8 : 0);
+    }
+    // Clauses (wavefronts) per workgroup; the wavefronts of a workgroup do not interact.  Two are best once
+    // every SIMD holds several wavefronts (steady epochs of 20,000 clauses: 0.11 ms per launch against
+    // 0.14 ms with four; a workgroup's slots are handed on only when its slowest clause is done).  With about
+    // one clause per SIMD four are better: they land on the four SIMDs of a CU, while two workgroups of two
+    // may share a pair of SIMDs (1,000 clauses: 4.0 ms per epoch against 5.0 ms).
+    const int tw = a.d.C <= ONE_PER_SIMD ? TRAIN_WAVES_MAX : 2;
+    const size_t lds = (size_t)a.lds_wave_words * tw * 4;
+    const dim3 grid((unsigned)((a.slot_hi - a.slot_lo + tw - 1) / tw)), block(64 * tw);
+    const bool regr = a.y_regr != nullptr;
+    if (full && !regr) hipLaunchKernelGGL((k_train<WPL, true, false, ROOMY, NARROW, DEEP>), grid, block, lds, st, p.X, p.XT, p.XB, p.gate, p.ngate, a);
+    else if (!regr) hipLaunchKernelGGL((k_train<WPL, false, false, ROOMY, NARROW, DEEP>), grid, block, lds, st, p.X, p.XT, p.XB, p.gate, p.ngate, a);
+    else if (full) hipLaunchKernelGGL((k_train<WPL, true, true, ROOMY, NARROW, DEEP>), grid, block, lds, st, p.X, p.XT, p.XB, p.gate, p.ngate, a);
+    else hipLaunchKernelGGL((k_train<WPL, false, true, ROOMY, NARROW, DEEP>), grid, block, lds, st, p.X, p.XT, p.XB, p.gate, p.ngate, a);
+}
+
+// The forms there are: F(part, register slots, roomy, deep, narrow)
+#define TM_TRAIN_FORMS(F)                                                                                                      \
+    F(1, 1, false, false, true) F(1, 1, true, false, false) F(1, 1, false, false, false) F(1, 1, true, true, false)            \
+    F(1, 1, false, true, false)                                                                                                \
+    F(2, 2, false, false, false) F(2, 2, true, true, false) F(2, 2, false, true, false)                                        \
+    F(2, 3, true, false, false) F(2, 3, false, false, false)                                                                   \
+    F(3, 3, true, true, false) F(3, 3, false, true, false) F(3, 4, true, false, false) F(3, 4, false, false, false)            \
+    F(4, 4, false, true, false) F(4, 6, true, false, false) F(4, 6, false, false, false) F(4, 6, true, true, false)            \
+    F(4, 6, false, true, false)                                                                                                \
+    F(5, 8, true, false, false) F(5, 8, false, false, false) F(5, 8, true, true, false) F(5, 8, false, true, false)            \
+    F(6, 10, true, false, false) F(6, 10, false, false, false) F(6, 10, true, true, false) F(6, 10, false, true, false)        \
+    F(7, 12, false, false, false) F(7, 12, false, true, false) F(7, 16, false, false, false)                                   \
+    F(8, 16, false, true, false) F(8, 20, false, false, false) F(8, 20, false, true, false)
+
+} // namespace tsetlin
+
+#endif

@@ -294,15 +294,18 @@ def test_feedback_step_narrow_clauses(o, N, s, regression, device):
     test_feedback_step_in_every_kernel_width(o, N, s, regression, device)
 
 
-# the widths of 4, 6, 8 and 10 register slots have a second form of the update, for launches of more clauses than the
-# first form keeps resident (3,072 with 4 and 6 slots, 2,048 with 8 and 10); one slot has one for thresholds of a single
-# Philox block (s = 2) and for regression.  Examples few enough for the oracle, blocks of 64 crossed by the ranges.
+# most widths have a second form of the update for launches of more clauses than the first form is for (1,024 with thresholds of
+# more than two Philox blocks and with 1 and 3 slots, else 3,072 with 4 and 6 slots, 2,048 with 8 and 10).  Examples few
+# enough for the oracle, blocks of 64 crossed by the ranges.
 @pytest.mark.parametrize("m,n,o,N,s,regression", [(2, 1538, 4001, 128, 5.0, False), (2, 1538, 3100, 100, 2.0, False),
                                                   (1, 3074, 4001, 128, 1.5, True), (2, 1538, 5003, 64, 3.0, False),
                                                   (2, 1026, 7001, 128, 10.0, False), (2, 1026, 9001, 128, 4.0, False),
                                                   (2, 1024, 9001, 128, 4.0, False), (2, 770, 90, 128, 1.0, False),
                                                   (3, 20, 300, 128, 2.0, False),
-                                                  (3, 20, 300, 100, 4.0, False), (1, 40, 300, 100, 3.0, True)])
+                                                  (3, 20, 300, 100, 4.0, False), (1, 40, 300, 100, 3.0, True),
+                                                  (2, 514, 784, 128, 10.0, False), (2, 514, 1056, 100, 5.0, False),
+                                                  (2, 514, 2500, 128, 5.0, False), (2, 514, 784, 128, 2.0, False),
+                                                  (1, 1026, 2500, 100, 2.0, True)])
 def test_feedback_step_in_both_forms_of_a_width(m, n, o, N, s, regression, device):
     print("feedback, forms", m, n, o, N, s, regression, flush=True)
     T, q = n, 70
@@ -327,6 +330,38 @@ def test_feedback_step_in_both_forms_of_a_width(m, n, o, N, s, regression, devic
     assert c["type1"] > 20 and c["type2_active"] > 20
     gpu.close()
 
+
+
+# the threshold's lowest set bit in each of the four Philox blocks (s = 10, 65536 / 6544, 65536 / 6400, 16), at every number
+# of words per slot that matters (one slot full, a second one just begun, 3 to 20), with states around the include boundary so
+# that the masks change at most events and outputs are taken example by example as well as block by block
+@pytest.mark.parametrize("s", [10.0, 65536 / 6544, 65536 / 6400, 16.0])
+@pytest.mark.parametrize("o,N,regression", [(1024, 128, False), (1056, 100, False), (2500, 128, False), (2500, 128, True), (3500, 100, False),
+                                            (5000, 128, False), (9999, 128, True), (12007, 128, False), (20000, 100, False)])
+def test_feedback_step_when_masks_change_often(o, N, regression, s, device):
+    print("feedback, frequent changes", o, N, regression, s, flush=True)
+    m, n, T, q = (1, 6, 6, 330) if regression else (2, 4, 3, 330)
+    rng = np.random.default_rng(o + int(1000 * s))
+    ora = O.Oracle(m, n, o, N, T, s, 23, regression=regression)
+    gpu = B.TsetlinMachine(m, n, o, N, T, s, 23, regression=regression)
+    X = (rng.random((q, o)) < 0.02).astype(np.uint8)
+    y = rng.integers(0, (T + 1) if regression else m, size=q).astype(np.int32)
+    near = rng.integers(N - 2, N + 1, size=ora.state.shape)  # excluded, up to three steps from the boundary
+    near[:, o:][rng.random((m * n, o)) < 0.04] = N + 1       # a few negated literals just included
+    far = rng.random(ora.state.shape) < 0.9
+    ora.state[:] = np.where(far & (near <= N), rng.integers(1, 4, size=near.shape), near)
+    push_state(gpu, ora.state)
+    gpu.bind_train(dev_bits(gpu, X), dev_i32(gpu, y))
+    tally, ostar = ora.sync_tallies(X)
+    fired = 0
+    for step, (i0, cnt) in enumerate([(0, q), (37, 200), (0, q)]):
+        B.tm_set_epoch(gpu.h, step)
+        fired += run_frozen(ora, gpu, X, y, step, i0, cnt, tally, ostar)
+        assert np.array_equal(gpu_state_as_oracle(gpu), ora.state), step
+        assert np.array_equal(gpu.tallies().cpu().numpy(), tally), step
+        assert np.array_equal(bits_to_u8(gpu.prev_outputs(), q), ostar), step
+    assert fired > 20
+    gpu.close()
 
 
 @pytest.mark.parametrize("s", [1.0, 2.0, 4.0, 3.9, 25.0])
