@@ -500,9 +500,9 @@ int launch_eval_sparse(tm_handle *h, const uint32_t *XB, int64_t q, uint32_t *li
     int rc = timing_mark(h, timed_kind, true, st);
     if (rc) return rc;
     a.ranges = (int)ranges;
-    const int64_t per_xcd = ((ranges + 7) / 8) * d.m * S; // workgroups of the XCD with the most ranges
-    a.by_xcd = (ranges >= 24 && per_xcd * 8 <= 0x7fffffff) ? 1 : 0; // few ranges would leave XCDs idle
-    const dim3 grid = a.by_xcd ? dim3((unsigned)(per_xcd * 8)) : dim3((unsigned)ranges, (unsigned)(d.m * S));
+    // a workgroup per (range, class, share), the same number for every XCD; a grid dimension counts at most 2^32 threads
+    const int64_t per_xcd = (ranges * d.m * S + 7) / 8, rows_y = (per_xcd + (1 << 19) - 1) >> 19;
+    const dim3 grid((unsigned)(8 * ((per_xcd + rows_y - 1) / rows_y)), (unsigned)rows_y);
     hipLaunchKernelGGL(k_eval_sparse, grid, dim3(64 * SP_WAVES), 0, st, lits, nlit, h->inc, XB, a);
     TM_HIP(h, hipGetLastError());
     rc = timing_mark(h, timed_kind, false, st);

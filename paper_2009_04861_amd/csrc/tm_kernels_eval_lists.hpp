@@ -21,9 +21,8 @@ namespace tsetlin {
 // but then some literal is false on every example after a few loads and the loop stops.
 // What bounds the kernel is the cache path: every (clause, literal, word of 32 examples) is four
 // bytes through the CU's vector L1, which delivers 64 bytes per clock (measured: 0.7 of that rate
-// on trained image-like clauses, with 3 of 10 accesses going on to the L2; on 20,000 clauses of 10,000 features and
-// 13 ranges of examples 0.4 of it, because there five of six accesses to the L2 miss it: 6.5 GB per launch come from the
-// last-level cache, at 7 TB/s).  Two words per lane
+// on trained image-like clauses, with 3 of 10 accesses going on to the L2; on 20,000 clauses of 10,000 features, whose
+// rows of one range are more than an L2 holds, 0.65 of it).  Two words per lane
 // (8-byte loads, 512 contiguous bytes per wavefront) ran at half the bytes per clock of 4-byte
 // loads, with all 32 loads of a round in flight as well as with the registers re-used early: the
 // load width is no way round it.
@@ -185,7 +184,7 @@ struct SparseArgs {
     int QW, QWq;         // words per row of XB; words that hold examples (ceil(q/32))
     int n, m, o, Wf, W;
     int lit_cap;         // entries per literal list
-    int ranges, by_xcd;  // ranges of 2048 examples; workgroup -> (range, class, share) mapping
+    int ranges;          // ranges of 2048 examples
     int S, chunk;        // clauses of a class are split over S workgroups, `chunk` (a multiple of 16) each
     int nbatch;          // batches of eight clauses per wavefront: ceil(chunk / 64) (list layout)
     int T;               // > 0: the sums are clamped to [Tlo, T] (only with S = 1)
@@ -240,17 +239,15 @@ __global__ __launch_bounds__(64 * SP_WAVES) void k_eval_sparse(const uint32_t *_
     __shared__ int32_t sums[64 * 33]; // [word of the range][example of the word], rows padded against bank conflicts
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // Workgroups go to the 8 XCDs in turn and every XCD has its own L2.  With many ranges
-    // XCD x is given the ranges x, x + 8, ...: then only an eighth of every literal row
-    // passes through each L2 (same speed, a third of the HBM fetches).
-    int range = blockIdx.x, cs = blockIdx.y;
-    if (a.by_xcd) {
-        const int mS = a.m * a.S;
-        const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-        range = xcd + 8 * (slot / mS);
-        cs = slot - (slot / mS) * mS;
-        if (range >= a.ranges) return;
-    }
+    // Workgroups go to the 8 XCDs in turn and every XCD has its own L2.  XCD x takes the x-th eighth of the
+    // (range, class, share) triples in this order, so that the literal rows of a range pass through one or two L2s instead of
+    // all eight and an XCD works on one or two ranges at a time (20,000 clauses of 10,000 features, 25,000 documents: 923 -> 560 us;
+    // 784 features, 30,000 examples 98 -> 84 us; 60,000, which had an XCD per range before, the same).
+    const int mS = a.m * a.S;
+    const int64_t per_xcd = (int64_t)(gridDim.x >> 3) * gridDim.y;
+    const int64_t item = (int64_t)(blockIdx.x & 7) * per_xcd + (int64_t)blockIdx.y * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    if (item >= (int64_t)a.ranges * mS) return;
+    const int range = (int)(item / mS), cs = (int)(item - (int64_t)range * mS);
     const int c = cs / a.S, s = cs - c * a.S;
     const int word0 = range * 64, word = word0 + lane;
     uint32_t valid = 0u;
