@@ -441,23 +441,22 @@ bool launch_train_slots(int wpl, bool narrow, bool deep, int clauses, const Trai
     return false;
 }
 
-// XB (rows of bits over the examples, and the all-ones row) of q examples given row-major.
-// Grid of the bit transposition: QW / 2 workgroups along the examples, and enough along the feature words
-// for a few thousand wavefronts when the examples are few.
-inline void xb_grid(const Dims &d, int64_t q, int64_t *nbx, int64_t *ny)
+// Tiles of the bit transposition.
+inline RowTile xb_tiles(const Dims &d, int64_t q)
 {
-    *nbx = xb_row_words(q) / 2;
-    *ny = std::max<int64_t>(1, std::min<int64_t>((d.Wf + 3) / 4, (2048 + *nbx - 1) / *nbx));
+    const int64_t examples = xb_row_words(q) * 32;
+    RowTile t{512, 8, examples / 512, (d.Wf + 7) / 8};
+    if (t.nbx * t.ny < ROW_TILES_MANY) t = RowTile{64, 4, examples / 64, (d.Wf + 3) / 4};
+    return t;
 }
 
-int build_xb(tm_handle *h, const uint32_t *X, int64_t q, uint32_t *XB, hipStream_t st)
+// The bound data as literal rows (XB) and word-major features (XT).
+int build_rows(tm_handle *h, hipStream_t st)
 {
     const Dims &d = h->d;
-    const int64_t QW = xb_row_words(q);
-    int64_t wgs_x, split;
-    xb_grid(d, q, &wgs_x, &split);
-    hipLaunchKernelGGL(k_transpose_bits, dim3((unsigned)wgs_x, (unsigned)split), dim3(256), 0, st, X, XB, q, d.Wf, d.o,
-                       (int)QW);
+    const RowTile t = xb_tiles(d, h->q);
+    hipLaunchKernelGGL(k_transpose_bits, dim3((unsigned)(t.nbx * t.ny)), dim3(256), 0, st, h->X, h->XB, h->XT, h->q, h->qp, d.Wf,
+                       d.o, (int)xb_row_words(h->q), t);
     TM_HIP(h, hipGetLastError());
     return TM_OK;
 }
@@ -489,10 +488,9 @@ int launch_eval_sparse(tm_handle *h, const uint32_t *XB, int64_t q, uint32_t *li
     la.zero = reinterpret_cast<uint32_t *>(acc); la.zero_words = zero_words;
     const unsigned list_blocks = blocks_for(list_slots(d.m, ll), 4);
     if (X_rows) { // XB is still to be built from the row-major examples: same launch
-        int64_t nbx, ny;
-        xb_grid(d, q, &nbx, &ny);
-        hipLaunchKernelGGL(k_rows_and_lists, dim3((unsigned)(nbx * ny) + list_blocks), dim3(256), 0, st, X_rows,
-                           const_cast<uint32_t *>(XB), q, (int)QW, (int)nbx, (int)ny, la);
+        const RowTile t = xb_tiles(d, q);
+        hipLaunchKernelGGL(k_rows_and_lists, dim3((unsigned)(t.nbx * t.ny) + list_blocks), dim3(256), 0, st, X_rows,
+                           const_cast<uint32_t *>(XB), q, (int)QW, t, la);
     } else {
         hipLaunchKernelGGL(k_literal_lists, dim3(list_blocks), dim3(256), 0, st, la);
     }
@@ -754,11 +752,8 @@ int tm_bind_train(tm_handle *h, const uint32_t *X, const int32_t *y, int64_t q, 
     if (rc) return rc;
     rc = fill(h, h->tally, (size_t)d.m * h->qp * 4, 0u, st);
     if (rc) return rc;
-    rc = build_xb(h, X, q, h->XB, st);
+    rc = build_rows(h, st);
     if (rc) return rc;
-    hipLaunchKernelGGL(k_transpose_x, dim3(blocks_for(h->qp * d.Wf, 256)), dim3(256), 0, st, X, h->XT, q, h->qp,
-                       d.Wf);
-    TM_HIP(h, hipGetLastError());
     h->bound = true;
     return sync_tallies(h, st);
 }

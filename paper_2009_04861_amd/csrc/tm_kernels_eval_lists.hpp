@@ -31,43 +31,105 @@ constexpr int LIT_CAP_MIN = 128, LIT_CAP_MAX = 1024; // bounds of the list capac
 constexpr int SP_WAVES = 8;    // wavefronts per workgroup of k_eval_sparse
 constexpr int SP_PLANES = 8;   // bit planes of a wavefront's vote counter: at most 255 clauses per wavefront
 
-// XB from row-major X: workgroups of 4 wavefronts per 64 examples (blockIdx.x) and share of the
-// feature words (blockIdx.y), each wavefront a contiguous share of the workgroup's words; the 64 ballots of bit b of a word are two words
-// of row 32 fw + b, their complement two words of row o + 32 fw + b.  Examples from q up
-// to 32 QW read as feature 0 (no clause output is taken from them).  Row 2o is set to ones.
-// (bx, by) = workgroup of a grid of (QW / 2) x ny
-__device__ __forceinline__ void transpose_bits_block(const uint32_t *__restrict__ X, uint32_t *__restrict__ XB,
-                                                     int64_t q, int Wf, int o, int QW, int bx, int by, int ny)
+// XB (and, at bind, XT) from row-major X.  A workgroup of 4 wavefronts takes a tile of 512 examples (bx) by 8 feature words
+// (by): the words come in with 8 lanes on each example (32 contiguous bytes), are turned over in LDS to lane = example, each
+// 32 x 32 block of bits is transposed by five exchanges between lanes, and every literal row goes out as 64 contiguous bytes.
+// What bounds it is memory: 25,000 examples of 10,000 features are 31 MB in and 66 MB out.  Measured, this / ballots bit by bit with
+// 8-byte pieces of rows going out: 25,000 examples of 10,000
+// features 200 / 40 us, 30,000 examples of 20,000 features 460 / 70 us (whole calls, differences).
+// Examples from q up to 32 QW read as feature 0 (no clause output is taken from them).  Row 2o is set to ones.
+// XT[fw][i] = X[i][fw], zero for q <= i < qp, or null.
+// Tiles of 64 examples by 4 words are for launches that have few of the larger ones (ROW_TILES_MANY): 2,000 clauses of 784 features,
+// 1,000 examples 33 us with large tiles, 29 with small; 10,000 features, 30,000 examples 174 and 200.
+constexpr int ROW_TILES_MANY = 128;
+struct RowTile {
+    int ex, fw;  // examples and feature words of a tile
+    int64_t nbx; // tiles along the examples
+    int ny;      // and along the feature words
+};
+constexpr int ROW_TILE_LDS = 8 * 548; // words of the larger tile
+
+template <int EX, int FW>
+__device__ __forceinline__ void transpose_bits_tile(const uint32_t *__restrict__ X, uint32_t *__restrict__ XB,
+                                                    uint32_t *__restrict__ XT, int64_t q, int64_t qp, int Wf, int o, int QW,
+                                                    int64_t bx, int by, uint32_t *lds)
 {
+    constexpr int WORDS = EX / 32;                                      // of a row of XB
+    constexpr int ROW = WORDS + 1;                                      // in LDS: one more against bank conflicts
+    constexpr int REGION = (EX > 32 * ROW ? EX : 32 * ROW) + 4;         // of a feature word: its examples, then its rows
+    constexpr int PASS = 256 / FW, LOADS = EX / PASS;                   // examples read at a time
+    static_assert(FW * REGION <= ROW_TILE_LDS && EX % PASS == 0 && EX % 64 == 0, "");
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t i = (int64_t)bx * 64 + lane;
-    if (threadIdx.x == 0 && by == 0) // these examples' two words of the all-ones row
-        *reinterpret_cast<uint2 *>(XB + (int64_t)2 * o * QW + (int64_t)bx * 2) = make_uint2(~0u, ~0u);
-    const int per = (Wf + 4 * ny - 1) / (4 * ny);
-    const int share = by * 4 + wave;
-    const int f_end = min(Wf, (share + 1) * per);
-    for (int fw = share * per; fw < f_end; ++fw) {
-        const uint32_t x = (i < q) ? X[i * Wf + fw] : 0u;
-        uint64_t r = 0;
+    const int64_t e0 = bx * EX;
+    const int f0 = by * FW;
+    if (by == 0 && threadIdx.x < WORDS) XB[(int64_t)2 * o * QW + bx * WORDS + threadIdx.x] = ~0u;
+    {
+        const int f = threadIdx.x % FW, e = threadIdx.x / FW;
+        uint32_t x[LOADS];
 #pragma unroll
-        for (int b = 0; b < 32; ++b) {
-            const uint64_t bal = ballot(((x >> b) & 1u) != 0u);
-            r = (lane == b) ? bal : r;
+        for (int k = 0; k < LOADS; ++k) {
+            const int64_t i = e0 + k * PASS + e;
+            x[k] = (i < q && f0 + f < Wf) ? X[i * Wf + f0 + f] : 0u;
         }
-        const int k = fw * 32 + lane;
-        if (lane < 32 && k < o) {
-            *reinterpret_cast<uint2 *>(XB + (int64_t)k * QW + (int64_t)bx * 2) =
-                make_uint2((uint32_t)r, (uint32_t)(r >> 32));
-            *reinterpret_cast<uint2 *>(XB + (int64_t)(o + k) * QW + (int64_t)bx * 2) =
-                make_uint2(~(uint32_t)r, ~(uint32_t)(r >> 32));
+#pragma unroll
+        for (int k = 0; k < LOADS; ++k) lds[f * REGION + k * PASS + e] = x[k];
+    }
+    __syncthreads();
+    for (int f = wave; f < FW && f0 + f < Wf; f += 4) { // a wavefront's own region from here on
+        uint32_t *region = lds + f * REGION;
+        uint32_t x[EX / 64];
+#pragma unroll
+        for (int k = 0; k < EX / 64; ++k) x[k] = region[k * 64 + lane];
+        if (XT) {
+#pragma unroll
+            for (int k = 0; k < EX / 64; ++k) {
+                const int64_t i = e0 + k * 64 + lane;
+                if (i < qp) XT[(int64_t)(f0 + f) * qp + i] = x[k];
+            }
+        }
+        // bit j of lane l and bit l of lane j change places within each half of the wavefront, a power of two at a time
+#pragma unroll
+        for (int d = 16; d; d >>= 1) {
+            const uint32_t keep = d == 16 ? 0x0000FFFFu : d == 8 ? 0x00FF00FFu : d == 4 ? 0x0F0F0F0Fu : d == 2 ? 0x33333333u : 0x55555555u;
+            const bool upper = (lane & d) != 0;
+#pragma unroll
+            for (int k = 0; k < EX / 64; ++k) {
+                const uint32_t y = (uint32_t)__shfl_xor((int)x[k], d, 64);
+                x[k] = upper ? bitselect(keep, y >> d, x[k]) : bitselect(keep, x[k], y << d);
+            }
+        }
+        wave_lds_sync();
+#pragma unroll
+        for (int k = 0; k < EX / 64; ++k) region[(lane & 31) * ROW + 2 * k + (lane >> 5)] = x[k]; // row = literal of the word
+        wave_lds_sync();
+#pragma unroll
+        for (int r = 0; r < 32; r += 64 / WORDS) { // 64 / WORDS rows at a time
+            const int row = r + lane / WORDS, k = (f0 + f) * 32 + row;
+            const uint32_t v = region[row * ROW + lane % WORDS];
+            if (k < o) {
+                const int64_t at = bx * WORDS + lane % WORDS;
+                XB[(int64_t)k * QW + at] = v;
+                XB[(int64_t)(o + k) * QW + at] = ~v;
+            }
         }
     }
 }
 
-__global__ __launch_bounds__(256) void k_transpose_bits(const uint32_t *__restrict__ X, uint32_t *__restrict__ XB,
-                                                        int64_t q, int Wf, int o, int QW)
+__device__ __forceinline__ void transpose_bits_block(const RowTile &t, const uint32_t *X, uint32_t *XB, uint32_t *XT, int64_t q,
+                                                     int64_t qp, int Wf, int o, int QW, int64_t block, uint32_t *lds)
 {
-    transpose_bits_block(X, XB, q, Wf, o, QW, (int)blockIdx.x, (int)blockIdx.y, (int)gridDim.y);
+    const int64_t bx = block / t.ny;
+    const int by = (int)(block - bx * t.ny);
+    if (t.ex == 512) transpose_bits_tile<512, 8>(X, XB, XT, q, qp, Wf, o, QW, bx, by, lds);
+    else transpose_bits_tile<64, 4>(X, XB, XT, q, qp, Wf, o, QW, bx, by, lds);
+}
+
+__global__ __launch_bounds__(256) void k_transpose_bits(const uint32_t *__restrict__ X, uint32_t *__restrict__ XB,
+                                                        uint32_t *__restrict__ XT, int64_t q, int64_t qp, int Wf, int o, int QW,
+                                                        const RowTile t)
+{
+    __shared__ uint32_t lds[ROW_TILE_LDS];
+    transpose_bits_block(t, X, XB, XT, q, qp, Wf, o, QW, blockIdx.x, lds);
 }
 
 // Literal lists of the clauses, laid out for the wavefronts that walk them.  k_eval_sparse gives
@@ -164,15 +226,14 @@ __global__ __launch_bounds__(256) void k_literal_lists(const ListArgs a)
 }
 
 // Both preparations of an inference call in one launch (they are independent of each other): the first
-// nbx * ny workgroups turn the examples into bit rows, the rest build the literal lists.
+// workgroups turn the examples into bit rows, the rest build the literal lists.
 __global__ __launch_bounds__(256) void k_rows_and_lists(const uint32_t *__restrict__ X, uint32_t *__restrict__ XB, int64_t q,
-                                                        int QW, int nbx, int ny, const ListArgs a)
+                                                        int QW, const RowTile t, const ListArgs a)
 {
-    const int64_t nt = (int64_t)nbx * ny;
-    if ((int64_t)blockIdx.x < nt)
-        transpose_bits_block(X, XB, q, a.Wf, a.o, QW, (int)(blockIdx.x % nbx), (int)(blockIdx.x / nbx), ny);
-    else
-        literal_lists_block(a, (int64_t)blockIdx.x - nt, (int64_t)gridDim.x - nt);
+    __shared__ uint32_t lds[ROW_TILE_LDS];
+    const int64_t nt = t.nbx * t.ny;
+    if ((int64_t)blockIdx.x < nt) transpose_bits_block(t, X, XB, nullptr, q, 0, a.Wf, a.o, QW, blockIdx.x, lds);
+    else literal_lists_block(a, (int64_t)blockIdx.x - nt, (int64_t)gridDim.x - nt);
 }
 
 struct SparseArgs {

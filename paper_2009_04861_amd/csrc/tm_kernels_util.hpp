@@ -84,16 +84,6 @@ __global__ void k_get_state(Dims d, const uint32_t *planes, uint8_t *out)
     }
 }
 
-// XT[fw][i] = X[i][fw], zero for q <= i < qp
-__global__ void k_transpose_x(const uint32_t *X, uint32_t *XT, int64_t q, int64_t qp, int Wf)
-{
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= qp * Wf) return;
-    const int fw = (int)(t / qp);
-    const int64_t i = t - (int64_t)fw * qp;
-    XT[t] = (i < q) ? X[i * Wf + fw] : 0u;
-}
-
 // labels must lie in [0, m) (regression mode: targets in [0, T], m = T + 1)
 __global__ void k_check_labels(const int32_t *y, int64_t q, int m, int32_t *flag)
 {
