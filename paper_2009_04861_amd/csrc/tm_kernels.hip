@@ -446,7 +446,7 @@ inline RowTile xb_tiles(const Dims &d, int64_t q)
 {
     const int64_t examples = xb_row_words(q) * 32;
     RowTile t{512, 8, examples / 512, (d.Wf + 7) / 8};
-    if (t.nbx * t.ny < ROW_TILES_MANY) t = RowTile{64, 4, examples / 64, (d.Wf + 3) / 4};
+    if (t.nbx * t.ny < ROW_TILES_MANY) t = RowTile{64, 8, examples / 64, (d.Wf + 7) / 8};
     return t;
 }
 
@@ -455,7 +455,7 @@ int build_rows(tm_handle *h, hipStream_t st)
 {
     const Dims &d = h->d;
     const RowTile t = xb_tiles(d, h->q);
-    hipLaunchKernelGGL(k_transpose_bits, dim3((unsigned)(t.nbx * t.ny)), dim3(256), 0, st, h->X, h->XB, h->XT, h->q, h->qp, d.Wf,
+    hipLaunchKernelGGL(k_transpose_bits, dim3((unsigned)(t.nbx * t.ny)), dim3(PREP_THREADS), 0, st, h->X, h->XB, h->XT, h->q, h->qp, d.Wf,
                        d.o, (int)xb_row_words(h->q), t);
     TM_HIP(h, hipGetLastError());
     return TM_OK;
@@ -486,13 +486,13 @@ int launch_eval_sparse(tm_handle *h, const uint32_t *XB, int64_t q, uint32_t *li
     la.inc = h->inc; la.lits = lits; la.nlit = nlit; la.m = d.m; la.n = d.n; la.Wf = d.Wf; la.W = d.W; la.o = d.o;
     la.ll = ll; la.row_bytes = (uint32_t)(QW * 4); la.fresh = fresh; la.qp = (int)h->qp;
     la.zero = reinterpret_cast<uint32_t *>(acc); la.zero_words = zero_words;
-    const unsigned list_blocks = blocks_for(list_slots(d.m, ll), 4);
+    const unsigned list_blocks = (unsigned)(list_slots(d.m, ll) / 8);
     if (X_rows) { // XB is still to be built from the row-major examples: same launch
         const RowTile t = xb_tiles(d, q);
-        hipLaunchKernelGGL(k_rows_and_lists, dim3((unsigned)(t.nbx * t.ny) + list_blocks), dim3(256), 0, st, X_rows,
+        hipLaunchKernelGGL(k_rows_and_lists, dim3((unsigned)(t.nbx * t.ny) + list_blocks), dim3(PREP_THREADS), 0, st, X_rows,
                            const_cast<uint32_t *>(XB), q, (int)QW, t, la);
     } else {
-        hipLaunchKernelGGL(k_literal_lists, dim3(list_blocks), dim3(256), 0, st, la);
+        hipLaunchKernelGGL(k_literal_lists, dim3(list_blocks), dim3(PREP_THREADS), 0, st, la);
     }
     TM_HIP(h, hipGetLastError());
     int rc = timing_mark(h, timed_kind, true, st);

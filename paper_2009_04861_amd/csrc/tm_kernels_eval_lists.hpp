@@ -31,7 +31,7 @@ constexpr int LIT_CAP_MIN = 128, LIT_CAP_MAX = 1024; // bounds of the list capac
 constexpr int SP_WAVES = 8;    // wavefronts per workgroup of k_eval_sparse
 constexpr int SP_PLANES = 8;   // bit planes of a wavefront's vote counter: at most 255 clauses per wavefront
 
-// XB (and, at bind, XT) from row-major X.  A workgroup of 4 wavefronts takes a tile of 512 examples (bx) by 8 feature words
+// XB (and, at bind, XT) from row-major X.  A workgroup of 8 wavefronts takes a tile of 512 examples (bx) by 8 feature words
 // (by): the words come in with 8 lanes on each example (32 contiguous bytes), are turned over in LDS to lane = example, each
 // 32 x 32 block of bits is transposed by five exchanges between lanes, and every literal row goes out as 64 contiguous bytes.
 // What bounds it is memory: 25,000 examples of 10,000 features are 31 MB in and 66 MB out.  Measured, this / ballots bit by bit with
@@ -39,14 +39,15 @@ constexpr int SP_PLANES = 8;   // bit planes of a wavefront's vote counter: at m
 // features 200 / 40 us, 30,000 examples of 20,000 features 460 / 70 us (whole calls, differences).
 // Examples from q up to 32 QW read as feature 0 (no clause output is taken from them).  Row 2o is set to ones.
 // XT[fw][i] = X[i][fw], zero for q <= i < qp, or null.
-// Tiles of 64 examples by 4 words are for launches that have few of the larger ones (ROW_TILES_MANY): 2,000 clauses of 784 features,
+// Tiles of 64 examples by 8 words are for launches that have few of the larger ones (ROW_TILES_MANY): 2,000 clauses of 784 features,
 // 1,000 examples 33 us with large tiles, 29 with small; 10,000 features, 30,000 examples 174 and 200.
-constexpr int ROW_TILES_MANY = 128;
 struct RowTile {
     int ex, fw;  // examples and feature words of a tile
     int64_t nbx; // tiles along the examples
     int ny;      // and along the feature words
 };
+constexpr int ROW_TILES_MANY = 128;
+constexpr int PREP_THREADS = 512; // per workgroup of the preparations
 constexpr int ROW_TILE_LDS = 8 * 548; // words of the larger tile
 
 template <int EX, int FW>
@@ -57,7 +58,7 @@ __device__ __forceinline__ void transpose_bits_tile(const uint32_t *__restrict__
     constexpr int WORDS = EX / 32;                                      // of a row of XB
     constexpr int ROW = WORDS + 1;                                      // in LDS: one more against bank conflicts
     constexpr int REGION = (EX > 32 * ROW ? EX : 32 * ROW) + 4;         // of a feature word: its examples, then its rows
-    constexpr int PASS = 256 / FW, LOADS = EX / PASS;                   // examples read at a time
+    constexpr int PASS = PREP_THREADS / FW, LOADS = EX / PASS;                   // examples read at a time
     static_assert(FW * REGION <= ROW_TILE_LDS && EX % PASS == 0 && EX % 64 == 0, "");
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t e0 = bx * EX;
@@ -75,7 +76,7 @@ __device__ __forceinline__ void transpose_bits_tile(const uint32_t *__restrict__
         for (int k = 0; k < LOADS; ++k) lds[f * REGION + k * PASS + e] = x[k];
     }
     __syncthreads();
-    for (int f = wave; f < FW && f0 + f < Wf; f += 4) { // a wavefront's own region from here on
+    for (int f = wave; f < FW && f0 + f < Wf; f += PREP_THREADS / 64) { // a wavefront's own region from here on
         uint32_t *region = lds + f * REGION;
         uint32_t x[EX / 64];
 #pragma unroll
@@ -121,10 +122,10 @@ __device__ __forceinline__ void transpose_bits_block(const RowTile &t, const uin
     const int64_t bx = block / t.ny;
     const int by = (int)(block - bx * t.ny);
     if (t.ex == 512) transpose_bits_tile<512, 8>(X, XB, XT, q, qp, Wf, o, QW, bx, by, lds);
-    else transpose_bits_tile<64, 4>(X, XB, XT, q, qp, Wf, o, QW, bx, by, lds);
+    else transpose_bits_tile<64, 8>(X, XB, XT, q, qp, Wf, o, QW, bx, by, lds);
 }
 
-__global__ __launch_bounds__(256) void k_transpose_bits(const uint32_t *__restrict__ X, uint32_t *__restrict__ XB,
+__global__ __launch_bounds__(PREP_THREADS) void k_transpose_bits(const uint32_t *__restrict__ X, uint32_t *__restrict__ XB,
                                                         uint32_t *__restrict__ XT, int64_t q, int64_t qp, int Wf, int o, int QW,
                                                         const RowTile t)
 {
@@ -140,11 +141,12 @@ __global__ __launch_bounds__(256) void k_transpose_bits(const uint32_t *__restri
 // so that a round's 32 entries are 128 contiguous bytes behind one pointer (two scalar loads and one
 // pointer increment per round instead of eight of each: the kernel is sensitive to the load of
 // the CU's scalar unit).  Entry = byte offset of the literal's row in XB; the first `cap` included
-// literals in literal order (cap = list capacity, a multiple of 64), the rest of the cap slots
-// filled with the all-ones row so that the clauses of a batch can be walked in step; slots of a
+// literals in literal order (cap = list capacity, a multiple of 64), then the all-ones row up to the end of the
+// longest list of the batch, so that the clauses of a batch can be walked in step (filling all cap entries was most of
+// the bytes of the launch: 20,000 clauses of 10,000 features, 33 examples, 83 -> 54 us per call); slots of a
 // batch beyond the clauses of the share hold the all-ones row throughout and length 0.
 // nlit = number of included literals (may exceed cap; such clauses are finished from their masks).
-// One wavefront per slot.
+// One workgroup per batch, one wavefront per slot.
 struct ListLayout {
     int S, chunk, nbatch; // shares per class, clauses per share, batches per wavefront = ceil(chunk / 64)
     int cap;              // entries per list
@@ -166,7 +168,7 @@ struct ListArgs {
 };
 
 // block = workgroup index within the nblocks workgroups that build the lists
-__device__ __forceinline__ void literal_lists_block(const ListArgs &a, int64_t block, int64_t nblocks)
+__device__ __forceinline__ void literal_lists_block(const ListArgs &a, int64_t block, int64_t nblocks, uint32_t *lengths)
 {
     const uint32_t *__restrict__ inc = a.inc;
     uint32_t *__restrict__ lits = a.lits;
@@ -176,16 +178,14 @@ __device__ __forceinline__ void literal_lists_block(const ListArgs &a, int64_t b
     const uint32_t row_bytes = a.row_bytes;
     int32_t *fresh = a.fresh;
     // on the side: clear the buffer in which the evaluation kernel will add up partial sums
-    for (int64_t t = block * 256 + threadIdx.x; t < a.zero_words; t += nblocks * 256) a.zero[t] = 0u;
+    for (int64_t t = block * PREP_THREADS + threadIdx.x; t < a.zero_words; t += nblocks * PREP_THREADS) a.zero[t] = 0u;
     // ahead of a tally pre-calculation: every stored output of every clause will be current
     if (fresh)
-        for (int64_t g = block * 256 + threadIdx.x; g < (int64_t)m * n; g += nblocks * 256)
+        for (int64_t g = block * PREP_THREADS + threadIdx.x; g < (int64_t)m * n; g += nblocks * PREP_THREADS)
             *reinterpret_cast<int4 *>(fresh + g * 4) = make_int4(0, 0, qp, 0);
     const int lane = threadIdx.x & 63;
-    const int64_t slot = block * 4 + (threadIdx.x >> 6);
-    if (slot >= list_slots(m, ll)) return;
-    const int u = (int)(slot & 7);
-    const int64_t B = slot >> 3;
+    const int u = threadIdx.x >> 6;
+    const int64_t B = block, slot = B * 8 + u;
     const int b = (int)(B % ll.nbatch);
     const int w = (int)((B / ll.nbatch) % SP_WAVES);
     const int cs = (int)(B / ((int64_t)ll.nbatch * SP_WAVES));
@@ -216,24 +216,33 @@ __device__ __forceinline__ void literal_lists_block(const ListArgs &a, int64_t b
         }
         base += __shfl(incl, 63, 64);
     }
-    for (int t = min(base, cap) + lane; t < cap; t += 64) L[(t >> 2) * 32 + (t & 3)] = 2u * (uint32_t)o * row_bytes;
-    if (lane == 0) nlit[slot] = base;
+    if (lane == 0) {
+        nlit[slot] = base;
+        lengths[u] = (uint32_t)base;
+    }
+    __syncthreads();
+    int longest = 0;
+#pragma unroll
+    for (int v = 0; v < 8; ++v) longest = max(longest, (int)lengths[v]);
+    longest = (min(longest, cap) + 3) & ~3; // whole rounds
+    for (int t = min(base, cap) + lane; t < longest; t += 64) L[(t >> 2) * 32 + (t & 3)] = 2u * (uint32_t)o * row_bytes;
 }
 
-__global__ __launch_bounds__(256) void k_literal_lists(const ListArgs a)
+__global__ __launch_bounds__(PREP_THREADS) void k_literal_lists(const ListArgs a)
 {
-    literal_lists_block(a, (int64_t)blockIdx.x, (int64_t)gridDim.x);
+    __shared__ uint32_t lengths[8];
+    literal_lists_block(a, (int64_t)blockIdx.x, (int64_t)gridDim.x, lengths);
 }
 
 // Both preparations of an inference call in one launch (they are independent of each other): the first
 // workgroups turn the examples into bit rows, the rest build the literal lists.
-__global__ __launch_bounds__(256) void k_rows_and_lists(const uint32_t *__restrict__ X, uint32_t *__restrict__ XB, int64_t q,
+__global__ __launch_bounds__(PREP_THREADS) void k_rows_and_lists(const uint32_t *__restrict__ X, uint32_t *__restrict__ XB, int64_t q,
                                                         int QW, const RowTile t, const ListArgs a)
 {
     __shared__ uint32_t lds[ROW_TILE_LDS];
     const int64_t nt = t.nbx * t.ny;
     if ((int64_t)blockIdx.x < nt) transpose_bits_block(t, X, XB, nullptr, q, 0, a.Wf, a.o, QW, blockIdx.x, lds);
-    else literal_lists_block(a, (int64_t)blockIdx.x - nt, (int64_t)gridDim.x - nt);
+    else literal_lists_block(a, (int64_t)blockIdx.x - nt, (int64_t)gridDim.x - nt, lds);
 }
 
 struct SparseArgs {
