@@ -748,8 +748,7 @@ int tm_bind_train(tm_handle *h, const uint32_t *X, const int32_t *y, int64_t q, 
     TM_HIP(h, hipStreamSynchronize(st));
     if (bad) return TM_EINVAL;
 
-    rc = fill(h, h->ostar, (size_t)d.C * h->Qw * 4, 0u, st);
-    if (rc) return rc;
+    // the stored outputs are written whole by the tally pre-calculation, the tallies up to example q
     rc = fill(h, h->tally, (size_t)d.m * h->qp * 4, 0u, st);
     if (rc) return rc;
     rc = build_rows(h, st);
@@ -901,8 +900,8 @@ int tm_get_ta_state(tm_handle *h, uint8_t *out, void *stream)
     if (!h || !out) return TM_EINVAL;
     TM_HIP(h, hipSetDevice(h->cfg.device));
     const int64_t nt = (int64_t)h->d.C * h->d.W;
-    hipLaunchKernelGGL(k_get_state, dim3(blocks_for(nt, 256)), dim3(256), 0, (hipStream_t)stream, h->d, h->planes,
-                       out);
+    hipLaunchKernelGGL(k_get_state, dim3(blocks_for(nt, STATE_WORDS)), dim3(STATE_WORDS), 0, (hipStream_t)stream, h->d,
+                       h->planes, out);
     TM_HIP(h, hipGetLastError());
     return TM_OK;
 }
@@ -912,7 +911,7 @@ int tm_set_ta_state(tm_handle *h, const uint8_t *in, void *stream)
     if (!h || !in) return TM_EINVAL;
     TM_HIP(h, hipSetDevice(h->cfg.device));
     const int64_t nt = (int64_t)h->d.C * h->d.W;
-    hipLaunchKernelGGL(k_set_state, dim3(blocks_for(nt, 256)), dim3(256), 0, (hipStream_t)stream, h->d, in,
+    hipLaunchKernelGGL(k_set_state, dim3(blocks_for(nt, STATE_WORDS)), dim3(STATE_WORDS), 0, (hipStream_t)stream, h->d, in,
                        h->planes, h->inc);
     TM_HIP(h, hipGetLastError());
     if (h->bound) return fresh_set(h, true, (hipStream_t)stream); // stored outputs no longer match the clauses

@@ -53,6 +53,29 @@ def test_state_roundtrip(shape, device):
     assert np.array_equal(gpu_state_as_oracle(gpu), st)
 
 
+# automata move in runs of 256 literal words through LDS: every alignment of the caller's buffer, halves that end inside
+# a word, clauses that end inside a run and runs that end inside a clause; bytes around the buffer stay as they are
+@pytest.mark.parametrize("offset", [0, 1, 2, 3])
+@pytest.mark.parametrize("C,o,N", [(2, 1, 128), (6, 31, 100), (50, 33, 128), (8, 4096, 3), (10, 4097, 128), (34, 784, 100)])
+def test_state_roundtrip_at_every_alignment(C, o, N, offset, device):
+    gpu = B.TsetlinMachine(2, C // 2 + (C // 2) % 2, o, N, 5, 3.0, 7)
+    size = gpu.C * gpu.L
+    rng = np.random.default_rng(o + offset)
+    want = torch.from_numpy(rng.integers(0, 2 * N, size=size, dtype=np.int64).astype(np.uint8)).to(gpu.dev)
+    given = torch.full((size + 16,), 201, dtype=torch.uint8, device=gpu.dev)
+    given[offset:offset + size] = want
+    B.tm_set_ta_state(gpu.h, given[offset:offset + size])
+    got = torch.full((size + 16,), 77, dtype=torch.uint8, device=gpu.dev)
+    B.tm_get_ta_state(gpu.h, got[offset:offset + size])
+    assert torch.equal(got[offset:offset + size], want)
+    assert bool((got[:offset] == 77).all()) and bool((got[offset + size:] == 77).all())
+    inc = gpu.state_buf[gpu.C * 2 * gpu.Wf * 32 + 255 & ~255:][:gpu.C * 2 * gpu.Wf * 4].cpu().numpy().view(np.uint32)
+    bits = np.unpackbits(inc.view(np.uint8), bitorder="little").reshape(gpu.C, 2, gpu.Wf * 32)
+    assert np.array_equal(bits[:, :, :o].reshape(gpu.C, 2 * o), (want.cpu().numpy().reshape(gpu.C, 2 * o) >= N).astype(np.uint8))
+    assert not bits[:, :, o:].any()  # padding automata stay excluded
+    gpu.close()
+
+
 @pytest.mark.parametrize("shape", SHAPES)
 @pytest.mark.parametrize("q", [1, 63, 300, 777])
 def test_inference_matches(shape, q, device):
