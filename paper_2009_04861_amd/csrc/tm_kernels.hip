@@ -182,22 +182,42 @@ inline int lit_cap(const Dims &d)
 }
 
 // How k_eval_sparse splits the clauses of a class: over S workgroups (8 wavefronts each, three of
-// them per CU) of `chunk` clauses (a multiple of 16).  About 1,024 workgroups in all, but at least 256
-// clauses per workgroup (zeroing, converting and adding up a workgroup's sums costs as much as walking
-// a few hundred clauses), at least 16 per workgroup.  Measured on 10 x 2,000 clauses: 60,000 examples
-// 0.23 -> 0.19 ms against one workgroup of 16 wavefronts per CU, 10,000 examples 0.072 -> 0.054 ms.
+// them per CU) of `chunk` clauses (a multiple of 16).  About 1,024 workgroups in all, but at least 192
+// clauses per workgroup, or 96 where that leaves CUs without one (zeroing, converting and adding up a workgroup's sums costs as
+// much as walking some hundred clauses; a class in one workgroup needs no adding up at all).  Measured on 10 x 2,000
+// clauses, at least 256 / 192 / 96: 10,000 test examples 68 / 63 / 80 us, 3,000 examples of few literals 40 / 37 / 31;
+// 25,000 documents on 2 x 10,000 clauses 585 / 575 / 572.  Wavefronts take whole batches of eight clauses where the split
+// allows it (the documents with 272 instead of 256 clauses per workgroup: 628 us).
 // A wavefront walks chunk / SP_WAVES clauses and counts their votes in SP_PLANES bit planes, so a
 // chunk holds at most (2^SP_PLANES - 1) * SP_WAVES clauses, rounded DOWN to a multiple of 16.
 // Returns false if the bound is violated (cannot happen).
 inline bool eval_shares(const Dims &d, int64_t ranges, int64_t *S_out, int64_t *chunk_out)
 {
     const int64_t chunk_max = (((int64_t)((1 << SP_PLANES) - 1) * SP_WAVES) / 16) * 16;
-    int64_t S = (8192 / SP_WAVES + d.m * ranges - 1) / (d.m * ranges);
-    S = std::min<int64_t>(S, std::max<int64_t>(1, d.n / 256));
+    const int64_t wanted = (8192 / SP_WAVES + d.m * ranges - 1) / (d.m * ranges);
+    // the split by at least 256 clauses sets the list memory that a workspace is given
+    int64_t S = std::min<int64_t>(wanted, std::max<int64_t>(1, d.n / 256));
     S = std::max<int64_t>(S, (d.n + chunk_max - 1) / chunk_max);
     S = std::min<int64_t>(S, (d.n + 15) / 16);
-    const int64_t chunk = std::min<int64_t>((((d.n + S - 1) / S) + 15) & ~(int64_t)15, chunk_max);
+    int64_t chunk = std::min<int64_t>((((d.n + S - 1) / S) + 15) & ~(int64_t)15, chunk_max);
     S = (d.n + chunk - 1) / chunk;
+    // more shares, in whole batches of eight clauses per wavefront, as long as the lists fit that memory
+    const int64_t slots = S * ((chunk + 63) / 64) * 64;
+    auto split = [&](int64_t least) {
+        for (int64_t more = std::min<int64_t>(wanted, std::max<int64_t>(1, d.n / least)); more > 0; --more) {
+            const int64_t c = ((d.n + more - 1) / more + 63) & ~(int64_t)63;
+            const int64_t shares = (d.n + c - 1) / c;
+            if (c > chunk_max) break;
+            if (shares * c <= slots) {
+                chunk = c;
+                S = shares;
+                break;
+            }
+        }
+    };
+    split(192);
+    const int64_t workgroups = S * d.m * ranges;
+    if (workgroups < 64 || (workgroups < 256 && S > 1)) split(96);
     *S_out = S;
     *chunk_out = chunk;
     return chunk / SP_WAVES < (1 << SP_PLANES) && S * chunk >= d.n && chunk % 16 == 0;

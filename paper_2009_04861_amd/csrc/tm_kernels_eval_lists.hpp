@@ -306,7 +306,9 @@ __global__ __launch_bounds__(64 * SP_WAVES) void k_eval_sparse(const uint32_t *_
                                                               const uint32_t *__restrict__ inc,
                                                               const uint32_t *__restrict__ XB, const SparseArgs a)
 {
-    __shared__ int32_t sums[64 * 33]; // [word of the range][example of the word], rows padded against bank conflicts
+    // [word of the range][example of the word, two 16-bit sums per entry: e and e + 16], rows padded against bank conflicts.  A
+    // sum is at most 8 x 255 in size; a borrow out of the lower half is undone when the halves are taken apart.
+    __shared__ int32_t sums[64 * 17];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // Workgroups go to the 8 XCDs in turn and every XCD has its own L2.  XCD x takes the x-th eighth of the
@@ -330,7 +332,7 @@ __global__ __launch_bounds__(64 * SP_WAVES) void k_eval_sparse(const uint32_t *_
     uint32_t word_off = (uint32_t)word * 4u;
     asm volatile("" : "+v"(word_off)); // keep the sum in the vector unit
     if (a.acc) {
-        for (int t = tid; t < 64 * 33; t += 64 * SP_WAVES) sums[t] = 0;
+        for (int t = tid; t < 64 * 17; t += 64 * SP_WAVES) sums[t] = 0;
         __syncthreads();
     }
     uint32_t planes[SP_PLANES];
@@ -407,18 +409,23 @@ __global__ __launch_bounds__(64 * SP_WAVES) void k_eval_sparse(const uint32_t *_
     }
     if (!a.acc) return;
     const bool positive = (wave & 1) != 0 || a.all_pos; // odd index within the class: positive polarity
-#pragma unroll 4
-    for (int e = 0; e < 32; ++e) {
-        int v = 0;
+    // Counts out of the planes four examples at a time: bytes 0 and 2 of v are those of examples e and e + 16, 1 and 3 those of
+    // e + 8 and e + 24.
+#pragma unroll 2
+    for (int e = 0; e < 8; ++e) {
+        uint32_t v = 0;
 #pragma unroll
-        for (int pl = 0; pl < SP_PLANES; ++pl) v |= (int)((planes[pl] >> e) & 1u) << pl;
-        if (v) atomicAdd(&sums[lane * 33 + e], positive ? v : -v);
+        for (int pl = 0; pl < SP_PLANES; ++pl) v |= ((planes[pl] >> e) & 0x01010101u) << pl;
+        const int lo = (int)(v & 0x00FF00FFu), hi = (int)((v >> 8) & 0x00FF00FFu);
+        if (lo) atomicAdd(&sums[lane * 17 + e], positive ? lo : -lo);
+        if (hi) atomicAdd(&sums[lane * 17 + e + 8], positive ? hi : -hi);
     }
     __syncthreads();
     for (int idx = tid; idx < 2048; idx += 64 * SP_WAVES) {
         const int64_t i = (int64_t)word0 * 32 + idx;
         if (i >= a.q) continue;
-        int v = sums[(idx >> 5) * 33 + (idx & 31)];
+        const int both = sums[(idx >> 5) * 17 + (idx & 15)], low = (int16_t)both; // examples e and e + 16
+        const int v = (idx & 16) ? (both - low) >> 16 : low;
         int32_t *dst = a.acc + i * a.acc_si + (int64_t)c * a.acc_sc;
         if (a.S == 1) *dst = a.T > 0 ? min(max(v, a.Tlo), a.T) : v;
         else if (v) atomicAdd(dst, v);

@@ -90,3 +90,19 @@ def test_vote_counter_capacity_holds_for_every_split_of_a_class():
             assert chunk % 16 == 0 and chunk <= 2032 and S * chunk >= n and (S - 1) * chunk < n, (m, q, n, S, chunk)
             worst = max(worst, chunk)
     assert worst == 2032      # the cap is reached (a share of 2,033 .. 2,040 clauses would round to 2,048)
+
+
+@pytest.mark.parametrize("m,o", [(2, 12), (10, 784), (100, 5000), (1, 256)])
+def test_lists_take_no_more_memory_than_shares_of_256_clauses(m, o):
+    """Whatever split the evaluation takes, its lists fit the memory that a split into shares of at least 256 clauses
+    (multiples of 16, at most 2,032) would need, so that no call outgrows a workspace or limit that held it."""
+    for q in (33, 2048, 2049, 10000, 60000, 300000):
+        ranges = (q + 2047) // 2048
+        for n in list(range(2, 1500, 2)) + list(range(1500, 70000, 334)):
+            S, chunk = B.tm_eval_shares(B.make_config(m, n, o, 128, 5, 3.0, 1, regression=m == 1), q)
+            s = min((1024 + m * ranges - 1) // (m * ranges), max(1, n // 256))
+            s = min(max(s, (n + 2031) // 2032), (n + 15) // 16)
+            c = min(((n + s - 1) // s + 15) // 16 * 16, 2032)
+            s = (n + c - 1) // c
+            assert S * ((chunk + 63) // 64) <= s * ((c + 63) // 64), (m, n, q)
+            assert chunk % 16 == 0 and chunk <= 2032 and S * chunk >= n and (S - 1) * chunk < n
