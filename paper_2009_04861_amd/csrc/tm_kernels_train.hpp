@@ -163,9 +163,9 @@ __device__ __forceinline__ uint64_t eval64(const uint32_t *eoff, const uint2 *em
 __host__ __device__ constexpr bool train_split(int wpl, bool roomy, bool deep) { return roomy || wpl == 4 || (!deep && (wpl == 1 || wpl == 3)); }
 __host__ __device__ constexpr int train_min_waves(int wpl, bool roomy) { return roomy ? 1 : wpl <= 2 ? 5 : wpl <= 6 ? 4 : wpl <= 10 ? 3 : 2; }
 
-// train_max_waves: roomy forms of 1 to 3 slots are for launches of one wavefront per SIMD; without a ceiling the compiler
+// train_max_waves: roomy forms of 2 and 3 slots are for launches of one wavefront per SIMD; without a ceiling the compiler
 // schedules for five (1,000 clauses of 2,500 features, s = 2: 0.91 of the speed).
-__host__ __device__ constexpr int train_max_waves(int wpl, bool roomy) { return roomy && wpl <= 3 ? 2 : 8; }
+__host__ __device__ constexpr int train_max_waves(int wpl, bool roomy) { return roomy && (wpl == 2 || wpl == 3) ? 2 : 8; }
 
 // Literals a clause's list in LDS can hold for the sweeps over outdated outputs; clauses
 // with more (untrained ones) are swept block by block with eval64.  Trained clauses of the
@@ -235,7 +235,17 @@ constexpr int TRAIN_WAVES_MAX = 4; // most clauses (wavefronts) per workgroup of
 // one another up to 10, 16 slower (LDS).
 __host__ __device__ constexpr int train_draw_events(int wpl) { return wpl == 1 ? 8 : wpl == 2 ? 4 : wpl <= 4 ? 2 : 1; }
 constexpr int DRAW_RING = 128; // words of literals waiting for their last two blocks: at most 31 left over and 64 new ones
-__host__ __device__ constexpr int train_draw_words(int wpl) { return 4 * DRAW_RING + 64 * wpl * train_draw_events(wpl); }
+// Launches of one wavefront per SIMD, one slot, DEEP: a second wavefront of the workgroup draws the gates and the Type I
+// events of a round of 64 gate entries while the first works through the round before.  A wavefront alone on its SIMD
+// leaves two thirds of the issue slots empty, and its time is the length of its own chain, of which the draws are almost half.
+// The two meet at one barrier per round; what is handed over lies in LDS twice.  Time before / now: 1,000 clauses of 784
+// features, 60,000 examples 3.76 / 2.85 ms (one wavefront: 3.88 before the draws were made ahead), 90 clauses of 297 features 2.4 / 1.3 ms.
+__host__ __device__ constexpr bool train_team(int wpl, bool roomy, bool deep, bool narrow) { return wpl == 1 && roomy && deep && !narrow; }
+constexpr int TEAM_ROUND = 64 + 8; // words handed over per round beside the draws: examples, masks of fired and target-1 lanes, open gates
+__host__ __device__ constexpr int train_draw_words(int wpl, bool team)
+{
+    return 4 * DRAW_RING + 64 * wpl * (team ? 2 * 64 : train_draw_events(wpl)) + (team ? 2 * TEAM_ROUND : 0);
+}
 
 // A clause whose class has many open gates in this launch is all but certain to get feedback: its
 // automata are loaded up front and the loop carries no check for them (the check and the pointers it
@@ -256,11 +266,12 @@ template <int WPL, bool FULL, bool REGR, bool LAZY, bool NARROW, bool ROOMY, boo
 __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, const uint32_t *__restrict__ XT,
                                              const uint32_t *__restrict__ XB, const int32_t *__restrict__ gate,
                                              const int k_hi, const TrainArgs &a, uint32_t *lds, const int g,
-                                             const int lane, const int wave)
+                                             const int lane, const int wave, const bool helper)
 {
+    constexpr bool TEAM = train_team(WPL, ROOMY, DEEP, NARROW);
     using Map = SlotMap<WPL, NARROW>;
     const Dims &d = a.d;
-    uint32_t *lmask = lds + wave * a.lds_wave_words;        // [W] include masks, literal-word order
+    uint32_t *lmask = lds + (TEAM ? 0 : wave) * a.lds_wave_words; // [W] include masks, literal-word order
     uint32_t *eoff = lmask + a.lds_mask_words;              // [Wf + EVAL_PAD] (rounded to 4 words)
     uint2 *emask = reinterpret_cast<uint2 *>(eoff + a.lds_off_words);
     uint32_t *llist = lmask + a.lds_wave_words - (TRAIN_LIT_MAX + 8); // [TRAIN_LIT_MAX + 8] literal list for the sweeps
@@ -310,10 +321,12 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
         }
         have_planes = true;
     };
-    if (!LAZY || k_hi >= TRAIN_EAGER_CANDIDATES) load_planes();
+    if ((!LAZY || k_hi >= TRAIN_EAGER_CANDIDATES) && !helper) load_planes();
     int nent = 0;
     bool list_ok = true; // the entries are those of the current masks
-    if constexpr (!NARROW) nent = build_entries<WPL>(p, lmask, eoff, emask, lane, d.Wf, d.W, row_bytes);
+    if constexpr (!NARROW) {
+        if (!helper) nent = build_entries<WPL>(p, lmask, eoff, emask, lane, d.Wf, d.W, row_bytes);
+    }
 
     // Narrow clauses.  An epoch of so small a machine is the chain of one clause's feedback events and block
     // changes, and costs their latency and nothing else.  So the words of the open block of 64 examples stay in
@@ -449,13 +462,13 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
         if (lane < cnt) draws[it.w] |= it.y & (d0 | (d1 & ge_low));
         wave_lds_sync();
     };
-    auto deep_draw = [&](uint64_t t1, int iv) { // t1: Type I events of the round still to come, iv: example of each gate lane
+    auto deep_draw = [&](uint64_t t1, int iv, int most, int place) { // at most `most` events, results from draws[place] on; t1: Type I events of the round still to come, iv: example of each gate lane
         int head = 0, cnt = 0;
         RngKey key = d.key;
         uint32_t nthr = ~d.thr;
         if (LAUNDER) asm volatile("" : "+s"(key.seed_lo), "+s"(key.seed_hi), "+s"(nthr));
         const int slots = SlotMap<WPL>::PAIRED ? 2 * ((d.Wf + 63) >> 6) : WPL;
-        for (n_ahead = 0; n_ahead < train_draw_events(WPL) && t1; ++n_ahead) {
+        for (n_ahead = 0; n_ahead < most && t1; ++n_ahead) {
             const uint32_t id = readlane((uint32_t)iv, __builtin_ctzll(t1));
             t1 &= t1 - 1;
 #pragma unroll 1
@@ -472,7 +485,7 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
                     d1 = majority3(w[k], d1, K);
                 }
                 const uint32_t undecided = Map::held(r, lane, d.Wf) ? d0 ^ d1 : 0u;
-                const uint32_t at = (uint32_t)((n_ahead * WPL + r) * 64 + lane);
+                const uint32_t at = (uint32_t)(place + (n_ahead * WPL + r) * 64 + lane);
                 draws[at] = d0;
                 const uint64_t b = ballot(undecided != 0u);
                 const int pre = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
@@ -804,51 +817,84 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
     int y_cur = load_y(ent_cur);
     int ent_nxt = load_ent(k_lo + 64);
 
+    auto draw_gates = [&](int k0, int &iv, uint64_t &fmask, uint64_t &tmask) { // the round of gate entries from k0 on
+        const int ent = ent_cur, v = v_cur, yv = y_cur;
+        ent_cur = ent_nxt;
+        v_cur = load_v(ent_cur);
+        y_cur = load_y(ent_cur);
+        ent_nxt = load_ent(k0 + 128);
+        if constexpr (NARROW) { // everything requested so far arrives here, ahead of the atomics
+            asm volatile("" : "+v"(bw_next[0]), "+v"(bw_next[1]), "+v"(bw_next[2]), "+v"(bw_next[3]), "+v"(bw_next[4]),
+                         "+v"(bw_next[5]), "+v"(bw_next[6]), "+v"(bw_next[7]), "+v"(os_next0), "+v"(os_next1));
+        }
+        refresh_held();
+        const bool valid = ent >= 0;
+        iv = ent >> 1;
+        bool target = (ent & 1) != 0;
+        bool fire = false, open = false;
+        if (valid) {
+            int e, span;
+            if (regr) {
+                // regression: error of the clipped vote sum against the target, probability e/T;
+                // below the target the clause is trained towards 1, above it towards 0
+                const int vc = min(max(v, 0), T);
+                target = vc < yv;
+                e = target ? yv - vc : vc - yv;
+                span = T;
+            } else {
+                const int vc = min(max(v, -T), T);
+                e = target ? T - vc : T + vc; // Algorithm 1: error of the recorded vote sum
+                span = 2 * T;
+            }
+            open = e > 0;
+            if (open) {
+                RngKey key = d.key;
+                if (LAUNDER) asm volatile("" : "+s"(key.seed_lo), "+s"(key.seed_hi));
+                const U4 r = draw(key, STREAM_GATE, 0, (uint32_t)g, (uint64_t)(uint32_t)iv, a.epoch);
+                fire = (uint64_t)r.x * (uint64_t)span < ((uint64_t)e << 32);
+            }
+        }
+        fmask = ballot(fire);
+        tmask = ballot(target);
+        n_draw += __builtin_popcountll(ballot(open));
+        n_fired += __builtin_popcountll(fmask);
+    };
+    uint32_t *handed = draws + 2 * 64 * WPL * 64; // TEAM: [round parity][TEAM_ROUND]
+    if constexpr (TEAM) {
+        if (helper) { // round k + 1 is drawn between barriers k and k + 1, in which the first wavefront works through round k
+            for (int k0 = k_lo; k0 < k_hi; k0 += 64) {
+                const int parity = (k0 >> 6) & 1;
+                int iv = 0;
+                uint64_t fmask = 0, tmask = 0;
+                draw_gates(k0, iv, fmask, tmask);
+                uint32_t *h = handed + parity * TEAM_ROUND;
+                h[lane] = (uint32_t)iv;
+                if (lane < 5)
+                    h[64 + lane] = lane == 0 ? (uint32_t)fmask : lane == 1 ? (uint32_t)(fmask >> 32) : lane == 2 ? (uint32_t)tmask
+                                 : lane == 3 ? (uint32_t)(tmask >> 32) : n_draw;
+                deep_draw(fmask & (pos ? tmask : ~tmask), iv, 64, parity * 64 * WPL * 64);
+                __syncthreads();
+            }
+            return;
+        }
+    }
+
     for (int k0 = k_lo;; k0 += 64) {
         const bool last = k0 >= k_hi; // all candidates done: one more round sweeps the remaining blocks
         uint64_t fmask = 0, tmask = 0;
         int iv = 0;
         if (!last) {
-            const int ent = ent_cur, v = v_cur, yv = y_cur;
-            ent_cur = ent_nxt;
-            v_cur = load_v(ent_cur);
-            y_cur = load_y(ent_cur);
-            ent_nxt = load_ent(k0 + 128);
-            if constexpr (NARROW) { // everything requested so far arrives here, ahead of the atomics
-                asm volatile("" : "+v"(bw_next[0]), "+v"(bw_next[1]), "+v"(bw_next[2]), "+v"(bw_next[3]), "+v"(bw_next[4]),
-                             "+v"(bw_next[5]), "+v"(bw_next[6]), "+v"(bw_next[7]), "+v"(os_next0), "+v"(os_next1));
+            if constexpr (TEAM) {
+                __syncthreads();
+                const uint32_t *h = handed + ((k0 >> 6) & 1) * TEAM_ROUND;
+                iv = (int)h[lane];
+                fmask = pack64(h[64], h[65]);
+                tmask = pack64(h[66], h[67]);
+                n_draw = (uint32_t)__builtin_amdgcn_readfirstlane((int)h[68]);
+                n_fired += __builtin_popcountll(fmask);
+            } else {
+                draw_gates(k0, iv, fmask, tmask);
             }
-            refresh_held();
-            const bool valid = ent >= 0;
-            iv = ent >> 1;
-            bool target = (ent & 1) != 0;
-            bool fire = false, open = false;
-            if (valid) {
-                int e, span;
-                if (regr) {
-                    // regression: error of the clipped vote sum against the target, probability e/T;
-                    // below the target the clause is trained towards 1, above it towards 0
-                    const int vc = min(max(v, 0), T);
-                    target = vc < yv;
-                    e = target ? yv - vc : vc - yv;
-                    span = T;
-                } else {
-                    const int vc = min(max(v, -T), T);
-                    e = target ? T - vc : T + vc; // Algorithm 1: error of the recorded vote sum
-                    span = 2 * T;
-                }
-                open = e > 0;
-                if (open) {
-                    RngKey key = d.key;
-                    if (LAUNDER) asm volatile("" : "+s"(key.seed_lo), "+s"(key.seed_hi));
-                    const U4 r = draw(key, STREAM_GATE, 0, (uint32_t)g, (uint64_t)(uint32_t)iv, a.epoch);
-                    fire = (uint64_t)r.x * (uint64_t)span < ((uint64_t)e << 32);
-                }
-            }
-            fmask = ballot(fire);
-            tmask = ballot(target);
-            n_draw += __builtin_popcountll(ballot(open));
-            n_fired += __builtin_popcountll(fmask);
         }
 
         // the row of the next fired example is requested while the current one is processed
@@ -990,8 +1036,8 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
                 }
             }
             if constexpr (DEEP) {
-                if (type1 && n_used == n_ahead) {
-                    deep_draw((fmask | (1ull << l)) & (pos ? tmask : ~tmask), iv);
+                if (!TEAM && type1 && n_used == n_ahead) {
+                    deep_draw((fmask | (1ull << l)) & (pos ? tmask : ~tmask), iv, train_draw_events(WPL), 0);
                     n_used = 0;
                 }
             }
@@ -1041,7 +1087,7 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
                         ge = (uint32_t)__shfl((int)ge_ahead, dr_src + (n_used << (wps + 3)), 64);
                         ++n_used;
                     } else if constexpr (DEEP) {
-                        ge = draws[(n_used * WPL + r) * 64 + lane];
+                        ge = draws[((TEAM ? (k0 & 64) : 0) + n_used) * WPL * 64 + r * 64 + lane];
                         if (r == WPL - 1) ++n_used;
                     } else {
 #pragma unroll
@@ -1155,14 +1201,16 @@ __global__ __launch_bounds__(64 * TRAIN_WAVES_MAX) __attribute__((amdgpu_waves_p
     extern __shared__ uint32_t lds[];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int slot = a.slot_lo + (int)(blockIdx.x * (blockDim.x >> 6)) + wave;
-    if (slot >= a.slot_hi) return; // whole wavefront; the kernel has no workgroup-wide barrier
+    constexpr bool TEAM = train_team(WPL, ROOMY, DEEP, NARROW); // one clause per workgroup of two wavefronts
+    const int slot = a.slot_lo + (TEAM ? (int)blockIdx.x : (int)(blockIdx.x * (blockDim.x >> 6)) + wave);
+    if (slot >= a.slot_hi) return; // whole wavefront (TEAM: both, and both walk the same rounds with one barrier in each)
+    const bool helper = TEAM && wave != 0;
     const int g = __builtin_amdgcn_readfirstlane(a.order[slot]);
     const int k_hi = __builtin_amdgcn_readfirstlane(ngate[g / a.d.n]);
     // From 6 slots on one version serves both, which loads up front where the gates are many: the check per event is
     // nothing beside the event, and a quiet pass moves no automata (16,000 clauses of 20,000 features, T = n / 40: 430 -> 300 us)
-    if (WPL <= 4 && k_hi >= TRAIN_EAGER_CANDIDATES) train_clause<WPL, FULL, REGR, false, NARROW, ROOMY, DEEP>(X, XT, XB, gate, k_hi, a, lds, g, lane, wave);
-    else train_clause<WPL, FULL, REGR, true, NARROW, ROOMY, DEEP>(X, XT, XB, gate, k_hi, a, lds, g, lane, wave);
+    if (WPL <= 4 && k_hi >= TRAIN_EAGER_CANDIDATES) train_clause<WPL, FULL, REGR, false, NARROW, ROOMY, DEEP>(X, XT, XB, gate, k_hi, a, lds, g, lane, wave, helper);
+    else train_clause<WPL, FULL, REGR, true, NARROW, ROOMY, DEEP>(X, XT, XB, gate, k_hi, a, lds, g, lane, wave, helper);
 }
 
 } // namespace tsetlin

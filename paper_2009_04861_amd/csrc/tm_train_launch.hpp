@@ -18,19 +18,20 @@ struct TrainPtrs {
 template <int WPL, bool ROOMY, bool DEEP, bool NARROW>
 void launch_train_form(const TrainPtrs &p, TrainArgs a, bool full, hipStream_t st)
 {
+    constexpr bool TEAM = train_team(WPL, ROOMY, DEEP, NARROW);
     if (!NARROW) {
         if (SlotMap<WPL>::PAIRED) a.lds_mask_words = 0; // the masks come out of the slots
         a.lds_draw_off = (a.lds_mask_words + a.lds_off_words + 2 * (a.d.Wf + EVAL_PAD) + 3) & ~3;
-        a.lds_wave_words = a.lds_draw_off + (DEEP ? train_draw_words(WPL) : 0) + (WPL <= 4 ? TRAIN_LIT_MAX + 8 : 0);
+        a.lds_wave_words = a.lds_draw_off + (DEEP ? train_draw_words(WPL, TEAM) : 0) + (WPL <= 4 ? TRAIN_LIT_MAX + 8 : 0);
     }
     // Clauses (wavefronts) per workgroup; the wavefronts of a workgroup do not interact.  Two are best once
     // every SIMD holds several wavefronts (steady epochs of 20,000 clauses: 0.11 ms per launch against
     // 0.14 ms with four; a workgroup's slots are handed on only when its slowest clause is done).  With about
     // one clause per SIMD four are better: they land on the four SIMDs of a CU, while two workgroups of two
     // may share a pair of SIMDs (1,000 clauses: 4.0 ms per epoch against 5.0 ms).
-    const int tw = a.d.C <= ONE_PER_SIMD ? TRAIN_WAVES_MAX : 2;
+    const int tw = TEAM ? 1 : a.d.C <= ONE_PER_SIMD ? TRAIN_WAVES_MAX : 2;
     const size_t lds = (size_t)a.lds_wave_words * tw * 4;
-    const dim3 grid((unsigned)((a.slot_hi - a.slot_lo + tw - 1) / tw)), block(64 * tw);
+    const dim3 grid((unsigned)((a.slot_hi - a.slot_lo + tw - 1) / tw)), block(64 * (TEAM ? 2 : tw));
     const bool regr = a.y_regr != nullptr;
     if (full && !regr) hipLaunchKernelGGL((k_train<WPL, true, false, ROOMY, NARROW, DEEP>), grid, block, lds, st, p.X, p.XT, p.XB, p.gate, p.ngate, a);
     else if (!regr) hipLaunchKernelGGL((k_train<WPL, false, false, ROOMY, NARROW, DEEP>), grid, block, lds, st, p.X, p.XT, p.XB, p.gate, p.ngate, a);
