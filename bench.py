@@ -41,14 +41,20 @@ TYPE2_OPS_PER_WORD = 2 + 16                              # mask + one ripple
 GATE_OPS = PHILOX_OPS + 8                                # one block + clip, error, 64-bit compare
 
 
-def type1_ops_per_word(s):
+def type1_ops_per_word(s, nominal=False):
     """Type I feedback on one word of 32 literals: the Philox blocks whose bits can decide u < thr (the
     comparator bits below the lowest set bit of thr = round(65536 / s) never do: 4 blocks for s = 10 or 5,
     1 block for s = 2), 4 comparator operations per block, 2 saturation tests (4 three-input operations
-    each), one pass over the 8 planes that moves both directions (2 operations per plane), event masks."""
+    each), one pass over the 8 planes that moves both directions (2 operations per plane), event masks.
+    Of more than two blocks the lower ones are needed only for words with a literal that the upper eight bits leave
+    undecided (one literal in 256), at 8 comparator operations per block; nominal=True counts all four."""
+    if nominal:
+        return 4 * (PHILOX_OPS + 4) + 8 + 16 + 6
     thr = int(min(65536.0, max(0.0, 65536.0 / s + 0.5)))
     tz = (thr & -thr).bit_length() - 1 if thr else 16
     blocks = 4 - min(tz >> 2, 4)
+    if blocks > 2:
+        return (2 + 2 * (1 - (255 / 256) ** 32)) * (PHILOX_OPS + 8) + 8 + 16 + 6
     return blocks * (PHILOX_OPS + 4) + 8 + 16 + 6
 
 
@@ -61,10 +67,10 @@ def type1_ops_per_word(s):
 # time of the profile runs); with other sources `traffic` is reported as null.
 MEASURED_TRAFFIC = {
     "profile": "profiles/image_like_default_benchmark.txt",
-    "kernel_sources_sha256": "4430cdcf7a9057fad84f53a7064061c4ad5a626b77a9d3e0bd2d74653e4223b9",
-    "image_like_train": {"fetch_kib": 50611.5, "fetch_scale": 2.0, "write_kib": 34450.3, "write_scale": 1.0},
+    "kernel_sources_sha256": "2f6c07ba1a52ce29f77e060d7853167bf2e9e7ba9cc4c2e6a12e20eb01c9e675",
+    "image_like_train": {"fetch_kib": 50735.6, "fetch_scale": 2.0, "write_kib": 32042.3, "write_scale": 1.0},
     # k_eval_sparse in tm_sync_tallies
-    "image_like_precalc": {"fetch_kib": 59315.0, "fetch_scale": 2.0, "write_kib": 165312.5, "write_scale": 1.0},
+    "image_like_precalc": {"fetch_kib": 60332.3, "fetch_scale": 2.0, "write_kib": 167613.8, "write_scale": 1.0},
 }
 
 
@@ -113,7 +119,7 @@ def train_kernel_ops(counters, W, lits, entries, nominal=False, s=10.0):
         ev = listed * 2 * (lits + 2) + (counters["blocks_evaluated"] - listed) * 64 * (1.5 * entries + 2)
         draws = counters["gate_draws"]
     return (ev + draws * GATE_OPS
-            + counters["type1"] * W * (type1_ops_per_word(10.0) if nominal else type1_ops_per_word(s))   # nominal: all 16 bits
+            + counters["type1"] * W * type1_ops_per_word(s, nominal)
             + counters["type2_active"] * W * TYPE2_OPS_PER_WORD)
 
 

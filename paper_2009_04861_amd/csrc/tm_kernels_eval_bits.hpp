@@ -1,5 +1,5 @@
 // Clause outputs from include masks and literal rows in LDS, lane = 64 examples (interpretation of a trained machine).
-// Part of the one translation unit tm_kernels.hip (included there, in this order).
+// Part of tm_kernels.hip (included there).
 #ifndef TM_KERNELS_EVAL_BITS_HPP_
 #define TM_KERNELS_EVAL_BITS_HPP_
 

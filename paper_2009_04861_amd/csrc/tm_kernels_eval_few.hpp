@@ -1,5 +1,5 @@
 // Clause evaluation for a few examples, lane = literal word (inference with a workspace, small calls).
-// Part of the one translation unit tm_kernels.hip (included there, in this order).
+// Part of tm_kernels.hip (included there).
 #ifndef TM_KERNELS_EVAL_FEW_HPP_
 #define TM_KERNELS_EVAL_FEW_HPP_
 

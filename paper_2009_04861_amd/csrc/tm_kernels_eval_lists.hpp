@@ -1,5 +1,5 @@
 // Clause evaluation from literal lists, lane = 32 examples (tally pre-calculation, inference with a workspace).
-// Part of the one translation unit tm_kernels.hip (included there, in this order).
+// Part of tm_kernels.hip (included there).
 #ifndef TM_KERNELS_EVAL_LISTS_HPP_
 #define TM_KERNELS_EVAL_LISTS_HPP_
 

@@ -1,5 +1,5 @@
 // Clause evaluation from include masks, lane = clause (inference without a workspace; clause outputs of few examples, narrow or very wide clauses).
-// Part of the one translation unit tm_kernels.hip (included there, in this order).
+// Part of tm_kernels.hip (included there).
 #ifndef TM_KERNELS_EVAL_MASKS_HPP_
 #define TM_KERNELS_EVAL_MASKS_HPP_
 

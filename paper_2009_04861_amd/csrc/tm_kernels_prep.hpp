@@ -1,5 +1,5 @@
 // Preparation of a launch of the training kernel: gate lists per class, launch order of the clauses.
-// Part of the one translation unit tm_kernels.hip (included there, in this order).
+// Part of tm_kernels.hip (included there).
 #ifndef TM_KERNELS_PREP_HPP_
 #define TM_KERNELS_PREP_HPP_
 

@@ -1,5 +1,5 @@
 // The training kernel: Algorithm 1, one wavefront per clause.
-// Part of the one translation unit tm_kernels.hip (included there, in this order).
+// Included by tm_train_launch.hpp; its forms are compiled in tm_train_part.hip.
 #ifndef TM_KERNELS_TRAIN_HPP_
 #define TM_KERNELS_TRAIN_HPP_
 

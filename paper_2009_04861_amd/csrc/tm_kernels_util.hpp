@@ -1,6 +1,6 @@
 // Small kernels around the main ones: fills, state conversion, transposes, label check,
 // negative class, clamp / argmax, copies.
-// Part of the one translation unit tm_kernels.hip (included there, in this order).
+// Part of tm_kernels.hip (included there).
 #ifndef TM_KERNELS_UTIL_HPP_
 #define TM_KERNELS_UTIL_HPP_
 
