@@ -67,7 +67,7 @@ def type1_ops_per_word(s, nominal=False):
 # time of the profile runs); with other sources `traffic` is reported as null.
 MEASURED_TRAFFIC = {
     "profile": "profiles/image_like_default_benchmark.txt",
-    "kernel_sources_sha256": "2f6c07ba1a52ce29f77e060d7853167bf2e9e7ba9cc4c2e6a12e20eb01c9e675",
+    "kernel_sources_sha256": "2c032bba769bb734239d43b537f00941c4d0f8c2645a7a3eb3c7b01930c8cd71",
     "image_like_train": {"fetch_kib": 50735.6, "fetch_scale": 2.0, "write_kib": 32042.3, "write_scale": 1.0},
     # k_eval_sparse in tm_sync_tallies
     "image_like_precalc": {"fetch_kib": 60332.3, "fetch_scale": 2.0, "write_kib": 167613.8, "write_scale": 1.0},

@@ -631,7 +631,12 @@ int launch_train(tm_handle *h, const int32_t *vhat, int64_t i_begin, int64_t i_e
         TM_HIP(h, hipGetLastError());
         int rc = timing_mark(h, TIMED_TRAIN, true, st);
         if (rc) return rc;
-        const bool deep = d.thr != 0 && __builtin_ctz(d.thr) < 8; // the Type I comparison needs more than two Philox blocks
+        // The Type I comparison needs more than two Philox blocks; with one slot and a SIMD per clause every threshold that needs
+        // any takes that form, whose draws a second wavefront makes (kernel
+        // time inline / handed over, s = 2: 90 clauses of 297 features 1.33 / 0.99 ms, 500 of 784 1.31 / 1.21, 1,000 of 784 0.76 / 0.74;
+        // s = 4: 80 of 600 3.6 / 2.6; with closed gates 0.98 to 1.05 of the speed, 1,000 clauses of 500 features 7.2 / 7.6 us)
+        const bool alone = a.slot_hi - a.slot_lo <= 1024;
+        const bool deep = d.thr != 0 && (__builtin_ctz(d.thr) < 8 || (d.thr < 65536u && wpl <= 1 && alone));
         if (!launch_train_slots(wpl, narrow, deep, a.slot_hi - a.slot_lo, p, a, full, st)) return TM_ELIMIT;
         TM_HIP(h, hipGetLastError());
         rc = timing_mark(h, TIMED_TRAIN, false, st);

@@ -235,7 +235,7 @@ constexpr int TRAIN_WAVES_MAX = 4; // most clauses (wavefronts) per workgroup of
 // one another up to 10, 16 slower (LDS).
 __host__ __device__ constexpr int train_draw_events(int wpl) { return wpl == 1 ? 8 : wpl == 2 ? 4 : wpl <= 4 ? 2 : 1; }
 constexpr int DRAW_RING = 128; // words of literals waiting for their last two blocks: at most 31 left over and 64 new ones
-// Launches of one wavefront per SIMD, one slot, DEEP: a second wavefront of the workgroup draws the gates and the Type I
+// Launches of one wavefront per SIMD, one slot, DEEP (which takes every threshold then): a second wavefront of the workgroup draws the gates and the Type I
 // events of a round of 64 gate entries while the first works through the round before.  A wavefront alone on its SIMD
 // leaves two thirds of the issue slots empty, and its time is the length of its own chain, of which the draws are almost half.
 // The two meet at one barrier per round; what is handed over lies in LDS twice.  Time before / now: 1,000 clauses of 784
