@@ -128,7 +128,8 @@ int tm_bind_train(tm_handle *h, const uint32_t *X, const int32_t *y, int64_t q, 
  * one other class, drawn per (epoch, example), towards 0.  The pass is cut into
  * launches (tm_train_chunk); an example whose error e is 0 under the tally as
  * it stands at the start of its launch (gate probability 0) is not visited for
- * feedback in that launch, all others are gated on the tally read at the visit.
+ * feedback in that launch, all others are gated on the live tally, which a
+ * clause reads in rounds of 64 such examples of its class, one round ahead.
  * Advances the handle's epoch counter (part of the random counter) by one. */
 int tm_fit_epoch(tm_handle *h, void *stream);
 

@@ -718,8 +718,11 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
     };
 
     // Candidate data are fetched ahead: entry words two candidate blocks ahead, tallies (which
-    // need the entry's example index) one block ahead.  Reading a tally early is within the
-    // method's premise of outdated tallies.
+    // need the entry's example index) one block ahead of the visit.  Reading a tally early is within the
+    // method's premise of outdated tallies.  The helper draws a round while the one before is worked through, so it reads
+    // tallies when it draws and not a round before that: the older they are, the further machines swing in which all clauses step
+    // together (live regression, 800 clauses of 400 features, s = 1.5, one launch: mean error 0.33 of T with tallies two rounds
+    // ahead of the visit, 0.08 with one).
     auto load_ent = [&](int k0) { // packed (example << 1 | target), or -1 beyond the range
         const int k = k0 + lane;
         return k < k_hi ? list[k] : -1;
@@ -813,14 +816,16 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
         }
     };
     int ent_cur = load_ent(k_lo);
-    int v_cur = load_v(ent_cur);
+    int v_cur = TEAM ? 0 : load_v(ent_cur);
     int y_cur = load_y(ent_cur);
     int ent_nxt = load_ent(k_lo + 64);
 
     auto draw_gates = [&](int k0, int &iv, uint64_t &fmask, uint64_t &tmask) { // the round of gate entries from k0 on
-        const int ent = ent_cur, v = v_cur, yv = y_cur;
+        const int ent = ent_cur, yv = y_cur;
+        int v = v_cur;
         ent_cur = ent_nxt;
-        v_cur = load_v(ent_cur);
+        if constexpr (TEAM) v = load_v(ent);
+        else v_cur = load_v(ent_cur);
         y_cur = load_y(ent_cur);
         ent_nxt = load_ent(k0 + 128);
         if constexpr (NARROW) { // everything requested so far arrives here, ahead of the atomics

@@ -254,6 +254,31 @@ def test_training_error_against_the_oracle(device):
     assert g <= c + 0.02 * T, (mg, mc, base)
 
 
+@pytest.mark.parametrize("n,share", [(800, 1.0), (1000, 0.6)])
+def test_regression_error_with_all_clauses_in_one_launch(n, share, device):
+    """Live epochs of 257 to 1,024 features with at most 1,024 clauses, all side by side: the clauses step through the examples
+    together, and how far their outputs swing depends on how old the tallies are that they gate on.  800 clauses must beat the best
+    constant predictor, 1,000 reach 0.6 of its error (what the workload at its full size is held to); with tallies read a round
+    of 64 gates earlier the errors are 2.3 and 0.63 to 0.8 of it, with those read one round ahead 0.6 and 0.4."""
+    Xtr, ytr, Xte, yte = synth.regression_like(8000, 2000, features=25, thresholds=16, T=n, seed=77)
+    base = float(np.abs(yte - np.median(ytr)).mean())
+    mean = []
+    for seed in (1, 2, 3):
+        gpu = B.TsetlinMachine(1, n, Xtr.shape[1], 128, n, 1.5, seed, regression=True)
+        gpu.bind_train(dev_bits(gpu, Xtr), dev_i32(gpu, ytr))
+        Xd = dev_bits(gpu, Xte)
+        errs = []
+        for ep in range(20):
+            gpu.fit_epoch()
+            if ep >= 10:
+                errs.append(np.abs(gpu.predict(Xd).cpu().numpy() - yte).mean())
+        mean.append(float(np.mean(errs)))
+        gpu.close()
+    print("live regression, %d clauses in one launch: late mean absolute errors %s of T = %d, constant predictor %.1f"
+          % (n, mean, n, base), flush=True)
+    assert np.mean(mean) < share * base
+
+
 def test_regression_workload_full_size_sampled_clauses(device):
     """The regression workload at its full size (13,911 x 256 bits, 1,280 clauses, T = 1,280, s = 1.5):
     sampled clauses and examples against the oracle, then asynchronous epochs with all clauses in
