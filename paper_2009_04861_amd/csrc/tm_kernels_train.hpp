@@ -780,9 +780,10 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
     // between rare changes, go through the entry list.  Measured, before / now: 3,328 documents on 20,000 clauses of 10,000
     // features (116 entries) 34.0 / 24.3 ms; 1,600 on 1,000 clauses of them 1.93 / 1.20 ms; 832 on 16,000 of 20,000 features
     // 34.9 / 22.8 ms.  With 2 slots the entries are too few (14 to 20: 0.91 to 0.98 of the speed); with 3 slots it pays only
-    // with a threshold of many blocks, where events take longer (s = 5 1.14 to 1.30, s = 2 0.89 to 0.98), and not in
-    // regression (0.92).
-    constexpr bool DIRECT = WPL >= 4 || (WPL == 3 && DEEP && !REGR);
+    // with a threshold of many blocks, where events take longer (s = 5 1.14 to 1.30, s = 2 0.89 to 0.98).  Never in regression,
+    // whose masks change less often (speed with it / without, 4 to 10 slots, 60 to 5,000 clauses: s = 2 0.78 to 0.92 / 0.95 to 1.06 of the block
+    // by block version before, s = 1.5 and 5 0.85 to 1.09 / 0.94 to 1.15).
+    constexpr bool DIRECT = !REGR && (WPL >= 4 || (WPL == 3 && DEEP));
     constexpr int DIRECT_ENTRIES = 12; // entries that cost a block about the latency of one example taken directly
     constexpr int DIRECT_CALM = 3;  // active events without a change after which changes count as rare
     bool hot = false;               // changes are frequent
