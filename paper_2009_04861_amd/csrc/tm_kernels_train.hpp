@@ -2,6 +2,7 @@
 // Included by tm_train_launch.hpp; its forms are compiled in tm_train_part.hip.
 #ifndef TM_KERNELS_TRAIN_HPP_
 #define TM_KERNELS_TRAIN_HPP_
+#include <type_traits>
 
 namespace tsetlin {
 
@@ -784,9 +785,14 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
     // whose masks change less often (speed with it / without, 4 to 10 slots, 60 to 5,000 clauses: s = 2 0.78 to 0.92 / 0.95 to 1.06 of the block
     // by block version before, s = 1.5 and 5 0.85 to 1.09 / 0.94 to 1.15).
     constexpr bool DIRECT = !REGR && (WPL >= 4 || (WPL == 3 && DEEP));
+    // LATER: the outputs after a change, and those of a block just opened, are taken when the next event or the end of the
+    // block needs them, whether changes are frequent or not: then every mask change goes one way.  Above 10 slots, where the registers of
+    // the example would have to be kept through the update, the update gathers the violated literals and calm blocks are
+    // evaluated at once.
+    constexpr bool LATER = WPL <= 10;
     constexpr int DIRECT_ENTRIES = 12; // entries that cost a block about the latency of one example taken directly
     constexpr int DIRECT_CALM = 3;  // active events without a change after which changes count as rare
-    bool hot = false;               // changes are frequent
+    std::conditional_t<LATER, int, bool> hot = 0; // changes are frequent
     int known = 64, calm = DIRECT_CALM + 1;
     auto direct_output = [&](const uint32_t (&x)[NX]) { // output of the clause on the example whose words are x
         uint32_t viol = 0u;
@@ -803,8 +809,8 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
     uint32_t gap_row[NX]; // words of an example between two events, requested ahead
     int gap_example = -1;
     auto below = [](int bit) { return bit < 64 ? (1ull << bit) - 1ull : ~0ull; };
-    auto know = [&](int upto) { // outputs of the open block below `upto`, with the current masks
-        if (known >= upto) return;
+    auto know = [&](int upto) { // outputs of the open block below `upto`, or all of them, with the current masks
+        if (!LATER && known >= upto) return;
         if (!hot || (upto - known - 1) * DIRECT_ENTRIES > nent) {
             obits = (obits & below(known)) | (list_outputs(cb) & ~below(known));
             known = 64;
@@ -936,7 +942,10 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
                     }
                 }
                 if (cb >= 0) {
-                    if constexpr (DIRECT) know(min(64, i_end - (cb << 6)));
+                    if constexpr (DIRECT) {
+                        const int end = min(64, i_end - (cb << 6));
+                        if (!LATER || known < end) know(end);
+                    }
                     close_block(cb, obits, ost, rmask, mask_changed);
                     next_block = cb + 1;
                     cb = -1;
@@ -969,7 +978,7 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
                         const uint32_t *op = a.ostar + (int64_t)g * a.Qw + (b0 >> 5);
                         const uint32_t o0 = op[0], o1 = op[1];
                         ost = pack64(o0, o1);
-                        if (DIRECT && hot) {
+                        if (DIRECT && (LATER || hot)) {
                             obits = 0;
                             known = max(0, i_begin - b0);
                         } else {
@@ -986,10 +995,12 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
             const int bl = ii & 63;                  // position of the example in the open block
             const bool tgt = (tmask >> l) & 1;
             if constexpr (DIRECT) {
-                know(bl);
-                if (known == bl) {
-                    if (direct_output(xnext)) obits |= 1ull << bl;
-                    known = bl + 1;
+                if (!LATER || __builtin_expect(known <= bl, 0)) {
+                    know(bl);
+                    if (known == bl) {
+                        if (direct_output(xnext)) obits |= 1ull << bl;
+                        known = bl + 1;
+                    }
                 }
             }
             const bool Cout = (obits >> bl) & 1;     // clause output on the state before the update
@@ -998,7 +1009,13 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
             uint32_t changed = 0, viol = 0; // viol: included literals that are 0, after the update
             uint32_t xw[NX];
 #pragma unroll
-            for (int r = 0; r < NX; ++r) xw[r] = NARROW ? 0u : xnext[r];
+            for (int r = 0; r < NX; ++r) {
+                xw[r] = NARROW ? 0u : xnext[r];
+                // the next example is requested into the registers that this one leaves: where the compiler takes others and
+                // copies them, the copies wait for the request.  200 to 3,000 clauses of 4,000 to 10,000 features,
+                // time with that wait / without: 1.0 to 1.09
+                if (DIRECT && LATER) asm volatile("" : "+v"(xw[r]));
+            }
             if (!NARROW && fmask) {
                 const int next = __builtin_amdgcn_readlane(iv, __builtin_ctzll(fmask));
                 load_row(next, xnext);
@@ -1060,7 +1077,7 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
                     const uint32_t old7 = sp[7];
                     ripple_inc(sp, ~lit & ~old7 & valid); // excluded automata (below the top bit) cannot overflow
                     changed |= sp[7] ^ old7;
-                    if (DIRECT) {
+                    if (DIRECT && !LATER) {
                         viol |= sp[7] & ~lit;
                         asm volatile("" : "+v"(viol));
                     }
@@ -1127,7 +1144,7 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
                     }
                     ripple_updown(sp, up, wk);
                     changed |= sp[7] ^ old7;
-                    if (DIRECT) {
+                    if (DIRECT && !LATER) {
                         viol |= sp[7] & ~lit;
                         asm volatile("" : "+v"(viol));
                     }
@@ -1143,19 +1160,22 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
             }
             const bool moved = ballot(changed != 0u) != 0;
             if constexpr (DIRECT) {
-                if (moved) {
+                if constexpr (LATER) {
+                    hot = moved ? (calm <= DIRECT_CALM ? 1 : 0) : (calm < DIRECT_CALM ? hot : 0);
+                    calm = moved ? 0 : min(calm, DIRECT_CALM) + 1;
+                } else if (moved) {
                     hot = calm <= DIRECT_CALM;
                     calm = 0;
                 } else if (++calm > DIRECT_CALM) {
-                    hot = false;
+                    hot = 0;
                 }
             }
             if (moved) { // the conjunction changed: re-evaluate this and the later examples of the block
                 mask_changed = true;
                 list_ok = false;
                 n_listed = -1;
-                if (DIRECT && hot) {
-                    obits = (obits & below(bl)) | (ballot(viol != 0u) == 0 ? 1ull << bl : 0ull);
+                if (DIRECT && (LATER || hot)) {
+                    obits = (obits & below(bl)) | ((LATER ? direct_output(xw) : ballot(viol != 0u) == 0) ? 1ull << bl : 0ull);
                     known = bl + 1;
                 } else {
                     uint64_t nb;
