@@ -32,7 +32,7 @@ def oracle_epoch_in_launches(ora, X, y, tally, ostar, epoch, chunk):
         ora.async_range(X, y, tally, ostar, epoch, i0, chunk, example_major=False)
 
 
-# (m, n, o, N, T, s, q, density): C <= 40; 1, 1, 3, 5 and 10 register slots per lane; the machines of
+# (m, n, o, N, T, s, q, density): C <= 40; 1, 3, 5 and 10 register slots per lane; the machines of
 # more than 4 slots cut an epoch into several launches (tm_train_chunk), q is chosen above that
 LIVE_SHAPES = [
     (2, 10, 12, 100, 15, 3.9, 700, 0.5),
@@ -41,6 +41,12 @@ LIVE_SHAPES = [
     (5, 2, 4200, 64, 3, 4.0, 4500, 0.2),
     (2, 4, 10000, 128, 3, 2.0, 1800, 0.1),
     (3, 6, 200, 100, 5, 3.9, 700, 0.3),  # seven feature words: narrow, one event per draw, corrections held back
+    # 257 to 1,024 features: a second wavefront reads the live tallies and draws, several rounds of 64 gates per clause;
+    # thresholds of four Philox blocks, of one and of two, a full last lane and a ragged last word
+    (3, 6, 784, 128, 5, 10.0, 700, 0.3),
+    (2, 8, 500, 100, 5, 2.0, 700, 0.3),
+    (3, 6, 1024, 128, 5, 4.0, 500, 0.2),
+    (2, 6, 257, 64, 5, 3.9, 900, 0.3),
 ]
 
 
@@ -94,7 +100,8 @@ def test_live_batches_match_sequential_algorithm1(device):
     gpu.close()
 
 
-@pytest.mark.parametrize("shape", [(24, 40, 20, 24, 1.5, 600), (12, 4200, 128, 12, 2.0, 4300)])
+@pytest.mark.parametrize("shape", [(24, 40, 20, 24, 1.5, 600), (12, 4200, 128, 12, 2.0, 4300),
+                                   (20, 600, 100, 20, 1.5, 900), (16, 300, 128, 16, 2.0, 700)])
 def test_live_regression_epochs_match_sequential_algorithm1(shape, device):
     n, o, N, T, s, q = shape
     print("live regression epochs", shape, flush=True)

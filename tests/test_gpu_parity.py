@@ -452,7 +452,7 @@ def test_set_state_after_bind_then_step_refreshes_everything(device):
         assert np.array_equal(bits_to_u8(gpu.prev_outputs(), q), ostar)
 
 
-@pytest.mark.parametrize("o", [100, 2500, 5000])
+@pytest.mark.parametrize("o", [100, 784, 2500, 5000])
 def test_long_runs_of_outdated_blocks_are_swept_through_literal_lists(o, device):
     """Sparse clauses pushed after bind leave every stored output outdated; few gates can open,
     so the passes refresh long runs of blocks, 2048 examples at a time through the clause's
