@@ -165,8 +165,10 @@ __host__ __device__ constexpr bool train_split(int wpl, bool roomy, bool deep) {
 __host__ __device__ constexpr int train_min_waves(int wpl, bool roomy) { return roomy ? 1 : wpl <= 2 ? 5 : wpl <= 6 ? 4 : wpl <= 10 ? 3 : 2; }
 
 // train_max_waves: roomy forms of 2 and 3 slots are for launches of one wavefront per SIMD; without a ceiling the compiler
-// schedules for five (1,000 clauses of 2,500 features, s = 2: 0.91 of the speed).
-__host__ __device__ constexpr int train_max_waves(int wpl, bool roomy) { return roomy && (wpl == 2 || wpl == 3) ? 2 : 8; }
+// schedules for five (1,000 clauses of 2,500 features, s = 2: 0.91 of the speed).  The roomy form of 4 slots is for up to three
+// wavefronts per SIMD: where registers leave room for a fourth, some SIMDs get four and others two, and the launch takes as long
+// as the fullest (3,000 clauses, s = 2, without a ceiling / with: 3,300 features 752 / 641 us, documents of 3,929 features 758 / 666).
+__host__ __device__ constexpr int train_max_waves(int wpl, bool roomy) { return !roomy ? 8 : wpl == 2 || wpl == 3 ? 2 : wpl == 4 ? 3 : 8; }
 
 // Literals a clause's list in LDS can hold for the sweeps over outdated outputs; clauses
 // with more (untrained ones) are swept block by block with eval64.  Trained clauses of the
