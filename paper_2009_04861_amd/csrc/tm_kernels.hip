@@ -402,11 +402,17 @@ namespace {
 
 // Launches the form for clauses of wpl register slots; false if there is none.  Roomy where a form has it: about one
 // wavefront per SIMD, or none to gain (train_split).
+// One slot: regression beyond a SIMD per clause takes the roomy form without draws made ahead for every threshold (its machines
+// settle at few events per round, which leaves little to share; speed with draws made ahead / this, against the version before
+// there were any: s = 1.5, 1,100 to 2,000 clauses 0.92 / 0.98, 6,000 0.96 / 0.99).  Thresholds of one or two blocks take it up to five clauses
+// per SIMD, as many as it holds; the other one holds six, so that its SIMDs fill unevenly below that (500 features, s = 2, other form / this:
+// 1,600 clauses 0.97 / 1.00, 5,000 0.93 / 1.03; beyond, 6,000 clauses: other form 1.09, held to five wavefronts 0.97).
 bool launch_train_slots(int wpl, bool narrow, bool deep, int clauses, const TrainPtrs &p, const TrainArgs &a, bool full,
                         hipStream_t st)
 {
     if (narrow) return launch_train_form<1, false, false, true>(p, a, full, st), true;
     const bool alone = clauses <= 1024, few = clauses <= 2 * 1024, some = clauses <= 3 * 1024;
+    if (wpl <= 1 && a.d.regr && !alone) return launch_train_form<1, true, false, false>(p, a, full, st), true;
 #define TM_TAKE(most, wpl_, roomy, deep_) \
     if (wpl <= most) return launch_train_form<wpl_, roomy, deep_, false>(p, a, full, st), true
     if (deep) {
@@ -431,15 +437,16 @@ bool launch_train_slots(int wpl, bool narrow, bool deep, int clauses, const Trai
         TM_TAKE(20, 20, false, true);
         return false;
     }
-    if (alone) {
+    if (clauses <= 5 * 1024) {
         TM_TAKE(1, 1, true, false);
-        TM_TAKE(2, 2, false, false);
+    }
+    TM_TAKE(1, 1, false, false);
+    TM_TAKE(2, 2, false, false);
+    if (alone) {
         TM_TAKE(3, 3, true, false);
     }
+    TM_TAKE(3, 3, false, false);
     if (some) {
-        TM_TAKE(1, 1, false, false);
-        TM_TAKE(2, 2, false, false);
-        TM_TAKE(3, 3, false, false);
         TM_TAKE(4, 4, true, false);
         TM_TAKE(6, 6, true, false);
     }
@@ -447,9 +454,6 @@ bool launch_train_slots(int wpl, bool narrow, bool deep, int clauses, const Trai
         TM_TAKE(8, 8, true, false);
         TM_TAKE(10, 10, true, false);
     }
-    TM_TAKE(1, 1, false, false);
-    TM_TAKE(2, 2, false, false);
-    TM_TAKE(3, 3, false, false);
     TM_TAKE(4, 4, false, false);
     TM_TAKE(6, 6, false, false);
     TM_TAKE(8, 8, false, false);

@@ -164,6 +164,10 @@ __device__ __forceinline__ uint64_t eval64(const uint32_t *eoff, const uint2 *em
 __host__ __device__ constexpr bool train_split(int wpl, bool roomy, bool deep) { return roomy || wpl == 4 || (!deep && (wpl == 1 || wpl == 3)); }
 __host__ __device__ constexpr int train_min_waves(int wpl, bool roomy) { return roomy ? 1 : wpl <= 2 ? 5 : wpl <= 6 ? 4 : wpl <= 10 ? 3 : 2; }
 
+// Lowest Philox block that a form without draws made ahead (not DEEP) may have to draw: thresholds of more than two blocks
+// reach it in regression of one slot only (launch_train_slots).
+__host__ __device__ constexpr int train_least_block(int wpl, bool roomy, bool regr) { return wpl == 1 && roomy && regr ? 0 : 2; }
+
 // train_max_waves: roomy forms of 2 and 3 slots are for launches of one wavefront per SIMD; without a ceiling the compiler
 // schedules for five (1,000 clauses of 2,500 features, s = 2: 0.91 of the speed).  The roomy form of 4 slots is for up to three
 // wavefronts per SIMD: where registers leave room for a fourth, some SIMDs get four and others two, and the launch takes as long
@@ -1116,7 +1120,7 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
                         if (r == WPL - 1) ++n_used;
                     } else {
 #pragma unroll
-                        for (int t = 2; t < 4; ++t) {
+                        for (int t = train_least_block(WPL, ROOMY, REGR); t < 4; ++t) {
                             if (t >= first_blk) {
                                 // With one or two slots, key and threshold are laundered as well (above):
                                 // their derived constants (20 round keys, 16 comparator masks) are then

@@ -33,10 +33,13 @@ void launch_train_form(const TrainPtrs &p, TrainArgs a, bool full, hipStream_t s
     const size_t lds = (size_t)a.lds_wave_words * tw * 4;
     const dim3 grid((unsigned)((a.slot_hi - a.slot_lo + tw - 1) / tw)), block(64 * (TEAM ? 2 : tw));
     const bool regr = a.y_regr != nullptr;
+    constexpr bool CLASSES_ONLY = WPL == 1 && !ROOMY && !NARROW; // regression of one slot takes the roomy forms (launch_train_slots)
     if (full && !regr) hipLaunchKernelGGL((k_train<WPL, true, false, ROOMY, NARROW, DEEP>), grid, block, lds, st, p.X, p.XT, p.XB, p.gate, p.ngate, a);
     else if (!regr) hipLaunchKernelGGL((k_train<WPL, false, false, ROOMY, NARROW, DEEP>), grid, block, lds, st, p.X, p.XT, p.XB, p.gate, p.ngate, a);
-    else if (full) hipLaunchKernelGGL((k_train<WPL, true, true, ROOMY, NARROW, DEEP>), grid, block, lds, st, p.X, p.XT, p.XB, p.gate, p.ngate, a);
-    else hipLaunchKernelGGL((k_train<WPL, false, true, ROOMY, NARROW, DEEP>), grid, block, lds, st, p.X, p.XT, p.XB, p.gate, p.ngate, a);
+    else if constexpr (!CLASSES_ONLY) {
+        if (full) hipLaunchKernelGGL((k_train<WPL, true, true, ROOMY, NARROW, DEEP>), grid, block, lds, st, p.X, p.XT, p.XB, p.gate, p.ngate, a);
+        else hipLaunchKernelGGL((k_train<WPL, false, true, ROOMY, NARROW, DEEP>), grid, block, lds, st, p.X, p.XT, p.XB, p.gate, p.ngate, a);
+    }
 }
 
 // The forms there are: F(part, register slots, roomy, deep, narrow)
