@@ -441,10 +441,11 @@ bool launch_train_slots(int wpl, bool narrow, bool deep, int clauses, const Trai
         TM_TAKE(1, 1, true, false);
     }
     TM_TAKE(1, 1, false, false);
-    TM_TAKE(2, 2, false, false);
     if (alone) {
+        TM_TAKE(2, 2, true, false);
         TM_TAKE(3, 3, true, false);
     }
+    TM_TAKE(2, 2, false, false);
     TM_TAKE(3, 3, false, false);
     if (some) {
         TM_TAKE(4, 4, true, false);

@@ -153,7 +153,8 @@ __device__ __forceinline__ uint64_t eval64(const uint32_t *eoff, const uint2 *em
 // of more than two Philox blocks (DEEP) always take one loop: with the draws out of the way two loops gain 2 to 6 % with
 // up to 2,000 clauses and lose 10 to 25 % with 5,000.  Other thresholds, time with one loop divided by time with two:
 //   1 slot: two loops (s = 2: 0.97 of one)
-//   2 slots: one loop (1,000 to 16,000 clauses: 0.96 to 0.97 of two)
+//   2 slots: one loop (1,000 to 16,000 clauses: 0.96 to 0.97 of two), roomy up to a SIMD per clause: nothing laundered, no
+//     floor of five wavefronts (800 clauses of 1,500 features, s = 2: 1,052 / 998 us)
 //   3 slots: two loops (0.93 to 0.99 of one at every clause count)
 //   4 slots: two loops; for many clauses held to four wavefronts by the launch bound (16,000 clauses: 0.90 to 0.97 of the
 //     time with three wavefronts, 0.94 to 0.99 of one loop; 3,000 clauses: 1.18 to 1.27)
@@ -161,7 +162,7 @@ __device__ __forceinline__ uint64_t eval64(const uint32_t *eoff, const uint2 *em
 //   12 to 20 slots: one loop; two would not leave room for two wavefronts
 // train_min_waves: the wavefronts per SIMD that a form is held to.  DEEP, time without the bound divided by time with
 // it: 1 slot (4 wavefronts instead of 5), 20,000 clauses 1.05; 10 slots (2 instead of 3) 1.25.
-__host__ __device__ constexpr bool train_split(int wpl, bool roomy, bool deep) { return roomy || wpl == 4 || (!deep && (wpl == 1 || wpl == 3)); }
+__host__ __device__ constexpr bool train_split(int wpl, bool roomy, bool deep) { return (roomy && (wpl != 2 || deep)) || wpl == 4 || (!deep && (wpl == 1 || wpl == 3)); }
 __host__ __device__ constexpr int train_min_waves(int wpl, bool roomy) { return roomy ? 1 : wpl <= 2 ? 5 : wpl <= 6 ? 4 : wpl <= 10 ? 3 : 2; }
 
 // Lowest Philox block that a form without draws made ahead (not DEEP) may have to draw: thresholds of more than two blocks

@@ -46,7 +46,7 @@ void launch_train_form(const TrainPtrs &p, TrainArgs a, bool full, hipStream_t s
 #define TM_TRAIN_FORMS(F)                                                                                                      \
     F(1, 1, false, false, true) F(1, 1, true, false, false) F(1, 1, false, false, false) F(1, 1, true, true, false)            \
     F(1, 1, false, true, false)                                                                                                \
-    F(2, 2, false, false, false) F(2, 2, true, true, false) F(2, 2, false, true, false)                                        \
+    F(2, 2, true, false, false) F(2, 2, false, false, false) F(2, 2, true, true, false) F(2, 2, false, true, false)                                        \
     F(2, 3, true, false, false) F(2, 3, false, false, false)                                                                   \
     F(3, 3, true, true, false) F(3, 3, false, true, false) F(3, 4, true, false, false) F(3, 4, false, false, false)            \
     F(4, 4, false, true, false) F(4, 6, true, false, false) F(4, 6, false, false, false) F(4, 6, true, true, false)            \

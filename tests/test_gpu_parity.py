@@ -318,7 +318,7 @@ def test_feedback_step_narrow_clauses(o, N, s, regression, device):
 
 
 # most widths have a second form of the update for launches of more clauses than the first form is for (1,024 with thresholds of
-# more than two Philox blocks and with 3 slots, else 5,120 with 1 slot, 3,072 with 4 and 6 slots, 2,048 with 8 and 10);
+# more than two Philox blocks and with 2 and 3 slots, else 5,120 with 1 slot, 3,072 with 4 and 6 slots, 2,048 with 8 and 10);
 # regression of 1 slot draws every block in turn beyond 1,024 clauses.  Examples few
 # enough for the oracle, blocks of 64 crossed by the ranges.
 @pytest.mark.parametrize("m,n,o,N,s,regression", [(2, 1538, 4001, 128, 5.0, False), (2, 1538, 3100, 100, 2.0, False),
@@ -332,7 +332,9 @@ def test_feedback_step_narrow_clauses(o, N, s, regression, device):
                                                   (1, 1026, 2500, 100, 2.0, True),
                                                   (1, 1026, 500, 128, 1.5, True), (1, 1028, 1024, 100, 65536 / 6400, True),
                                                   (1, 1026, 300, 128, 2.0, True), (1, 1026, 300, 100, 1.0, True),
-                                                  (2, 2560, 300, 128, 4.0, False), (2, 2562, 300, 128, 4.0, False)])
+                                                  (2, 2560, 300, 128, 4.0, False), (2, 2562, 300, 128, 4.0, False),
+                                                  (2, 30, 1056, 100, 2.0, False), (2, 514, 1500, 128, 4.0, False),
+                                                  (1, 60, 2048, 128, 2.0, True)])
 def test_feedback_step_in_both_forms_of_a_width(m, n, o, N, s, regression, device):
     print("feedback, forms", m, n, o, N, s, regression, flush=True)
     T, q = n, 70
