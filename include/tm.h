@@ -152,7 +152,9 @@ int tm_predict(tm_handle *h, const uint32_t *X, int64_t q, int32_t *pred, int32_
 
 /* Size in bytes of the workspace of tm_class_sums_ws / tm_predict_ws for q
  * examples (the literals as bit rows over the examples, and the list of
- * included literals of every clause).  Host-only computation. */
+ * included literals of every clause).  It serves calls of that q: fewer examples
+ * can need more (their classes are split into more lists), so ask for the
+ * largest size over the q that a workspace is to serve.  Host-only computation. */
 int tm_infer_ws_bytes(const tm_config *cfg, int64_t q, size_t *out);
 
 /* tm_class_sums / tm_predict with a workspace (device, tm_infer_ws_bytes, 256-

@@ -182,10 +182,11 @@ inline int lit_cap(const Dims &d)
 }
 
 // How k_eval_sparse splits the clauses of a class: over S workgroups (8 wavefronts each, three of
-// them per CU) of `chunk` clauses (a multiple of 16).  About 1,024 workgroups in all, but at least 192
-// clauses per workgroup, or 96 where that leaves CUs without one (zeroing, converting and adding up a workgroup's sums costs as
-// much as walking some hundred clauses; a class in one workgroup needs no adding up at all).  Measured on 10 x 2,000
-// clauses, at least 256 / 192 / 96: 10,000 test examples 68 / 63 / 80 us, 3,000 examples of few literals 40 / 37 / 31;
+// them per CU) of `chunk` clauses (a multiple of 16).  About 1,024 workgroups in all, but at least 192 clauses each before a
+// share is rounded up to whole batches of eight clauses per wavefront (2,000 clauses: 10 shares of 200, that is 8 of 256); at least 96
+// with fewer than 64 workgroups, and with fewer than 256 (CUs) if the class is split already: zeroing, converting and adding up a
+// workgroup's sums costs as much as walking some hundred clauses, and a class in one workgroup needs no adding up at all.  Rounding can leave
+// fewer shares than a split into multiples of 16.  Measured on 10 x 2,000 clauses, at least 256 / 192 / 96: 10,000 test examples 68 / 63 / 80 us, 3,000 examples of few literals 40 / 37 / 31;
 // 25,000 documents on 2 x 10,000 clauses 585 / 575 / 572.  Wavefronts take whole batches of eight clauses where the split
 // allows it (the documents with 272 instead of 256 clauses per workgroup: 628 us).
 // A wavefront walks chunk / SP_WAVES clauses and counts their votes in SP_PLANES bit planes, so a
@@ -600,7 +601,7 @@ int launch_train(tm_handle *h, const int32_t *vhat, int64_t i_begin, int64_t i_e
     a.q = (int32_t)h->q; a.qp = (int32_t)h->qp; a.Qw = (int32_t)h->Qw; a.epoch = h->epoch;
     a.lds_mask_words = (d.W + 3) & ~3;
     a.lds_off_words = (d.Wf + EVAL_PAD + 3) & ~3;
-    a.lds_wave_words = a.lds_mask_words + a.lds_off_words + 2 * ((d.Wf + EVAL_PAD + 1) & ~1) + TRAIN_LIT_MAX + 8;
+    a.lds_wave_words = a.lds_draw_off = 0; // other forms: launch_train_form
     // at most 16 literal words: the version whose feedback events touch neither memory nor LDS lists.  With more than four
     // feature words its draws go one event at a time, which pays only if a comparison needs several Philox blocks (the
     // threshold has a bit below 12 set).  Where no draw is needed at all (s = 1) it draws all the same, which is free only
@@ -639,7 +640,7 @@ int launch_train(tm_handle *h, const int32_t *vhat, int64_t i_begin, int64_t i_e
         // The Type I comparison needs more than two Philox blocks; with one slot and a SIMD per clause every threshold that needs
         // any takes that form, whose draws a second wavefront makes (kernel
         // time inline / handed over, s = 2: 90 clauses of 297 features 1.33 / 0.99 ms, 500 of 784 1.31 / 1.21, 1,000 of 784 0.76 / 0.74;
-        // s = 4: 80 of 600 3.6 / 2.6; with closed gates 0.98 to 1.05 of the speed, 1,000 clauses of 500 features 7.2 / 7.6 us)
+        // s = 4: 80 of 600 3.6 / 2.6; with closed gates it loses up to 5 %: 1,000 clauses of 500 features 7.2 / 7.6 us)
         const bool alone = a.slot_hi - a.slot_lo <= 1024;
         const bool deep = d.thr != 0 && (__builtin_ctz(d.thr) < 8 || (d.thr < 65536u && wpl <= 1 && alone));
         if (!launch_train_slots(wpl, narrow, deep, a.slot_hi - a.slot_lo, p, a, full, st)) return TM_ELIMIT;

@@ -39,8 +39,8 @@ struct TrainArgs {
 // another, lw = 64 r + lane, which wastes no lanes where a clause has few of them.
 // What bounds a wide clause is the register file, i.e. how many wavefronts a SIMD holds to hide the latency
 // of each other's multiplies, LDS trips and scalar loads.  With paired slots and the planes of a slot finished in
-// its turn (see the feedback loop) 10 slots take 161 instead of 235 registers (three wavefronts per SIMD instead
-// of two) and 20 slots 256 and 12 spilled ones instead of 462 (two instead of one).  Measured: a batch of 3,328 documents on 20,000
+// its turn (see the feedback loop) 10 slots take 161 to 168 instead of 235 registers (three wavefronts per SIMD instead
+// of two) and 20 slots 256 and 11 (thresholds of one or two Philox blocks) or 25 spilled ones instead of 462 (two instead of one).  Measured: a batch of 3,328 documents on 20,000
 // clauses of 10,000 features 45.2 -> 32.2 ms, 832 examples on 16,384 clauses of 20,000 features 50.8 -> 28.2 ms.
 // Narrow clauses (at most 16 literal words, one slot): lane f holds the plain literals of feature word f, lane 8 + f
 // the negated ones, so that the masks of a feature word sit at fixed lanes.
@@ -150,8 +150,9 @@ __device__ __forceinline__ uint64_t eval64(const uint32_t *eoff, const uint2 *em
 // an event costs a wavefront is least, but the registers of the slots are live together.  Otherwise one loop serves
 // both types (a branch per slot, two more steps of latency), which needs the fewest registers.  Fewer registers are more
 // wavefronts per SIMD, so the second form pays as soon as the launch has wavefronts for them, and only then.  Thresholds
-// of more than two Philox blocks (DEEP) always take one loop: with the draws out of the way two loops gain 2 to 6 % with
-// up to 2,000 clauses and lose 10 to 25 % with 5,000.  Other thresholds, time with one loop divided by time with two:
+// of more than two Philox blocks (DEEP) take two loops where the form is roomy (up to a SIMD per clause) or has 4 slots, else
+// one: with the draws out of the way two loops gain 2 to 6 % with up to 2,000 clauses and lose 10 to 25 % with 5,000.
+// Other thresholds, time with one loop divided by time with two:
 //   1 slot: two loops (s = 2: 0.97 of one)
 //   2 slots: one loop (1,000 to 16,000 clauses: 0.96 to 0.97 of two), roomy up to a SIMD per clause: nothing laundered, no
 //     floor of five wavefronts (800 clauses of 1,500 features, s = 2: 1,052 / 998 us)
@@ -247,7 +248,7 @@ constexpr int DRAW_RING = 128; // words of literals waiting for their last two b
 // events of a round of 64 gate entries while the first works through the round before.  A wavefront alone on its SIMD
 // leaves two thirds of the issue slots empty, and its time is the length of its own chain, of which the draws are almost half.
 // The two meet at one barrier per round; what is handed over lies in LDS twice.  Time before / now: 1,000 clauses of 784
-// features, 60,000 examples 3.76 / 2.85 ms (one wavefront: 3.88 before the draws were made ahead), 90 clauses of 297 features 2.4 / 1.3 ms.
+// features, 60,000 examples 3.81 / 2.69 ms (one wavefront: 3.88 before the draws were made ahead), 90 clauses of 297 features 2.4 / 1.3 ms.
 __host__ __device__ constexpr bool train_team(int wpl, bool roomy, bool deep, bool narrow) { return wpl == 1 && roomy && deep && !narrow; }
 constexpr int TEAM_ROUND = 64 + 8; // words handed over per round beside the draws: examples, masks of fired and target-1 lanes, open gates
 __host__ __device__ constexpr int train_draw_words(int wpl, bool team)
@@ -785,8 +786,10 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
     // stand in the registers: the outputs of the open block are known below position `known`, those of the examples
     // between two events are taken when the second one comes up (the first one's words are requested an event ahead),
     // and after a change the update loop leaves the violated literals of its own example.  Longer runs, and blocks
-    // between rare changes, go through the entry list.  Measured, before / now: 3,328 documents on 20,000 clauses of 10,000
-    // features (116 entries) 34.0 / 24.3 ms; 1,600 on 1,000 clauses of them 1.93 / 1.20 ms; 832 on 16,000 of 20,000 features
+    // between rare changes, go through the entry list.  Where changes are neither frequent nor rare this loses (image-like data of
+    // 3,300 features, s = 2: 0.96 of the speed; planted conjunctions, 5,500 features, s = 2: 0.97 to 1.0; calling changes frequent after one
+    // at the last event or the one before only: 0.97, but s = 5 1.27 instead of 1.32).  Measured, before / now: 3,328 documents on 20,000 clauses of 10,000
+    // features (116 entries) 32.6 / 21.4 ms; 1,600 on 1,000 clauses of them 1.93 / 1.20 ms; 832 on 16,000 of 20,000 features
     // 34.9 / 22.8 ms.  With 2 slots the entries are too few (14 to 20: 0.91 to 0.98 of the speed); with 3 slots it pays only
     // with a threshold of many blocks, where events take longer (s = 5 1.14 to 1.30, s = 2 0.89 to 0.98).  Never in regression,
     // whose masks change less often (speed with it / without, 4 to 10 slots, 60 to 5,000 clauses: s = 2 0.78 to 0.92 / 0.95 to 1.06 of the block

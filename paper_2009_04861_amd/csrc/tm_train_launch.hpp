@@ -24,7 +24,7 @@ void launch_train_form(const TrainPtrs &p, TrainArgs a, bool full, hipStream_t s
         a.lds_draw_off = (a.lds_mask_words + a.lds_off_words + 2 * (a.d.Wf + EVAL_PAD) + 3) & ~3;
         a.lds_wave_words = a.lds_draw_off + (DEEP ? train_draw_words(WPL, TEAM) : 0) + (WPL <= 4 ? TRAIN_LIT_MAX + 8 : 0);
     }
-    // Clauses (wavefronts) per workgroup; the wavefronts of a workgroup do not interact.  Two are best once
+    // Clauses per workgroup: one of two wavefronts (TEAM), else one per wavefront, and these do not interact.  Two are best once
     // every SIMD holds several wavefronts (steady epochs of 20,000 clauses: 0.11 ms per launch against
     // 0.14 ms with four; a workgroup's slots are handed on only when its slowest clause is done).  With about
     // one clause per SIMD four are better: they land on the four SIMDs of a CU, while two workgroups of two
