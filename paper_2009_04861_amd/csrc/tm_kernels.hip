@@ -610,7 +610,7 @@ int launch_train(tm_handle *h, const int32_t *vhat, int64_t i_begin, int64_t i_e
     // 0.97 (20,000 clauses 0.95)
     const bool several = d.thr != 0 && __builtin_ctz(d.thr) < 12, drawn = d.thr != 0 && d.thr < 65536u;
     const bool narrow = d.W <= 16 && (several || (d.Wf <= 4 && (drawn || d.C <= ONE_PER_SIMD)));
-    if (narrow) a.lds_wave_words = 8 * 64 + TRAIN_LIT_MAX + 8; // the words of the open block and the list for the sweeps
+    if (narrow) a.lds_wave_words = 8 * 64 + TRAIN_LIT_MAX + LIT_PAD; // the words of the open block and the list for the sweeps
     a.QW = (int)xb_row_words(h->q);
     const bool full = (d.N == 128);
     const int wpl = (d.W + 63) / 64;

@@ -67,8 +67,8 @@ constexpr int EVAL_PAD = 16; // empty entries after the list: a group may read t
 // offset of that word's row in XT, emask[k] = {mask of plain literals, mask of
 // negated literals}; padded with EVAL_PAD empty entries.  Rebuilt whenever plane 7
 // changes.
-template <int WPL>
-__device__ __forceinline__ int build_entries(const u32x8 (&p)[WPL], uint32_t *lmask, uint32_t *eoff,
+template <int WPL, class Masks>
+__device__ __forceinline__ int build_entries(const Masks &m7, uint32_t *lmask, uint32_t *eoff,
                                              uint2 *emask, int lane, int Wf, int W, uint32_t row_bytes)
 {
     int n = 0;
@@ -84,12 +84,12 @@ __device__ __forceinline__ int build_entries(const u32x8 (&p)[WPL], uint32_t *lm
     };
     if constexpr (SlotMap<WPL>::PAIRED) { // both masks of a feature word sit in one lane (0 where the lane holds no word)
 #pragma unroll
-        for (int k = 0; k < WPL / 2; ++k) append(k * 64 + lane, p[2 * k][7], p[2 * k + 1][7]);
+        for (int k = 0; k < WPL / 2; ++k) append(k * 64 + lane, m7(2 * k), m7(2 * k + 1));
     } else {
 #pragma unroll
         for (int r = 0; r < WPL; ++r) {
             const int lw = r * 64 + lane;
-            if (lw < W) lmask[lw] = p[r][7];
+            if (lw < W) lmask[lw] = m7(r);
         }
         wave_lds_sync();
         for (int f0 = 0; f0 < Wf; f0 += 64) {
@@ -116,11 +116,10 @@ __device__ __forceinline__ int build_entries(const u32x8 (&p)[WPL], uint32_t *lm
 // spills 60: 832 examples on 16,384 clauses of 20,000 features 27.2 against 28.5 ms.
 __host__ __device__ constexpr int eval_group(int wpl) { return wpl > 10 ? 8 : 16; }
 
-template <int WPL>
+template <int WPL, int GROUP = eval_group(WPL)>
 __device__ __forceinline__ uint64_t eval64(const uint32_t *eoff, const uint2 *emask, int nent,
                                            const uint32_t *__restrict__ xt_block, int lane)
 {
-    constexpr int GROUP = eval_group(WPL);
     uint32_t viol = 0;
     const char *base = reinterpret_cast<const char *>(xt_block);
     const uint32_t lane4 = (uint32_t)lane * 4u;
@@ -182,17 +181,18 @@ __host__ __device__ constexpr int train_max_waves(int wpl, bool roomy) { return 
 // 30 epochs and past 128 within 100 (always-true negated literals of pixels that are never set
 // cost nothing to include); block by block such a clause took 0.45 ms alone when it changed.
 constexpr int TRAIN_LIT_MAX = 256;
+constexpr int LIT_PAD = 16;     // entries of the all-ones row after the list
 constexpr int SWEEP_WORDS = 2; // words of 32 examples per lane and pass of a sweep through the literal list
 
 // Number of included literals of the clause held in p: the per-lane counts are summed bit by
 // bit with ballots, a loop-free wave sum.  (An atomic add on one LDS word would do, but the
 // compiler expands it into a 64-step scalar loop over the lanes.)
-template <int WPL>
-__device__ __forceinline__ int count_literals(const u32x8 (&p)[WPL])
+template <int WPL, class Masks>
+__device__ __forceinline__ int count_literals(const Masks &m7)
 {
     uint32_t cnt = 0;
 #pragma unroll
-    for (int r = 0; r < WPL; ++r) cnt += (uint32_t)__builtin_popcount(p[r][7]); // 0 where a lane holds no word
+    for (int r = 0; r < WPL; ++r) cnt += (uint32_t)__builtin_popcount(m7(r)); // 0 where a lane holds no word
     int total = 0;
 #pragma unroll
     for (int bit = 0; bit < 8; ++bit) // cnt <= 32 * WPL <= 128 for the narrow clauses this is used for
@@ -201,13 +201,13 @@ __device__ __forceinline__ int count_literals(const u32x8 (&p)[WPL])
 }
 
 // List of the included literals of the clause held in p (lane = literal word), as byte
-// offsets of their rows in XB, padded to a multiple of 8 with the all-ones row; returns
+// offsets of their rows in XB, padded to a multiple of LIT_PAD with the all-ones row; returns
 // the number of included literals.  Only called for clauses with at most TRAIN_LIT_MAX.
 // The order of the list does not matter (the output is their conjunction): a round takes one
 // literal of every word that has one left, compacted over the lanes by ballot, so that a slot costs
 // as many rounds as its fullest word has literals.
-template <int WPL, bool NARROW>
-__device__ __forceinline__ int build_literals(const u32x8 (&p)[WPL], uint32_t *llist, int lane, int Wf, int o,
+template <int WPL, bool NARROW, class Masks>
+__device__ __forceinline__ int build_literals(const Masks &m7, uint32_t *llist, int lane, int Wf, int o,
                                               uint32_t xb_row_bytes)
 {
     int base = 0;
@@ -215,7 +215,7 @@ __device__ __forceinline__ int build_literals(const u32x8 (&p)[WPL], uint32_t *l
     for (int r = 0; r < WPL; ++r) {
         int lw = SlotMap<WPL, NARROW>::word(r, lane, Wf);
         asm volatile("" : "+v"(lw)); // recomputed here, not kept for every slot
-        uint32_t m = p[r][7]; // 0 where the lane holds no word
+        uint32_t m = m7(r); // 0 where the lane holds no word
         const uint32_t k0 = lw >= Wf ? (uint32_t)o + (uint32_t)(lw - Wf) * 32u : (uint32_t)lw * 32u; // literal of bit 0
         for (uint64_t bal; (bal = ballot(m != 0u)) != 0;) { // one literal of every word that has one left
             const int pos = base + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
@@ -224,7 +224,7 @@ __device__ __forceinline__ int build_literals(const u32x8 (&p)[WPL], uint32_t *l
             base += __builtin_popcountll(bal);
         }
     }
-    if (lane < 8) llist[min(base, TRAIN_LIT_MAX) + lane] = 2u * (uint32_t)o * xb_row_bytes;
+    if (lane < LIT_PAD) llist[min(base, TRAIN_LIT_MAX) + lane] = 2u * (uint32_t)o * xb_row_bytes;
     wave_lds_sync();
     return base;
 }
@@ -244,16 +244,30 @@ constexpr int TRAIN_WAVES_MAX = 4; // most clauses (wavefronts) per workgroup of
 // one another up to 10, 16 slower (LDS).
 __host__ __device__ constexpr int train_draw_events(int wpl) { return wpl == 1 ? 8 : wpl == 2 ? 4 : wpl <= 4 ? 2 : 1; }
 constexpr int DRAW_RING = 128; // words of literals waiting for their last two blocks: at most 31 left over and 64 new ones
-// Launches of one wavefront per SIMD, one slot, DEEP (which takes every threshold then): a second wavefront of the workgroup draws the gates and the Type I
-// events of a round of 64 gate entries while the first works through the round before.  A wavefront alone on its SIMD
-// leaves two thirds of the issue slots empty, and its time is the length of its own chain, of which the draws are almost half.
-// The two meet at one barrier per round; what is handed over lies in LDS twice.  Time before / now: 1,000 clauses of 784
-// features, 60,000 examples 3.81 / 2.69 ms (one wavefront: 3.88 before the draws were made ahead), 90 clauses of 297 features 2.4 / 1.3 ms.
+// Launches of one wavefront per SIMD, one slot, DEEP (which takes every threshold then): other wavefronts of the workgroup draw the
+// gates and the Type I events of a round of gate entries while the first works through the round before.  A wavefront alone on its
+// SIMD leaves two thirds of the issue slots empty, and its time is the length of its own chain, of which the draws are almost half.
+// They meet at one barrier per round; what is handed over lies in LDS twice.
+// Four wavefronts with train_spans, two with train_clause.
 __host__ __device__ constexpr bool train_team(int wpl, bool roomy, bool deep, bool narrow) { return wpl == 1 && roomy && deep && !narrow; }
-constexpr int TEAM_ROUND = 64 + 8; // words handed over per round beside the draws: examples, masks of fired and target-1 lanes, open gates
-__host__ __device__ constexpr int train_draw_words(int wpl, bool team)
+// Forms that come with train_spans as well, for classification; 2 slots with many clauses and DEEP are faster without (0.88 to
+// 0.92 of the speed with, 8,000 clauses of 1,500 features).
+__host__ __device__ constexpr bool train_has_spans(int wpl, bool roomy, bool deep, bool narrow)
 {
-    return 4 * DRAW_RING + 64 * wpl * (team ? 2 * 64 : train_draw_events(wpl)) + (team ? 2 * TEAM_ROUND : 0);
+    return wpl <= 3 && !narrow && !(wpl == 2 && deep && !roomy);
+}
+// Least gate entries per class and launch, as the host expects them (every gate open), for which they take it.  Short launches mean
+// young machines, whose masks change at every second or third event, and then an open block is the cheaper place for the outputs.
+// Speed with spans, by expected entries (200 to 5,000 clauses per class of 400 to 2,500 features, s = 2 and 10): 400 0.85 to 0.97, 800 0.93
+// to 1.05, 1,600 1.0 to 1.3, 4,000 1.06 to 1.4, 8,000 1.1 to 1.8; teams 400 0.98, 800 1.05, 1,600 1.16 to 1.4; two slots and DEEP 1,600 0.97, 4,000 1.03.
+__host__ __device__ constexpr int train_spans_from(int wpl, bool roomy, bool deep) { return train_team(wpl, roomy, deep, false) ? 800 : wpl == 2 && deep ? 3000 : 1500; }
+constexpr int TEAM_ROUND = 32;     // gate entries per round
+constexpr int TEAM_DRAWERS = 2;    // wavefronts that draw Type I events
+constexpr int TEAM_HANDED = 36;    // words handed over per round beside rows and draws
+constexpr int PAIR_ROUND = 64 + 8; // words handed over per round of 64 entries: examples, masks of fired and target-1 lanes, open gates
+__host__ __device__ constexpr int train_draw_words(int wpl, bool team) // without spans
+{
+    return 4 * DRAW_RING + 64 * wpl * (team ? 2 * 64 : train_draw_events(wpl)) + (team ? 2 * PAIR_ROUND : 0);
 }
 
 // A clause whose class has many open gates in this launch is all but certain to get feedback: its
@@ -261,6 +275,25 @@ __host__ __device__ constexpr int train_draw_words(int wpl, bool team)
 // keeps alive cost the feedback-bound regime 3-10 %).  With few open gates - a trained machine - most
 // clauses get none, and the lazy version saves moving their automata (16 % of a quiet epoch).
 constexpr int TRAIN_EAGER_CANDIDATES = 256;
+
+// Event counters of one clause: 64 interleaved sets, because thousands of wavefronts ending at the
+// same time on one address serialise in the L2 atomic unit (measured: ~1.7 ms per launch)
+__device__ __forceinline__ void store_counters(const TrainArgs &a, int g, int lane, uint32_t n_listed_blocks, uint32_t n_fired,
+                                               uint32_t n_type1, uint32_t n_changes, uint32_t n_type2, uint32_t n_eval,
+                                               uint32_t n_draw, bool moved)
+{
+    if (lane < 10) { // slot 4 (trained pairs) is counted by the launch preparation; slot 8: examples this clause
+                     // walked; slot 9: 1 if its automata were fetched (and written back)
+        const uint32_t v = lane == 0 ? n_listed_blocks : lane == 1 ? n_fired : lane == 2 ? n_type1 : lane == 3 ? n_changes
+                         : lane == 4 ? 0u : lane == 5 ? n_type2 : lane == 6 ? n_eval : lane == 7 ? n_draw
+                         : lane == 8 ? (uint32_t)(a.i_end - a.i_begin) : (moved ? 1u : 0u);
+        if (v) atomicAdd(&a.counters[(g & (COUNTER_SETS - 1)) * COUNTER_WIDTH + lane], (unsigned long long)v);
+    }
+}
+
+} // namespace tsetlin
+#include "tm_kernels_train_spans.hpp"
+namespace tsetlin {
 
 // One wavefront = one clause of class c.  The examples whose gate can open for this
 // clause are those of the gate list of c for this launch (label c: trained towards 1;
@@ -283,7 +316,7 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
     uint32_t *lmask = lds + (TEAM ? 0 : wave) * a.lds_wave_words; // [W] include masks, literal-word order
     uint32_t *eoff = lmask + a.lds_mask_words;              // [Wf + EVAL_PAD] (rounded to 4 words)
     uint2 *emask = reinterpret_cast<uint2 *>(eoff + a.lds_off_words);
-    uint32_t *llist = lmask + a.lds_wave_words - (TRAIN_LIT_MAX + 8); // [TRAIN_LIT_MAX + 8] literal list for the sweeps
+    uint32_t *llist = lmask + a.lds_wave_words - (TRAIN_LIT_MAX + LIT_PAD); // [TRAIN_LIT_MAX + LIT_PAD] literal list for the sweeps
 
     const int c = g / d.n;
     constexpr bool regr = REGR;                   // regression mode: every clause votes +1 (a compile-time
@@ -331,10 +364,11 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
         have_planes = true;
     };
     if ((!LAZY || k_hi >= TRAIN_EAGER_CANDIDATES) && !helper) load_planes();
+    auto masks_now = [&](int r) { return p[r][7]; };
     int nent = 0;
     bool list_ok = true; // the entries are those of the current masks
     if constexpr (!NARROW) {
-        if (!helper) nent = build_entries<WPL>(p, lmask, eoff, emask, lane, d.Wf, d.W, row_bytes);
+        if (!helper) nent = build_entries<WPL>(masks_now, lmask, eoff, emask, lane, d.Wf, d.W, row_bytes);
     }
 
     // Narrow clauses.  An epoch of so small a machine is the chain of one clause's feedback events and block
@@ -681,7 +715,7 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
     };
     auto list_outputs = [&](int b) { // outputs of the clause on block b from the entries, rebuilt if the masks changed
         if (!list_ok) {
-            nent = build_entries<WPL>(p, lmask, eoff, emask, lane, d.Wf, d.W, row_bytes);
+            nent = build_entries<WPL>(masks_now, lmask, eoff, emask, lane, d.Wf, d.W, row_bytes);
             list_ok = true;
         }
         return eval64<WPL>(eoff, emask, nent, XT + (b << 6), lane);
@@ -701,8 +735,8 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
         // clauses (their registers hold the automata) and untrained ones (hundreds of literals).
         if (WPL <= 4 && n_blocks >= (n_listed < 0 ? 8 : 3)) {
             if (n_listed < 0) {
-                n_listed = count_literals<WPL>(p);
-                if (n_listed <= TRAIN_LIT_MAX) build_literals<WPL, NARROW>(p, llist, lane, d.Wf, d.o, (uint32_t)a.QW * 4u);
+                n_listed = count_literals<WPL>(masks_now);
+                if (n_listed <= TRAIN_LIT_MAX) build_literals<WPL, NARROW>(masks_now, llist, lane, d.Wf, d.o, (uint32_t)a.QW * 4u);
             }
             if (n_listed <= TRAIN_LIT_MAX) {
                 if (s1 < e1) sweep_listed(s1, e1);
@@ -881,7 +915,7 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
         n_draw += __builtin_popcountll(ballot(open));
         n_fired += __builtin_popcountll(fmask);
     };
-    uint32_t *handed = draws + 2 * 64 * WPL * 64; // TEAM: [round parity][TEAM_ROUND]
+    uint32_t *handed = draws + 2 * 64 * WPL * 64;
     if constexpr (TEAM) {
         if (helper) { // round k + 1 is drawn between barriers k and k + 1, in which the first wavefront works through round k
             for (int k0 = k_lo; k0 < k_hi; k0 += 64) {
@@ -889,7 +923,7 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
                 int iv = 0;
                 uint64_t fmask = 0, tmask = 0;
                 draw_gates(k0, iv, fmask, tmask);
-                uint32_t *h = handed + parity * TEAM_ROUND;
+                uint32_t *h = handed + parity * PAIR_ROUND;
                 h[lane] = (uint32_t)iv;
                 if (lane < 5)
                     h[64 + lane] = lane == 0 ? (uint32_t)fmask : lane == 1 ? (uint32_t)(fmask >> 32) : lane == 2 ? (uint32_t)tmask
@@ -908,7 +942,7 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
         if (!last) {
             if constexpr (TEAM) {
                 __syncthreads();
-                const uint32_t *h = handed + ((k0 >> 6) & 1) * TEAM_ROUND;
+                const uint32_t *h = handed + ((k0 >> 6) & 1) * PAIR_ROUND;
                 iv = (int)h[lane];
                 fmask = pack64(h[64], h[65]);
                 tmask = pack64(h[66], h[67]);
@@ -1217,18 +1251,10 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
     }
     for (int sh = 32; sh > 0; sh >>= 1) n_changes_v += __shfl_xor(n_changes_v, sh, 64);
     n_changes += n_changes_v;
-    // event counters: 64 interleaved sets, because thousands of wavefronts ending at the
-    // same time on one address serialise in the L2 atomic unit (measured: ~1.7 ms per launch)
-    if (lane < 10) { // slot 4 (trained pairs) is counted by the launch preparation; slot 8: examples this clause
-                     // walked; slot 9: 1 if its automata were fetched (and written back)
-        const uint32_t v = lane == 0 ? n_listed_blocks : lane == 1 ? n_fired : lane == 2 ? n_type1 : lane == 3 ? n_changes
-                         : lane == 4 ? 0u : lane == 5 ? n_type2 : lane == 6 ? n_eval : lane == 7 ? n_draw
-                         : lane == 8 ? (uint32_t)(i_end - i_begin) : ((!LAZY || have_planes) ? 1u : 0u);
-        if (v) atomicAdd(&a.counters[(g & (COUNTER_SETS - 1)) * COUNTER_WIDTH + lane], (unsigned long long)v);
-    }
+    store_counters(a, g, lane, n_listed_blocks, n_fired, n_type1, n_changes, n_type2, n_eval, n_draw, !LAZY || have_planes);
 }
 
-template <int WPL, bool FULL, bool REGR, bool ROOMY, bool NARROW, bool DEEP>
+template <int WPL, bool FULL, bool REGR, bool ROOMY, bool NARROW, bool DEEP, bool SPANS>
 __global__ __launch_bounds__(64 * TRAIN_WAVES_MAX) __attribute__((amdgpu_waves_per_eu(train_min_waves(WPL, ROOMY || NARROW), train_max_waves(WPL, ROOMY)))) void k_train(const uint32_t *__restrict__ X, const uint32_t *__restrict__ XT,
                                                             const uint32_t *__restrict__ XB,
                                                             const int32_t *__restrict__ gate,
@@ -1237,16 +1263,22 @@ __global__ __launch_bounds__(64 * TRAIN_WAVES_MAX) __attribute__((amdgpu_waves_p
     extern __shared__ uint32_t lds[];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    constexpr bool TEAM = train_team(WPL, ROOMY, DEEP, NARROW); // one clause per workgroup of two wavefronts
+    constexpr bool TEAM = train_team(WPL, ROOMY, DEEP, NARROW); // one clause per workgroup
     const int slot = a.slot_lo + (TEAM ? (int)blockIdx.x : (int)(blockIdx.x * (blockDim.x >> 6)) + wave);
-    if (slot >= a.slot_hi) return; // whole wavefront (TEAM: both, and both walk the same rounds with one barrier in each)
-    const bool helper = TEAM && wave != 0;
+    if (slot >= a.slot_hi) return; // whole wavefront (TEAM: all of them, and all walk the same rounds with one barrier in each)
     const int g = __builtin_amdgcn_readfirstlane(a.order[slot]);
     const int k_hi = __builtin_amdgcn_readfirstlane(ngate[g / a.d.n]);
-    // From 6 slots on one version serves both, which loads up front where the gates are many: the check per event is
-    // nothing beside the event, and a quiet pass moves no automata (16,000 clauses of 20,000 features, T = n / 40: 430 -> 300 us)
-    if (WPL <= 4 && k_hi >= TRAIN_EAGER_CANDIDATES) train_clause<WPL, FULL, REGR, false, NARROW, ROOMY, DEEP>(X, XT, XB, gate, k_hi, a, lds, g, lane, wave, helper);
-    else train_clause<WPL, FULL, REGR, true, NARROW, ROOMY, DEEP>(X, XT, XB, gate, k_hi, a, lds, g, lane, wave, helper);
+    const bool many = k_hi >= TRAIN_EAGER_CANDIDATES;
+    if constexpr (SPANS) {
+        if (many) train_spans<WPL, FULL, false, ROOMY, DEEP>(X, XT, XB, gate, k_hi, a, lds, g, lane, wave);
+        else train_spans<WPL, FULL, true, ROOMY, DEEP>(X, XT, XB, gate, k_hi, a, lds, g, lane, wave);
+    } else {
+        // From 6 slots on one version serves both, which loads up front where the gates are many: the check per event is
+        // nothing beside the event, and a quiet pass moves no automata (16,000 clauses of 20,000 features, T = n / 40: 430 -> 300 us)
+        const bool helper = TEAM && wave != 0;
+        if (WPL <= 4 && many) train_clause<WPL, FULL, REGR, false, NARROW, ROOMY, DEEP>(X, XT, XB, gate, k_hi, a, lds, g, lane, wave, helper);
+        else train_clause<WPL, FULL, REGR, true, NARROW, ROOMY, DEEP>(X, XT, XB, gate, k_hi, a, lds, g, lane, wave, helper);
+    }
 }
 
 } // namespace tsetlin

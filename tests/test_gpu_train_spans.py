@@ -1,0 +1,60 @@
+"""GPU parity of the training forms that take clause outputs span by span: clauses of one to three register slots
+in launches of many gate entries, with a wavefront or a team of them per clause.  Exact, against the oracle, on all clauses of
+small machines and on sampled clauses of machines that fill the GPU."""
+import numpy as np
+import pytest
+
+from paper_2009_04861_amd import binding as B
+from tests.helpers import bits_to_u8, dev_bits, dev_i32, gpu_state_as_oracle, make_pair, push_state, sparse_random_state
+
+pytestmark = pytest.mark.gpu
+
+# (m, n, o, N, s, boost): slots at the ends of their widths, thresholds of one Philox block to four, up to a SIMD per
+# clause and more clauses than that (with one slot and one block: more than five per SIMD)
+CASES = [
+    (2, 6, 257, 128, 10.0, False), (2, 6, 1024, 100, 2.0, False), (3, 6, 784, 128, 5.0, True), (2, 6, 500, 128, 1.0, False),
+    (2, 6, 1025, 128, 2.0, False), (2, 6, 2048, 128, 3.9, False), (2, 6, 2049, 128, 2.0, False), (2, 6, 3072, 20, 10.0, False),
+    (2, 520, 300, 128, 10.0, False), (2, 520, 300, 100, 2.0, False), (2, 2600, 264, 128, 4.0, False),
+    (2, 520, 1040, 128, 2.0, False), (2, 520, 2100, 128, 2.0, False), (2, 520, 2100, 100, 3.9, False),
+]
+
+
+@pytest.mark.parametrize("case", CASES)
+def test_long_passes_span_by_span(case, device):
+    m, n, o, N, s, boost = case
+    print(case, flush=True)
+    rng = np.random.default_rng(o)
+    q, T = 3100 if m == 2 else 3700, max(4, n // 2)
+    ora, gpu = make_pair(m, n, o, N, T, s, 77, boost=boost)
+    X = (rng.random((q, o)) < 0.3).astype(np.uint8)
+    y = rng.integers(0, m, size=q).astype(np.int32)
+    if o >= 300:
+        X[:, 8:290] = 0                                       # never set: their negations are always true
+    gpu.bind_train(dev_bits(gpu, X), dev_i32(gpu, y))
+    ids = np.unique(np.r_[0, 1, 2, 3, rng.choice(ora.C, size=min(ora.C, 20), replace=False)]).astype(np.int32)
+    ora.state[:] = sparse_random_state(rng, ora.C, ora.L, N, 2.5 / o)
+    ora.state[0, :] = 1                                        # an empty clause
+    if o >= 300:
+        ora.state[1, o + 8:o + 90] = 2 * N                     # several rounds of the literal list
+        ora.state[2, o + 8:o + 285] = 2 * N                    # more literals than the list holds, all of them true
+        ora.state[2, :8] = 1
+    ora.state[3, :] = rng.integers(1, 2 * N + 1, size=ora.L)   # a young clause: half of all literals
+    push_state(gpu, ora.state)
+    gpu.sync_tallies()
+    ostar = ora.clause_outputs_subset(X, ids)
+    # the second pass closes most gates, so that spans grow beyond what may wait
+    for ep, (i0, cnt, share) in enumerate([(0, q, 1.0), (37, q - 37, 0.01), (0, q - 50, 1.0), (0, q, 0.3)]):
+        snap = np.full((q, m), -T, dtype=np.int32)
+        snap[np.arange(q), y] = T
+        opened = rng.random(q) < share
+        snap[opened] = rng.integers(-T, T + 1, size=(int(opened.sum()), m))
+        B.tm_set_epoch(gpu.h, ep)
+        gpu.feedback_step(dev_i32(gpu, snap), i0, cnt)
+        fired = ora.feedback_step_subset(X, y, snap, ostar, ep, i0, cnt, ids)
+        assert fired > 0
+        assert np.array_equal(gpu_state_as_oracle(gpu)[ids], ora.state[ids]), ep
+        prev = bits_to_u8(gpu.prev_outputs(), q)
+        assert np.array_equal(prev[ids], ostar), ep
+        sign = np.where(np.arange(ora.C) % n % 2 == 1, 1, -1)
+        want = np.stack([sign[c * n:(c + 1) * n] @ prev[c * n:(c + 1) * n].astype(np.int64) for c in range(m)], 1)
+        assert np.array_equal(gpu.tallies().cpu().numpy(), want), ep
