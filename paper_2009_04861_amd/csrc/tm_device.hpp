@@ -137,6 +137,22 @@ __device__ __forceinline__ void wave_lds_sync()
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 __device__ __forceinline__ int lane_id() { return (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)); }
 
+// +1 and -1 in the lanes of the mask m: it goes in as the carry
+__device__ __forceinline__ uint32_t add_lanes(uint32_t v, uint64_t m)
+{
+    uint32_t r;
+    uint64_t carry;
+    asm("v_addc_co_u32_e64 %0, %1, %2, 0, %3" : "=v"(r), "=s"(carry) : "v"(v), "s"(m));
+    return r;
+}
+__device__ __forceinline__ uint32_t sub_lanes(uint32_t v, uint64_t m)
+{
+    uint32_t r;
+    uint64_t borrow;
+    asm("v_subbrev_co_u32_e64 %0, %1, 0, %2, %3" : "=v"(r), "=s"(borrow) : "v"(v), "s"(m));
+    return r;
+}
+
 // ---- bit-sliced Tsetlin automata -------------------------------------------
 // The 2N-state counter of 32 automata is held as 8 bit planes p[0..7] (plane b
 // = bit b of every counter).  The stored value is (state - 1) + (128 - N), so

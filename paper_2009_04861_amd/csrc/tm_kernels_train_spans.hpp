@@ -277,7 +277,7 @@ __device__ __forceinline__ void train_spans(const uint32_t *__restrict__ X, cons
     }
     int n_listed = 0, nent = 0; // literals in the list, entries for eval64
     enum { NOTHING, LIST, ENTRIES } have = NOTHING; // which of them LDS holds, of the present masks
-    uint32_t n_eval = 0, n_listed_blocks = 0, n_changes_v = 0;
+    uint32_t n_eval = 0, n_listed_blocks = 0, n_changes_v = 0; // the first two in examples until they are stored
     const char *xb_base = reinterpret_cast<const char *>(XB);
     uint32_t *ostar_row = a.ostar + (int64_t)g * a.Qw;
     // Examples [lo, hi) from the literal list, 16 loads in flight: two words of 32 examples per lane with eight literals at a
@@ -396,10 +396,9 @@ __device__ __forceinline__ void train_spans(const uint32_t *__restrict__ X, cons
             for (int part = 0; part < 2; ++part) {
                 const int lo = part ? s2 : s1, hi = part ? to : e1;
                 if (lo >= hi) continue;
-                const uint32_t nb = (uint32_t)(((hi + 63) >> 6) - (lo >> 6));
-                n_eval += nb;
+                n_eval += (uint32_t)(hi - lo);
                 if (listed) {
-                    n_listed_blocks += nb;
+                    n_listed_blocks += (uint32_t)(hi - lo);
                     sweep(lo, hi);
                 } else {
                     blocks(lo, hi);
@@ -658,7 +657,7 @@ __device__ __forceinline__ void train_spans(const uint32_t *__restrict__ X, cons
     }
     for (int sh = 32; sh > 0; sh >>= 1) n_changes_v += __shfl_xor(n_changes_v, sh, 64);
     n_changes += n_changes_v;
-    store_counters(a, g, lane, n_listed_blocks, n_fired, n_type1, n_changes, n_type2, n_eval, n_draw, !LAZY || have_planes);
+    store_counters(a, g, lane, (n_listed_blocks + 63) >> 6, n_fired, n_type1, n_changes, n_type2, (n_eval + 63) >> 6, n_draw, !LAZY || have_planes);
 }
 
 } // namespace tsetlin

@@ -41,12 +41,21 @@ void launch_train_form(const TrainPtrs &p, TrainArgs a, bool full, hipStream_t s
     const dim3 grid((unsigned)((a.slot_hi - a.slot_lo + tw - 1) / tw)), block(64 * (team ? (spans ? 2 + TEAM_DRAWERS : 2) : tw));
     constexpr bool CLASSES_ONLY = WPL == 1 && !ROOMY && !NARROW; // regression of one slot takes the roomy forms (launch_train_slots)
     auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, lds, st, p.X, p.XT, p.XB, p.gate, p.ngate, a); };
+    auto choose = [&](auto spans_too, auto tiny) {
+        constexpr bool SPANS = decltype(spans_too)::value;
+        constexpr int TINY = decltype(tiny)::value;
+        if (!regr) return full ? launch(k_train<WPL, true, false, ROOMY, NARROW, DEEP, SPANS, TINY>) : launch(k_train<WPL, false, false, ROOMY, NARROW, DEEP, SPANS, TINY>);
+        if constexpr (!CLASSES_ONLY && !SPANS)
+            return full ? launch(k_train<WPL, true, true, ROOMY, NARROW, DEEP, false, TINY>) : launch(k_train<WPL, false, true, ROOMY, NARROW, DEEP, false, TINY>);
+    };
+    using std::integral_constant;
     if constexpr (HAS_SPANS) {
-        if (spans) return full ? launch(k_train<WPL, true, false, ROOMY, NARROW, DEEP, true>) : launch(k_train<WPL, false, false, ROOMY, NARROW, DEEP, true>);
+        if (spans) return choose(std::true_type{}, integral_constant<int, 0>{});
     }
-    if (!regr) return full ? launch(k_train<WPL, true, false, ROOMY, NARROW, DEEP, false>) : launch(k_train<WPL, false, false, ROOMY, NARROW, DEEP, false>);
-    if constexpr (!CLASSES_ONLY)
-        return full ? launch(k_train<WPL, true, true, ROOMY, NARROW, DEEP, false>) : launch(k_train<WPL, false, true, ROOMY, NARROW, DEEP, false>);
+    if constexpr (NARROW) {
+        if (a.d.Wf <= 1) return choose(std::false_type{}, integral_constant<int, 1>{});
+    }
+    choose(std::false_type{}, integral_constant<int, 0>{});
 }
 
 // The forms there are: F(part, register slots, roomy, deep, narrow)

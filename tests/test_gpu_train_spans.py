@@ -58,3 +58,26 @@ def test_long_passes_span_by_span(case, device):
         sign = np.where(np.arange(ora.C) % n % 2 == 1, 1, -1)
         want = np.stack([sign[c * n:(c + 1) * n] @ prev[c * n:(c + 1) * n].astype(np.int64) for c in range(m)], 1)
         assert np.array_equal(gpu.tallies().cpu().numpy(), want), ep
+
+
+# one feature word, ends of the literal word, both ends of the state range, s = 1; two to eight words, which a team takes
+# in passes this long and the narrow form in short ones
+@pytest.mark.parametrize("m,n,o,N,s", [(2, 10, 1, 128, 2.0), (2, 10, 12, 100, 3.9), (3, 20, 31, 3, 1.0), (2, 40, 32, 128, 25.0), (2, 10, 33, 128, 3.9),
+                                       (3, 6, 64, 20, 2.0), (2, 10, 100, 128, 10.0), (2, 6, 256, 128, 3.9)])
+def test_long_and_short_passes_of_narrow_clauses(m, n, o, N, s, device):
+    print(m, n, o, N, s, flush=True)
+    rng = np.random.default_rng(o)
+    q, T = 2501, max(2, n // 3)
+    ora, gpu = make_pair(m, n, o, N, T, s, 78)
+    X = (rng.random((q, o)) < 0.5).astype(np.uint8)
+    y = ((X[:, 0] ^ X[:, min(1, o - 1)] ^ (rng.random(q) < 0.2)) % m).astype(np.int32)
+    gpu.bind_train(dev_bits(gpu, X), dev_i32(gpu, y))
+    tally, ostar = ora.sync_tallies(X)
+    for ep, (i0, cnt) in enumerate([(0, q), (3, 700), (0, q), (1000, 64), (5, q - 5), (0, q)]):
+        snap = tally.copy()
+        B.tm_set_epoch(gpu.h, ep)
+        gpu.feedback_step(dev_i32(gpu, snap), i0, cnt)
+        ora.feedback_step(X, y, snap, tally, ostar, ep, i0, cnt)
+        assert np.array_equal(gpu_state_as_oracle(gpu), ora.state), ep
+        assert np.array_equal(gpu.tallies().cpu().numpy(), tally), ep
+        assert np.array_equal(bits_to_u8(gpu.prev_outputs(), q), ostar), ep
