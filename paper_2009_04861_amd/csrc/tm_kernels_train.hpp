@@ -326,7 +326,7 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
     // the whole kernel they overflow the scalar registers and come back through readlane, a vector instruction each
     // (20,000 clauses of 784 features: 2 % of a loaded epoch, 7 % of a quiet one).  A wavefront alone on its SIMD waits for
     // the scalar additions instead (90 clauses of 297 features, quiet: 29 us kept, 35 us laundered).
-    constexpr bool LAUNDER = !NARROW && !ROOMY;
+    constexpr bool LAUNDER = TINY > 0 || (!NARROW && !ROOMY);
     const bool pos = ((g - c * d.n) & 1) != 0 || regr; // odd index within the class: positive polarity
     const int sign = pos ? 1 : -1;
     const int T = d.T;
@@ -491,20 +491,29 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
     const uint32_t dr_ctr = 4u * (uint32_t)(dr_f + dr_h * d.Wf) + (uint32_t)dr_t;
     const int dr_src = ((lane >> 3) & 1) * (1 << wps) + (lane & ((1 << wps) - 1)); // draw lane (event 0) of this state lane
     uint32_t ge_ahead = 0u;
+    int t1_done = 0; // TINY: Type I events of the round drawn so far
     int n_ahead = 0; // events drawn ahead and not used yet; they are consecutive Type I events of the round
     auto narrow_draw = [&](uint64_t t1, int iv) { // t1: Type I events of the round still to come, iv: example of each gate lane
         if constexpr (NARROW) {
             const int per_call = 8 >> wps;
             uint32_t ii = 0u;
-            for (n_ahead = 0; n_ahead < per_call && t1; ++n_ahead) {
-                const uint32_t id = readlane((uint32_t)iv, __builtin_ctzll(t1));
-                t1 &= t1 - 1;
-                ii = dr_e == n_ahead ? id : ii;
+            if constexpr (TINY > 0) { // the examples of the round's Type I events lie side by side in LDS
+                n_ahead = min(per_call, __builtin_popcountll(t1));
+                ii = lmask[t1_done + dr_e];
+                t1_done += n_ahead;
+            } else {
+                for (n_ahead = 0; n_ahead < per_call && t1; ++n_ahead) {
+                    const uint32_t id = readlane((uint32_t)iv, __builtin_ctzll(t1));
+                    t1 &= t1 - 1;
+                    ii = dr_e == n_ahead ? id : ii;
+                }
             }
             // Over the four planes of one block the comparison is "the value that went in if the four bits
             // equal those of thr, else decided": two runs of the chain, from 0 and from 1, give what is
             // decided (d0) and where the input passes (d0 ^ d1).
-            const U4 R = draw(d.key, STREAM_TYPE1, dr_ctr, (uint32_t)g, (uint64_t)ii, a.epoch);
+            RngKey key = d.key;
+            if (TINY > 0) asm volatile("" : "+s"(key.seed_lo), "+s"(key.seed_hi)); // the scalar registers are wanted for the masks
+            const U4 R = draw(key, STREAM_TYPE1, dr_ctr, (uint32_t)g, (uint64_t)ii, a.epoch);
             const uint32_t w[4] = {R.x, R.y, R.z, R.w};
             uint32_t d0 = 0u, d1 = ~0u;
 #pragma unroll
@@ -1020,6 +1029,13 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
         uint32_t xnext[NX];
         if (!NARROW && fmask) load_row(__builtin_amdgcn_readlane(iv, __builtin_ctzll(fmask)), xnext);
         n_ahead = n_used = 0;
+        if constexpr (TINY > 0) {
+            const uint64_t t1 = fmask & (pos ? tmask : ~tmask);
+            wave_lds_sync();
+            if ((t1 >> lane) & 1ull) lmask[__builtin_amdgcn_mbcnt_hi((uint32_t)(t1 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)t1, 0u))] = (uint32_t)iv;
+            wave_lds_sync();
+            t1_done = 0;
+        }
 
         for (;;) {
             // next event: a fired candidate, or (after the last candidate) the end of the range
