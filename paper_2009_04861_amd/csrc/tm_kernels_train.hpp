@@ -62,13 +62,17 @@ struct SlotMap {
 
 constexpr int EVAL_PAD = 16; // empty entries after the list: a group may read that far past its end
 
+// Include mask of a register slot: plane 7 of its automata, or the mask itself.
+__device__ __forceinline__ uint32_t include_mask(const u32x8 &planes) { return planes[7]; }
+__device__ __forceinline__ uint32_t include_mask(const uint32_t &mask) { return mask; }
+
 // The clause as the evaluation loop wants it: one entry per feature word whose
 // plain or negated mask word is non-zero, compacted in LDS: eoff[k] = byte
 // offset of that word's row in XT, emask[k] = {mask of plain literals, mask of
 // negated literals}; padded with EVAL_PAD empty entries.  Rebuilt whenever plane 7
 // changes.
-template <int WPL, class Masks>
-__device__ __forceinline__ int build_entries(const Masks &m7, uint32_t *lmask, uint32_t *eoff,
+template <int WPL, class Slot>
+__device__ __forceinline__ int build_entries(const Slot (&p)[WPL], uint32_t *lmask, uint32_t *eoff,
                                              uint2 *emask, int lane, int Wf, int W, uint32_t row_bytes)
 {
     int n = 0;
@@ -84,12 +88,12 @@ __device__ __forceinline__ int build_entries(const Masks &m7, uint32_t *lmask, u
     };
     if constexpr (SlotMap<WPL>::PAIRED) { // both masks of a feature word sit in one lane (0 where the lane holds no word)
 #pragma unroll
-        for (int k = 0; k < WPL / 2; ++k) append(k * 64 + lane, m7(2 * k), m7(2 * k + 1));
+        for (int k = 0; k < WPL / 2; ++k) append(k * 64 + lane, include_mask(p[2 * k]), include_mask(p[2 * k + 1]));
     } else {
 #pragma unroll
         for (int r = 0; r < WPL; ++r) {
             const int lw = r * 64 + lane;
-            if (lw < W) lmask[lw] = m7(r);
+            if (lw < W) lmask[lw] = include_mask(p[r]);
         }
         wave_lds_sync();
         for (int f0 = 0; f0 < Wf; f0 += 64) {
@@ -181,18 +185,18 @@ __host__ __device__ constexpr int train_max_waves(int wpl, bool roomy) { return 
 // 30 epochs and past 128 within 100 (always-true negated literals of pixels that are never set
 // cost nothing to include); block by block such a clause took 0.45 ms alone when it changed.
 constexpr int TRAIN_LIT_MAX = 256;
-constexpr int LIT_PAD = 16;     // entries of the all-ones row after the list
+constexpr int LIT_PAD = 8;       // entries of the all-ones row after the list
 constexpr int SWEEP_WORDS = 2; // words of 32 examples per lane and pass of a sweep through the literal list
 
 // Number of included literals of the clause held in p: the per-lane counts are summed bit by
 // bit with ballots, a loop-free wave sum.  (An atomic add on one LDS word would do, but the
 // compiler expands it into a 64-step scalar loop over the lanes.)
-template <int WPL, class Masks>
-__device__ __forceinline__ int count_literals(const Masks &m7)
+template <int WPL, class Slot>
+__device__ __forceinline__ int count_literals(const Slot (&p)[WPL])
 {
     uint32_t cnt = 0;
 #pragma unroll
-    for (int r = 0; r < WPL; ++r) cnt += (uint32_t)__builtin_popcount(m7(r)); // 0 where a lane holds no word
+    for (int r = 0; r < WPL; ++r) cnt += (uint32_t)__builtin_popcount(include_mask(p[r])); // 0 where a lane holds no word
     int total = 0;
 #pragma unroll
     for (int bit = 0; bit < 8; ++bit) // cnt <= 32 * WPL <= 128 for the narrow clauses this is used for
@@ -201,13 +205,13 @@ __device__ __forceinline__ int count_literals(const Masks &m7)
 }
 
 // List of the included literals of the clause held in p (lane = literal word), as byte
-// offsets of their rows in XB, padded to a multiple of LIT_PAD with the all-ones row; returns
+// offsets of their rows in XB, padded to a multiple of PAD with the all-ones row; returns
 // the number of included literals.  Only called for clauses with at most TRAIN_LIT_MAX.
 // The order of the list does not matter (the output is their conjunction): a round takes one
 // literal of every word that has one left, compacted over the lanes by ballot, so that a slot costs
 // as many rounds as its fullest word has literals.
-template <int WPL, bool NARROW, class Masks>
-__device__ __forceinline__ int build_literals(const Masks &m7, uint32_t *llist, int lane, int Wf, int o,
+template <int WPL, bool NARROW, int PAD = LIT_PAD, class Slot>
+__device__ __forceinline__ int build_literals(const Slot (&p)[WPL], uint32_t *llist, int lane, int Wf, int o,
                                               uint32_t xb_row_bytes)
 {
     int base = 0;
@@ -215,7 +219,7 @@ __device__ __forceinline__ int build_literals(const Masks &m7, uint32_t *llist, 
     for (int r = 0; r < WPL; ++r) {
         int lw = SlotMap<WPL, NARROW>::word(r, lane, Wf);
         asm volatile("" : "+v"(lw)); // recomputed here, not kept for every slot
-        uint32_t m = m7(r); // 0 where the lane holds no word
+        uint32_t m = include_mask(p[r]); // 0 where the lane holds no word
         const uint32_t k0 = lw >= Wf ? (uint32_t)o + (uint32_t)(lw - Wf) * 32u : (uint32_t)lw * 32u; // literal of bit 0
         for (uint64_t bal; (bal = ballot(m != 0u)) != 0;) { // one literal of every word that has one left
             const int pos = base + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
@@ -224,7 +228,7 @@ __device__ __forceinline__ int build_literals(const Masks &m7, uint32_t *llist, 
             base += __builtin_popcountll(bal);
         }
     }
-    if (lane < LIT_PAD) llist[min(base, TRAIN_LIT_MAX) + lane] = 2u * (uint32_t)o * xb_row_bytes;
+    if (lane < PAD) llist[min(base, TRAIN_LIT_MAX) + lane] = 2u * (uint32_t)o * xb_row_bytes;
     wave_lds_sync();
     return base;
 }
@@ -396,23 +400,19 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
         have_planes = true;
     };
     if ((!LAZY || k_hi >= TRAIN_EAGER_CANDIDATES) && !helper) load_planes();
-    auto masks_now = [&](int r) {
-        if constexpr (TINY > 0) { // lane f the plain word f, lane 8 + f the negated one
-            uint32_t m = 0u;
+    auto tiny_mask = [&]() { // lane f the plain word f, lane 8 + f the negated one
+        uint32_t m = 0u;
 #pragma unroll
-            for (int k = 0; k < TW; ++k) {
-                m = lane == k ? (uint32_t)inc64[k] : m;
-                m = lane == 8 + k ? (uint32_t)(inc64[k] >> 32) : m;
-            }
-            return m;
-        } else {
-            return p[r][7];
+        for (int k = 0; k < TW; ++k) {
+            m = lane == k ? (uint32_t)inc64[k] : m;
+            m = lane == 8 + k ? (uint32_t)(inc64[k] >> 32) : m;
         }
+        return m;
     };
     int nent = 0;
     bool list_ok = true; // the entries are those of the current masks
     if constexpr (!NARROW) {
-        if (!helper) nent = build_entries<WPL>(masks_now, lmask, eoff, emask, lane, d.Wf, d.W, row_bytes);
+        if (!helper) nent = build_entries<WPL>(p, lmask, eoff, emask, lane, d.Wf, d.W, row_bytes);
     }
 
     // Narrow clauses.  An epoch of so small a machine is the chain of one clause's feedback events and block
@@ -771,7 +771,7 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
     };
     auto list_outputs = [&](int b) { // outputs of the clause on block b from the entries, rebuilt if the masks changed
         if (!list_ok) {
-            nent = build_entries<WPL>(masks_now, lmask, eoff, emask, lane, d.Wf, d.W, row_bytes);
+            nent = build_entries<WPL>(p, lmask, eoff, emask, lane, d.Wf, d.W, row_bytes);
             list_ok = true;
         }
         return eval64<WPL>(eoff, emask, nent, XT + (b << 6), lane);
@@ -791,8 +791,9 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
         // clauses (their registers hold the automata) and untrained ones (hundreds of literals).
         if (WPL <= 4 && n_blocks >= (n_listed < 0 ? 8 : 3)) {
             if (n_listed < 0) {
-                n_listed = count_literals<WPL>(masks_now);
-                if (n_listed <= TRAIN_LIT_MAX) build_literals<WPL, NARROW>(masks_now, llist, lane, d.Wf, d.o, (uint32_t)a.QW * 4u);
+                if constexpr (TINY > 0) p[0][7] = tiny_mask();
+                n_listed = count_literals<WPL>(p);
+                if (n_listed <= TRAIN_LIT_MAX) build_literals<WPL, NARROW>(p, llist, lane, d.Wf, d.o, (uint32_t)a.QW * 4u);
             }
             if (n_listed <= TRAIN_LIT_MAX) {
                 if (s1 < e1) sweep_listed(s1, e1);
@@ -1400,7 +1401,12 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
     }
     for (int sh = 32; sh > 0; sh >>= 1) n_changes_v += __shfl_xor(n_changes_v, sh, 64);
     n_changes += n_changes_v;
-    store_counters(a, g, lane, n_listed_blocks, n_fired, n_type1, n_changes, n_type2, n_eval, n_draw, !LAZY || have_planes);
+    if (lane < 10) { // as store_counters, written out: called, it costs this kernel scalar registers (1 to 5 % of short launches)
+        const uint32_t v = lane == 0 ? n_listed_blocks : lane == 1 ? n_fired : lane == 2 ? n_type1 : lane == 3 ? n_changes
+                         : lane == 4 ? 0u : lane == 5 ? n_type2 : lane == 6 ? n_eval : lane == 7 ? n_draw
+                         : lane == 8 ? (uint32_t)(i_end - i_begin) : ((!LAZY || have_planes) ? 1u : 0u);
+        if (v) atomicAdd(&a.counters[(g & (COUNTER_SETS - 1)) * COUNTER_WIDTH + lane], (unsigned long long)v);
+    }
 }
 
 template <int WPL, bool FULL, bool REGR, bool ROOMY, bool NARROW, bool DEEP, bool SPANS, int TINY>

@@ -5,6 +5,8 @@
 
 namespace tsetlin {
 
+constexpr int SPAN_LIT_PAD = 16; // entries of the all-ones row after the literal list
+
 // Rows of fired examples that a wavefront takes into LDS at a time.
 __host__ __device__ constexpr int span_rows(int wpl) { return wpl == 1 ? 16 : 8; }
 
@@ -44,7 +46,7 @@ __device__ __forceinline__ void train_spans(const uint32_t *__restrict__ X, cons
     // LDS of the wavefront (TEAM: of the workgroup): what evaluates spans - the literal list or, for clauses of more literals than
     // it holds, entries for eval64 - and then the events of a round, rows and draws.
     uint32_t *lds_w = lds + (TEAM ? 0 : wave) * a.lds_wave_words;
-    uint32_t *llist = lds_w, *lmask = lds_w;   // [TRAIN_LIT_MAX + LIT_PAD]; [W] include masks, literal-word order
+    uint32_t *llist = lds_w, *lmask = lds_w;   // [TRAIN_LIT_MAX + SPAN_LIT_PAD]; [W] include masks, literal-word order
     uint32_t *eoff = lmask + a.lds_mask_words; // [Wf + EVAL_PAD] (rounded to 4 words)
     uint2 *emask = reinterpret_cast<uint2 *>(eoff + a.lds_off_words);
     uint32_t *lds_draw = lds_w + a.lds_draw_off;
@@ -370,20 +372,19 @@ __device__ __forceinline__ void train_spans(const uint32_t *__restrict__ X, cons
             // One block is evaluated from entries: building the list costs as much as that does.
             const bool brief = ((to + 63) >> 6) - (from >> 6) <= 1;
             if (have == NOTHING || (have == ENTRIES && !brief)) {
-                auto masks = [&](int r) { return m7[r]; };
                 bool dense = false; // a word of more than 20 literals: not worth counting
 #pragma unroll
                 for (int r = 0; r < WPL; ++r) dense |= __builtin_popcount(m7[r]) > 20;
                 wave_lds_sync();
                 have = ENTRIES;
                 if (!brief && ballot(dense) == 0) {
-                    n_listed = count_literals<WPL>(masks);
+                    n_listed = count_literals<WPL>(m7);
                     if (n_listed <= TRAIN_LIT_MAX) {
                         have = LIST;
-                        build_literals<WPL, false>(masks, llist, lane, d.Wf, d.o, (uint32_t)a.QW * 4u);
+                        build_literals<WPL, false, SPAN_LIT_PAD>(m7, llist, lane, d.Wf, d.o, (uint32_t)a.QW * 4u);
                     }
                 }
-                if (have == ENTRIES) nent = build_entries<WPL>(masks, lmask, eoff, emask, lane, d.Wf, d.W, (uint32_t)a.qp * 4u);
+                if (have == ENTRIES) nent = build_entries<WPL>(m7, lmask, eoff, emask, lane, d.Wf, d.W, (uint32_t)a.qp * 4u);
             }
             const bool listed = have == LIST;
             // words at the ends of a span may have been written by another lane of this wavefront a span before

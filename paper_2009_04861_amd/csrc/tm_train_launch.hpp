@@ -20,23 +20,25 @@ void launch_train_form(const TrainPtrs &p, TrainArgs a, bool full, hipStream_t s
 {
     const bool regr = a.y_regr != nullptr;
     constexpr bool HAS_SPANS = train_has_spans(WPL, ROOMY, DEEP, NARROW), team = train_team(WPL, ROOMY, DEEP, NARROW);
-    const bool spans = HAS_SPANS && !regr && 2 * (int64_t)(a.i_end - a.i_begin) / a.d.m >= train_spans_from(WPL, ROOMY, DEEP);
+    const int64_t entries = 2 * (int64_t)(a.i_end - a.i_begin) / a.d.m; // of a class's gate list where every gate is open
+    const bool spans = HAS_SPANS && !regr && entries >= train_spans_from(WPL, ROOMY, DEEP);
     if (!NARROW) {
         if (SlotMap<WPL>::PAIRED) a.lds_mask_words = 0; // the masks come out of the slots
         a.lds_draw_off = (a.lds_mask_words + a.lds_off_words + 2 * (a.d.Wf + EVAL_PAD) + 3) & ~3;
         if (spans) { // the literal list takes the place of the entries; then the events of a round, their rows and draws
-            a.lds_draw_off = a.lds_draw_off > TRAIN_LIT_MAX + LIT_PAD ? a.lds_draw_off : TRAIN_LIT_MAX + LIT_PAD;
+            a.lds_draw_off = a.lds_draw_off > TRAIN_LIT_MAX + SPAN_LIT_PAD ? a.lds_draw_off : TRAIN_LIT_MAX + SPAN_LIT_PAD;
             a.lds_wave_words = a.lds_draw_off + span_lds_words(WPL, team, DEEP);
         } else {
             a.lds_wave_words = a.lds_draw_off + (DEEP ? train_draw_words(WPL, team) : 0) + (WPL <= 4 ? TRAIN_LIT_MAX + LIT_PAD : 0);
         }
     }
-    // Clauses per workgroup: one of several wavefronts (team), else one per wavefront, and these do not interact.  Two are best once
-    // every SIMD holds several wavefronts (steady epochs of 20,000 clauses: 0.11 ms per launch against
-    // 0.14 ms with four; a workgroup's slots are handed on only when its slowest clause is done).  With about
-    // one clause per SIMD four are better: they land on the four SIMDs of a CU, while two workgroups of two
-    // may share a pair of SIMDs (1,000 clauses: 4.0 ms per epoch against 5.0 ms).
-    const int tw = team ? 1 : a.d.C <= ONE_PER_SIMD ? TRAIN_WAVES_MAX : 2;
+    // Clauses per workgroup: one of several wavefronts (team), else one per wavefront, and these do not interact.  A workgroup's
+    // slots are handed on only when its slowest clause is done, so one is best once every SIMD holds several wavefronts (speed against
+    // two: 16,384 clauses of 20,000 features 1.08, settled 8,000 of them 1.47; 3,000 clauses of 784 features 1.15; 20,000 1.03), and two
+    // where clauses have few gate entries to work through and few slots (20,000 clauses of 300 to 784 features, 200 entries: one 0.98 of
+    // two).  With about one clause per SIMD four are better: they land on the four SIMDs of a CU, while two workgroups of two may share a
+    // pair of SIMDs (1,000 clauses: 4.0 ms per epoch against 5.0 ms).
+    const int tw = team ? 1 : a.d.C <= ONE_PER_SIMD ? TRAIN_WAVES_MAX : WPL <= 2 && entries < 600 ? 2 : 1;
     const size_t lds = (size_t)a.lds_wave_words * tw * 4;
     const dim3 grid((unsigned)((a.slot_hi - a.slot_lo + tw - 1) / tw)), block(64 * (team ? (spans ? 2 + TEAM_DRAWERS : 2) : tw));
     constexpr bool CLASSES_ONLY = WPL == 1 && !ROOMY && !NARROW; // regression of one slot takes the roomy forms (launch_train_slots)
