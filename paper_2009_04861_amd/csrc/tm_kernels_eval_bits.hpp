@@ -17,10 +17,13 @@ namespace tsetlin {
 // every word per step, into a list of the wavefront; 64 / (RW / 2) groups of lanes AND the rows of different
 // literals, a lane holding 64 examples.  The steps end when no example is left.  Literals that are true on the whole
 // range (blank pixels, rare words: a trained clause may hold hundreds of them) are dropped from the masks first.
-// Pair p of row k stands at place (p + k) mod (RW / 2), so that the 32 rows a transposition writes at once
-// spread over the banks.
+// Pair p of row k stands at place p ^ (k mod (RW / 2)), so that the 32 rows a transposition writes at once
+// spread over the banks, and a list entry is the address of its row with that folded in: an exclusive or with
+// the lane's pair finds the word (seven operations an entry with row numbers).  Lists are filled up to 64 entries with a row
+// of ones, so that reading them takes neither a clamp nor an address of its own per entry.
 // What bounds it is the issue of the list and row steps of every (clause, range) and, with few clauses per share, the
-// transposition.  Measured: 10,000 examples on 20,000 trained clauses of 784 features 250 -> 98 us.
+// transposition.  Measured: 10,000 examples on 20,000 trained clauses of 784 features 250 -> 98 (row numbers) -> 72 us; clauses
+// of 100 literals of 2,400 features, false on every example, are the one form measured slower (2,000 of them 35 -> 42 us).
 
 constexpr int BITS_WAVES = 16; // wavefronts per workgroup
 
@@ -31,15 +34,16 @@ __global__ __launch_bounds__(64 * BITS_WAVES) void k_eval_bits(const uint32_t *_
                                                                const EvalArgs a, int share)
 {
     constexpr int PAIRS = RW / 2, GROUPS = 64 / PAIRS, NW = (2 * WF + 63) / 64, AHEAD = 8;
-    static_assert(BITS_WAVES % PAIRS == 0 && WF * 32 <= 32768, "wavefronts per pair of words, 15-bit row numbers");
-    __shared__ uint2 rows[WF * 32 * PAIRS];
+    static_assert(BITS_WAVES % PAIRS == 0, "wavefronts per pair of words");
+    __shared__ uint2 rows[(WF * 32 + 1) * PAIRS]; // the last one: ones
     __shared__ uint32_t always[2 * WF]; // literals that are true on every example of the range
-    __shared__ uint16_t lists[BITS_WAVES][64];
+    __shared__ uint32_t lists[BITS_WAVES][64];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int64_t e0 = (int64_t)blockIdx.x * (RW * 32);
 
     for (int w = (int)threadIdx.x; w < 2 * WF; w += 64 * BITS_WAVES) always[w] = ~0u;
+    if (threadIdx.x < PAIRS) rows[WF * 32 * PAIRS + threadIdx.x] = make_uint2(~0u, ~0u);
     __syncthreads();
     { // rows: this wavefront's 64 examples, every (BITS_WAVES / PAIRS)-th feature word
         constexpr int STEP = BITS_WAVES / PAIRS;
@@ -68,14 +72,18 @@ __global__ __launch_bounds__(64 * BITS_WAVES) void k_eval_bits(const uint32_t *_
                     atomicAnd(&always[a.Wf + fw], (uint32_t)zeros & (uint32_t)(zeros >> 32));
                 }
                 const int k = fw * 32 + (lane & 31);
-                out[(k * PAIRS + ((p + k) & (PAIRS - 1))) * 2] = v;
+                out[(k * PAIRS + (p ^ (k & (PAIRS - 1)))) * 2] = v;
             }
         }
     }
     __syncthreads();
 
     const int t = lane & (PAIRS - 1), grp = lane / PAIRS;
-    uint16_t *list = lists[wave];
+    uint32_t *list = lists[wave];
+    const char *row_bytes = reinterpret_cast<const char *>(rows);
+    constexpr uint32_t ROW = 8u * PAIRS, NEGATED = 0x80000000u; // bytes of a row; bit 31 of an entry: the literal is negated
+    constexpr uint32_t ONES = (uint32_t)(WF * 32) * ROW; // WF * 32 mod PAIRS is 0: nothing to fold in
+    const uint32_t t8 = 8u * (uint32_t)t;
     const int64_t words = (a.q + 31) >> 5;
     const int g_end = min(a.C, ((int)blockIdx.y + 1) * share);
     uint32_t mk[NW], next[NW], skip[NW];
@@ -97,26 +105,25 @@ __global__ __launch_bounds__(64 * BITS_WAVES) void k_eval_bits(const uint32_t *_
 #pragma unroll
         for (int r = 0; r < NW; ++r) {
             const int lw = r * 64 + lane;
-            const uint32_t first = lw >= a.Wf ? (uint32_t)(lw - a.Wf) * 32u | 0x8000u : (uint32_t)lw * 32u;
+            const uint32_t first = lw >= a.Wf ? (uint32_t)(lw - a.Wf) * (32u * ROW) | NEGATED : (uint32_t)lw * (32u * ROW);
             while (left) {
                 const uint64_t b = ballot(mk[r] != 0u);
                 if (b == 0) break;
-                if (mk[r] != 0u) {
-                    list[(int)__builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u))] =
-                        (uint16_t)(first + (uint32_t)__builtin_ctz(mk[r]));
-                    mk[r] &= mk[r] - 1u;
-                }
                 const int cnt = __builtin_popcountll(b);
+                const int pre = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
+                const uint32_t bit = (uint32_t)__builtin_ctz(mk[r]); // of a word: rows of a word begin at a multiple of PAIRS
+                const bool has = mk[r] != 0u;
+                list[has ? pre : cnt + lane - pre] = has ? first + (bit * ROW | (bit & (PAIRS - 1)) * 8u) : ONES;
+                mk[r] &= mk[r] - 1u; // stays 0 once it is 0
                 wave_lds_sync();
-                for (int j = 0; j < cnt; j += 4 * GROUPS) { // past the end: the last literal again
+                for (int j = 0; j < cnt; j += 4 * GROUPS) {
                     uint32_t ent[4];
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) ent[u] = list[min(j + u * GROUPS + grp, cnt - 1)];
+                    for (int u = 0; u < 4; ++u) ent[u] = list[j + u * GROUPS + grp];
 #pragma unroll
                     for (int u = 0; u < 4; ++u) {
-                        const int k = (int)(ent[u] & 0x7fffu);
-                        const uint32_t neg = 0u - (ent[u] >> 15);
-                        const uint2 v = rows[k * PAIRS + ((t + k) & (PAIRS - 1))];
+                        const uint32_t neg = (uint32_t)((int32_t)ent[u] >> 31);
+                        const uint2 v = *reinterpret_cast<const uint2 *>(row_bytes + ((ent[u] & ~NEGATED) ^ t8));
                         acc.x &= v.x ^ neg;
                         acc.y &= v.y ^ neg;
                     }
