@@ -30,9 +30,10 @@
 //   k_eval_resident, k_eval_stream lane = clause : include masks in VGPRs, example words arrive
 //            through scalar loads, one bit-select per feature word and pair; clause votes are
 //            summed with wave ballot + popcount (inference without a workspace, other clause outputs).
-//   k_train  one wavefront = one clause (Algorithm 1 gives every clause its own
-//            thread); lane = gate-list entry for the gates, lane = literal word for
-//            feedback, lane = example for the evaluation of a block of 64 examples.
+//   k_train  one wavefront, or a team of them, = one clause (Algorithm 1 gives every clause its own
+//            thread); lane = gate-list entry for the gates, lane = literal word (clauses of one
+//            feature word: lane = automaton) for feedback, lane = example for the evaluation of a block of
+//            64 examples, lane = 32 examples where outputs are taken span by span.
 #include <hip/hip_runtime.h>
 #include <algorithm>
 #include <math.h>
@@ -359,7 +360,7 @@ int launch_eval(tm_handle *h, const uint32_t *X, int64_t q, uint32_t *bits, int6
     // example are as cheap (128 features, 10,000 examples 92 / 138; 256 features, 1,280 clauses 26 / 14 to 17); above
     // 76 feature words the rows do not fit.  What the rule cannot see is the number of literals that are true on almost,
     // but not quite, every example; 20,000 clauses of 784 features, 10,000 examples: 50 of them 250 / 165, 100 249 / 257,
-    // 300 250 / 582 (2,400 features, 300: 1,600 / 920).  Up to 32 words a lane holds one mask word and the rows of 1,024
+    // 300 250 / 582 (2,400 features, 300: 1,600 / 920); the rows have become 10 to 40 % faster since.  Up to 32 words a lane holds one mask word and the rows of 1,024
     // examples leave one workgroup per CU either way (1,000 features with one mask word instead of two: 103 -> 98).
     if (bits && !acc && q >= 128 && d.Wf > 16 && d.Wf <= 76) {
         if (d.Wf <= 32) return launch_eval_bits_t<32, 32>(h, p, a, st);

@@ -355,7 +355,7 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
     // over the lanes in scalar registers.  An event is a handful of scalar operations and four vector ones (add, subtract, clamp,
     // compare) instead of the fifty dependent ones of the bit planes, and what an epoch of so small a machine costs is its
     // events' latency.  Outputs of the open block are taken when the masks change and when it is closed.
-    // Noisy XOR (20 clauses, 5,000 examples) 958 -> 650 us, 4,000 clauses of 12 features 570 -> 453; with two words the
+    // Noisy XOR (20 clauses, 5,000 examples) 958 -> 620 us, 4,000 clauses of 12 features 570 -> 418; with two words the
     // planes are as fast (0.91 to 0.94 of their speed), with four faster (0.63 to 0.78).
     constexpr int TW = TINY ? TINY : 1;
     uint32_t st[TW] = {};           // stored states

@@ -30,8 +30,8 @@ constexpr int SPAN_MOST = 2048;
 // the feedback events of an image-like machine with every gate open: 60 to 90 walks of 18 literals take the place of 1,000
 // evaluations of blocks of 64 examples, which were a sixth of the vector instructions of such a pass.
 // What bounds it is vector issue (0.85 of the peak rate).  20,000 clauses of 784 features, 60,000 examples, s = 10: vector
-// instructions 12.2e9 -> 9.4e9, scalar 8.3e9 -> 6.0e9, 24.4 -> 17.4 ms.
-// With about one clause per SIMD a team of four wavefronts takes a clause (TEAM below): 1,000 clauses of 784 features 2.72 -> 1.23 ms.
+// instructions 12.2e9 -> 9.4e9, scalar 8.3e9 -> 6.0e9, 24.4 -> 16.9 ms.
+// With about one clause per SIMD a team of four wavefronts takes a clause (TEAM below): 1,000 clauses of 784 features 2.72 -> 1.21 ms.
 template <int WPL, bool FULL, bool LAZY, bool ROOMY, bool DEEP>
 __device__ __forceinline__ void train_spans(const uint32_t *__restrict__ X, const uint32_t *__restrict__ XT,
                                             const uint32_t *__restrict__ XB, const int32_t *__restrict__ gate,
