@@ -45,19 +45,18 @@ void launch_train_form(const TrainPtrs &p, TrainArgs a, bool full, hipStream_t s
     auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, lds, st, p.X, p.XT, p.XB, p.gate, p.ngate, a); };
     auto choose = [&](auto spans_too, auto tiny) {
         constexpr bool SPANS = decltype(spans_too)::value;
-        constexpr int TINY = decltype(tiny)::value;
+        constexpr bool TINY = decltype(tiny)::value;
         if (!regr) return full ? launch(k_train<WPL, true, false, ROOMY, NARROW, DEEP, SPANS, TINY>) : launch(k_train<WPL, false, false, ROOMY, NARROW, DEEP, SPANS, TINY>);
         if constexpr (!CLASSES_ONLY && !SPANS)
             return full ? launch(k_train<WPL, true, true, ROOMY, NARROW, DEEP, false, TINY>) : launch(k_train<WPL, false, true, ROOMY, NARROW, DEEP, false, TINY>);
     };
-    using std::integral_constant;
     if constexpr (HAS_SPANS) {
-        if (spans) return choose(std::true_type{}, integral_constant<int, 0>{});
+        if (spans) return choose(std::true_type{}, std::false_type{});
     }
     if constexpr (NARROW) {
-        if (a.d.Wf <= 1) return choose(std::false_type{}, integral_constant<int, 1>{});
+        if (a.d.Wf <= 1) return choose(std::false_type{}, std::true_type{});
     }
-    choose(std::false_type{}, integral_constant<int, 0>{});
+    choose(std::false_type{}, std::false_type{});
 }
 
 // The forms there are: F(part, register slots, roomy, deep, narrow)
