@@ -397,12 +397,12 @@ int launch_eval(tm_handle *h, const uint32_t *X, int64_t q, uint32_t *bits, int6
 }
 
 #define TM_EXTERN(part, wpl, roomy, deep, narrow) \
-    extern template void tsetlin::launch_train_form<wpl, roomy, deep, narrow>(const TrainPtrs &, TrainArgs, bool, hipStream_t);
+    extern template void tsetlin::launch_train_form<wpl, roomy, deep, narrow>(const TrainPtrs &, TrainArgs, bool, hipStream_t, int *);
 } // namespace
 TM_TRAIN_FORMS(TM_EXTERN)
 namespace {
 
-// Launches the form for clauses of wpl register slots; false if there is none.  Roomy where a form has it: about one
+// Launches the form for clauses of wpl register slots; false if there is none (clauses_per_group: see launch_train_form).  Roomy where a form has it: about one
 // wavefront per SIMD, or none to gain (train_split).
 // One slot: regression beyond a SIMD per clause takes the roomy form without draws made ahead for every threshold (its machines
 // settle at few events per round, which leaves little to share; speed with draws made ahead / this, against the version before
@@ -410,13 +410,13 @@ namespace {
 // per SIMD, as many as it holds; the other one holds six, so that its SIMDs fill unevenly below that (500 features, s = 2, other form / this:
 // 1,600 clauses 0.97 / 1.00, 5,000 0.93 / 1.03; beyond, 6,000 clauses: other form 1.09, held to five wavefronts 0.97).
 bool launch_train_slots(int wpl, bool narrow, bool deep, int clauses, const TrainPtrs &p, const TrainArgs &a, bool full,
-                        hipStream_t st)
+                        hipStream_t st, int *clauses_per_group = nullptr)
 {
-    if (narrow) return launch_train_form<1, false, false, true>(p, a, full, st), true;
+    if (narrow) return launch_train_form<1, false, false, true>(p, a, full, st, clauses_per_group), true;
     const bool alone = clauses <= 1024, few = clauses <= 2 * 1024, some = clauses <= 3 * 1024;
-    if (wpl <= 1 && a.d.regr && !alone) return launch_train_form<1, true, false, false>(p, a, full, st), true;
+    if (wpl <= 1 && a.d.regr && !alone) return launch_train_form<1, true, false, false>(p, a, full, st, clauses_per_group), true;
 #define TM_TAKE(most, wpl_, roomy, deep_) \
-    if (wpl <= most) return launch_train_form<wpl_, roomy, deep_, false>(p, a, full, st), true
+    if (wpl <= most) return launch_train_form<wpl_, roomy, deep_, false>(p, a, full, st, clauses_per_group), true
     if (deep) {
         if (alone) {
             TM_TAKE(1, 1, true, true);
@@ -624,20 +624,6 @@ int launch_train(tm_handle *h, const int32_t *vhat, int64_t i_begin, int64_t i_e
         a.slot_lo = (int)((int64_t)d.C * grp / h->clause_groups);
         a.slot_hi = (int)((int64_t)d.C * (grp + 1) / h->clause_groups);
         if (a.slot_hi <= a.slot_lo) continue;
-        PrepArgs pa;
-        pa.y = h->y; pa.key = d.key; pa.epoch = h->epoch; pa.tally = h->tally; pa.vhat = vhat; pa.fresh = h->fresh;
-        pa.gate = h->gate; pa.ngate = h->ngate; pa.order = h->order; pa.seg_cnt = h->seg_cnt; pa.counters = h->counters;
-        pa.i_begin = a.i_begin; pa.i_end = a.i_end; pa.qp = a.qp; pa.m = d.m; pa.n = d.n; pa.C = d.C; pa.T = d.T;
-        pa.regr = d.regr; pa.g_lo = a.slot_lo; pa.g_hi = a.slot_hi;
-        pa.segs = (int)prep_segments(d, h->qp);
-        const int64_t items = std::max<int64_t>(a.i_end - a.i_begin, a.slot_hi - a.slot_lo);
-        const dim3 pgrid((unsigned)((items + PREP_SEG - 1) / PREP_SEG), (unsigned)(d.m + 1));
-        hipLaunchKernelGGL(k_launch_prep<false>, pgrid, dim3(1024), 0, st, pa);
-        TM_HIP(h, hipGetLastError());
-        hipLaunchKernelGGL(k_launch_prep<true>, pgrid, dim3(1024), 0, st, pa);
-        TM_HIP(h, hipGetLastError());
-        int rc = timing_mark(h, TIMED_TRAIN, true, st);
-        if (rc) return rc;
         // The Type I comparison needs more than two Philox blocks; with one slot and a SIMD per clause every threshold that needs
         // any takes that form, whose draws a second wavefront makes (kernel
         // time inline / handed over, s = 2: 90 clauses of 297 features 1.33 / 0.99 ms, 500 of 784 1.31 / 1.21, 1,000 of 784 0.76 / 0.74;
@@ -647,6 +633,25 @@ int launch_train(tm_handle *h, const int32_t *vhat, int64_t i_begin, int64_t i_e
         // A team takes narrow clauses of more than one feature word as well (speed against the narrow form, 20 to 1,000 clauses of 50
         // to 256 features, 800 to 5,000 gate entries per class: 1.03 to 2.1; one word: 0.89 to 1.8, that form without bit planes 1.23 to 1.35).
         const bool team = !d.regr && deep && wpl <= 1 && d.Wf > 1 && alone && 2 * (int64_t)(a.i_end - a.i_begin) / d.m >= train_spans_from(1, true, true);
+        int clauses_per_group = 0;
+        if (!launch_train_slots(wpl, narrow && !team, deep, a.slot_hi - a.slot_lo, p, a, full, st, &clauses_per_group)) return TM_ELIMIT;
+        PrepArgs pa;
+        pa.y = h->y; pa.key = d.key; pa.epoch = h->epoch; pa.tally = h->tally; pa.vhat = vhat; pa.fresh = h->fresh;
+        pa.gate = h->gate; pa.ngate = h->ngate; pa.order = h->order; pa.seg_cnt = h->seg_cnt; pa.counters = h->counters;
+        pa.i_begin = a.i_begin; pa.i_end = a.i_end; pa.qp = a.qp; pa.m = d.m; pa.n = d.n; pa.C = d.C; pa.T = d.T;
+        pa.regr = d.regr; pa.g_lo = a.slot_lo; pa.g_hi = a.slot_hi;
+        // Above 4 slots a launch covers so few examples (train_chunk) that the lead is short, and XCDs of one polarity are faster (16,384
+        // clauses of 20,000 features 23.1 ms, paired 26.6); in regression every clause has the same polarity.
+        pa.paired = !d.regr && wpl <= 4 && clauses_per_group == 1;
+        pa.segs = (int)prep_segments(d, h->qp);
+        const int64_t items = std::max<int64_t>(a.i_end - a.i_begin, a.slot_hi - a.slot_lo);
+        const dim3 pgrid((unsigned)((items + PREP_SEG - 1) / PREP_SEG), (unsigned)(d.m + 1));
+        hipLaunchKernelGGL(k_launch_prep<false>, pgrid, dim3(1024), 0, st, pa);
+        TM_HIP(h, hipGetLastError());
+        hipLaunchKernelGGL(k_launch_prep<true>, pgrid, dim3(1024), 0, st, pa);
+        TM_HIP(h, hipGetLastError());
+        int rc = timing_mark(h, TIMED_TRAIN, true, st);
+        if (rc) return rc;
         if (!launch_train_slots(wpl, narrow && !team, deep, a.slot_hi - a.slot_lo, p, a, full, st)) return TM_ELIMIT;
         TM_HIP(h, hipGetLastError());
         rc = timing_mark(h, TIMED_TRAIN, false, st);

@@ -1381,15 +1381,7 @@ __global__ __launch_bounds__(64 * TRAIN_WAVES_MAX) __attribute__((amdgpu_waves_p
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     constexpr bool TEAM = train_team(WPL, ROOMY, DEEP, NARROW); // one clause per workgroup
-    // Workgroups go to the XCDs in turn.  With one clause in each, clauses of positive polarity (odd) would all run on four XCDs and
-    // those of negative polarity on the others, whose pace differs: on the live tallies one polarity would run ahead of the other.  So of
-    // every 16 workgroups the two of an XCD take neighbouring clauses (10 x 2,000 clauses of 784 features, T = 50: second live
-    // epoch 1.24 -> 0.30 ms; 10 x 400 noisier ones, T = 20: test accuracy 0.960 -> 0.986).  Above 4 slots a
-    // launch covers so few examples (tm_train_chunk) that the lead is short, and XCDs of one polarity are faster (16,384 clauses of 20,000
-    // features 23.1 ms, paired 26.6).
-    const int group = (int)blockIdx.x, clauses = TEAM ? 1 : (int)(blockDim.x >> 6);
-    const bool paired = WPL <= 4 && clauses == 1 && (group | 15) < (int)gridDim.x;
-    const int slot = a.slot_lo + (paired ? (group & ~15) | (group & 7) << 1 | (group >> 3 & 1) : group * clauses + wave * (TEAM ? 0 : 1));
+    const int slot = a.slot_lo + (TEAM ? (int)blockIdx.x : (int)(blockIdx.x * (blockDim.x >> 6)) + wave);
     if (slot >= a.slot_hi) return; // whole wavefront (TEAM: all of them, and all walk the same rounds with one barrier in each)
     const int g = __builtin_amdgcn_readfirstlane(a.order[slot]);
     const int k_hi = __builtin_amdgcn_readfirstlane(ngate[g / a.d.n]);

@@ -15,8 +15,9 @@ struct TrainPtrs {
     const int32_t *gate, *ngate;
 };
 
+// With clauses_per_group nothing is launched; it receives how many clauses a workgroup of the launch would hold.
 template <int WPL, bool ROOMY, bool DEEP, bool NARROW>
-void launch_train_form(const TrainPtrs &p, TrainArgs a, bool full, hipStream_t st)
+void launch_train_form(const TrainPtrs &p, TrainArgs a, bool full, hipStream_t st, int *clauses_per_group)
 {
     const bool regr = a.y_regr != nullptr;
     constexpr bool HAS_SPANS = train_has_spans(WPL, ROOMY, DEEP, NARROW), team = train_team(WPL, ROOMY, DEEP, NARROW);
@@ -39,6 +40,10 @@ void launch_train_form(const TrainPtrs &p, TrainArgs a, bool full, hipStream_t s
     // two).  With about one clause per SIMD four are better: they land on the four SIMDs of a CU, while two workgroups of two may share a
     // pair of SIMDs (1,000 clauses: 4.0 ms per epoch against 5.0 ms).
     const int tw = team ? 1 : a.d.C <= ONE_PER_SIMD ? TRAIN_WAVES_MAX : WPL <= 2 && entries < 600 ? 2 : 1;
+    if (clauses_per_group) {
+        *clauses_per_group = tw;
+        return;
+    }
     const size_t lds = (size_t)a.lds_wave_words * tw * 4;
     const dim3 grid((unsigned)((a.slot_hi - a.slot_lo + tw - 1) / tw)), block(64 * (team ? (spans ? 2 + TEAM_DRAWERS : 2) : tw));
     constexpr bool CLASSES_ONLY = WPL == 1 && !ROOMY && !NARROW; // regression of one slot takes the roomy forms (launch_train_slots)

@@ -5,7 +5,7 @@ namespace tsetlin {
 
 #define TM_FORM(part, wpl, roomy, deep, narrow) TM_FORM_##part(wpl, roomy, deep, narrow)
 #define TM_INSTANTIATE(wpl, roomy, deep, narrow) \
-    template void launch_train_form<wpl, roomy, deep, narrow>(const TrainPtrs &, TrainArgs, bool, hipStream_t);
+    template void launch_train_form<wpl, roomy, deep, narrow>(const TrainPtrs &, TrainArgs, bool, hipStream_t, int *);
 #if TM_TRAIN_PART == 1
 #define TM_FORM_1 TM_INSTANTIATE
 #else
