@@ -632,7 +632,7 @@ int launch_train(tm_handle *h, const int32_t *vhat, int64_t i_begin, int64_t i_e
         const bool deep = d.thr != 0 && (__builtin_ctz(d.thr) < 8 || (d.thr < 65536u && wpl <= 1 && alone));
         // A team takes narrow clauses of more than one feature word as well (speed against the narrow form, 20 to 1,000 clauses of 50
         // to 256 features, 800 to 5,000 gate entries per class: 1.03 to 2.1; one word: 0.89 to 1.8, that form without bit planes 1.23 to 1.35).
-        const bool team = !d.regr && deep && wpl <= 1 && d.Wf > 1 && alone && 2 * (int64_t)(a.i_end - a.i_begin) / d.m >= train_spans_from(1, true, true);
+        const bool team = !d.regr && !train_swings(a) && deep && wpl <= 1 && d.Wf > 1 && alone && 2 * (int64_t)(a.i_end - a.i_begin) / d.m >= train_spans_from(1, true, true);
         int clauses_per_group = 0;
         if (!launch_train_slots(wpl, narrow && !team, deep, a.slot_hi - a.slot_lo, p, a, full, st, &clauses_per_group)) return TM_ELIMIT;
         PrepArgs pa;

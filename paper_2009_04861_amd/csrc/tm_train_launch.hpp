@@ -15,6 +15,15 @@ struct TrainPtrs {
     const int32_t *gate, *ngate;
 };
 
+// Live classification passes with T below a quarter of n.  An error of one vote moves the expected feedback of a class by n / 2T
+// clauses; where that is several, a machine swings about its margin, the more the further its clauses walk in step, reading
+// tallies that all of them are about to correct alike.  How far they do depends on how long the clauses take between two looks at the
+// tallies, and the span forms, in which they take much the same time, do worse (test accuracy of late epochs, block by block / span by span;
+// T / n = 1 / 20: 2 x 2,000 clauses of 900 bag-of-words features 0.995 / 0.93, 2 x 1,000 of 2,500 0.92 / 0.75, 10 x 400 of 784 noisy pixels
+// 0.994 / 0.987, 4 x 1,000 of 2,500 0.61 / 0.95; 1 / 5, 2 x 100 of 64 features, which a team would take, 0.985 / 0.981).  From a tenth of n on they
+// are alike elsewhere (24 machines of 700 to 10,000 features: within 0.002, gates fired within 5 %), from a quarter on everywhere.
+inline bool train_swings(const TrainArgs &a) { return !a.vhat && !a.y_regr && 4 * (int64_t)a.d.T < a.d.n; }
+
 // With clauses_per_group nothing is launched; it receives how many clauses a workgroup of the launch would hold.
 template <int WPL, bool ROOMY, bool DEEP, bool NARROW>
 void launch_train_form(const TrainPtrs &p, TrainArgs a, bool full, hipStream_t st, int *clauses_per_group)
@@ -22,7 +31,7 @@ void launch_train_form(const TrainPtrs &p, TrainArgs a, bool full, hipStream_t s
     const bool regr = a.y_regr != nullptr;
     constexpr bool HAS_SPANS = train_has_spans(WPL, ROOMY, DEEP, NARROW), team = train_team(WPL, ROOMY, DEEP, NARROW);
     const int64_t entries = 2 * (int64_t)(a.i_end - a.i_begin) / a.d.m; // of a class's gate list where every gate is open
-    const bool spans = HAS_SPANS && !regr && entries >= train_spans_from(WPL, ROOMY, DEEP);
+    const bool spans = HAS_SPANS && !regr && !train_swings(a) && entries >= train_spans_from(WPL, ROOMY, DEEP);
     if (!NARROW) {
         if (SlotMap<WPL>::PAIRED) a.lds_mask_words = 0; // the masks come out of the slots
         a.lds_draw_off = (a.lds_mask_words + a.lds_off_words + 2 * (a.d.Wf + EVAL_PAD) + 3) & ~3;

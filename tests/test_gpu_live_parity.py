@@ -47,6 +47,20 @@ LIVE_SHAPES = [
     (2, 8, 500, 100, 5, 2.0, 700, 0.3),
     (3, 6, 1024, 128, 5, 4.0, 500, 0.2),
     (2, 6, 257, 64, 5, 3.9, 900, 0.3),
+    # passes long enough for outputs span by span, T from a quarter of n on: one slot in a team (784 features) and, where no Type I draw is
+    # needed (s = 1), by one wavefront, which reads the live tallies a round ahead; narrow clauses in a team; two and three slots with thresholds of several
+    # Philox blocks and of one
+    (2, 6, 784, 128, 5, 10.0, 1700, 0.3),
+    (2, 6, 500, 128, 5, 1.0, 1700, 0.3),
+    (2, 8, 100, 128, 2, 3.9, 1100, 0.4),
+    (2, 4, 1500, 128, 3, 5.0, 3100, 0.2),
+    (2, 4, 1300, 100, 3, 2.0, 1600, 0.2),
+    (2, 4, 2500, 128, 3, 5.0, 1600, 0.2),
+    (2, 4, 3000, 128, 3, 4.0, 1600, 0.2),
+    # the same with T below a quarter of n: block by block
+    (2, 6, 784, 128, 1, 10.0, 1700, 0.3),
+    (2, 8, 100, 128, 1, 3.9, 1100, 0.4),
+    (2, 6, 2500, 128, 1, 4.0, 1600, 0.2),
 ]
 
 
