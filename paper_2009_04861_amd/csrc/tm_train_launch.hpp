@@ -47,8 +47,10 @@ void launch_train_form(const TrainPtrs &p, TrainArgs a, bool full, hipStream_t s
     // two: 16,384 clauses of 20,000 features 1.12, 20,000 of 10,000 features 1.06, 20,000 of 784 features 1.02), and two
     // where clauses have few gate entries to work through and few slots (20,000 clauses of 300 to 784 features, 200 entries: one 0.98 of
     // two).  With about one clause per SIMD four are better: they land on the four SIMDs of a CU, while two workgroups of two may share a
-    // pair of SIMDs (1,000 clauses: 4.0 ms per epoch against 5.0 ms).
-    const int tw = team ? 1 : a.d.C <= ONE_PER_SIMD ? TRAIN_WAVES_MAX : WPL <= 2 && entries < 600 ? 2 : 1;
+    // pair of SIMDs (1,000 clauses: 4.0 ms per epoch against 5.0 ms).  Live passes that swing hold two: neighbours, one of either polarity,
+    // then walk side by side (T = 0.05 and 0.075 n, 2 x 3,000 clauses of 4,100 bag-of-words features: test accuracy 0.944 and 0.917, one
+    // clause per workgroup 0.815 and 0.901).
+    const int tw = team ? 1 : a.d.C <= ONE_PER_SIMD ? TRAIN_WAVES_MAX : train_swings(a) || (WPL <= 2 && entries < 600) ? 2 : 1;
     if (clauses_per_group) {
         *clauses_per_group = tw;
         return;
