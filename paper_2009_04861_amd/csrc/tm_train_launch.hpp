@@ -50,7 +50,13 @@ void launch_train_form(const TrainPtrs &p, TrainArgs a, bool full, hipStream_t s
     // pair of SIMDs (1,000 clauses: 4.0 ms per epoch against 5.0 ms).  Live passes that swing hold two: neighbours, one of either polarity,
     // then walk side by side (T = 0.05 and 0.075 n, 2 x 3,000 clauses of 4,100 bag-of-words features: test accuracy 0.944 and 0.917, one
     // clause per workgroup 0.815 and 0.901).
-    const int tw = team ? 1 : a.d.C <= ONE_PER_SIMD ? TRAIN_WAVES_MAX : train_swings(a) || (WPL <= 2 && entries < 600) ? 2 : 1;
+    // Single wavefronts spread unevenly over the SIMDs, depending on what ran before: one too many on some costs little where a SIMD
+    // gets three or more than four, but not where it gets two or four, which pairs fill evenly (speed of one against two, best and worst after
+    // different work: 2,000 clauses of 5,000 to 10,000 features 1.04 and 0.82; 4,000 of 1,500 1.0 and 0.84; 3,000 of 300 to 2,500 1.1 to 1.2).  That
+    // goes for forms of which a SIMD holds as many.
+    const int clauses = a.slot_hi - a.slot_lo;
+    const bool even = (WPL <= 10 && clauses <= 2 * 1024) || (WPL <= 4 && clauses > 3 * 1024 && clauses <= 4 * 1024);
+    const int tw = team ? 1 : a.d.C <= ONE_PER_SIMD ? TRAIN_WAVES_MAX : even || train_swings(a) || (WPL <= 2 && entries < 600) ? 2 : 1;
     if (clauses_per_group) {
         *clauses_per_group = tw;
         return;
