@@ -254,17 +254,22 @@ constexpr int DRAW_RING = 128; // words of literals waiting for their last two b
 // They meet at one barrier per round; what is handed over lies in LDS twice.
 // Four wavefronts with train_spans, two with train_clause.
 __host__ __device__ constexpr bool train_team(int wpl, bool roomy, bool deep, bool narrow) { return wpl == 1 && roomy && deep && !narrow; }
-// Forms that come with train_spans as well, for classification; 2 slots with many clauses and DEEP are faster without (0.88 to
-// 0.92 of the speed with, 8,000 clauses of 1,500 features).
+// Forms that come with train_spans as well, for classification.  Spans gain where masks change seldom and lose where they change at every
+// second event, as on bag-of-words data: speed with against without, 60 to 20,000 clauses with s = 2 and 10, noisy images / bags of words: one
+// slot, teams 1.5 to 2.0 / 0.96 to 1.15, wavefronts 1.15 to 1.5 / 0.85 to 1.15; two slots, DEEP and few clauses 1.18 / 0.88, DEEP and many 0.88
+// to 0.92 (images), not DEEP 1.04 to 1.11 / 0.77 to 0.84 (without); three slots 1.15 to 1.5 / 0.74 to 1.05.
 __host__ __device__ constexpr bool train_has_spans(int wpl, bool roomy, bool deep, bool narrow)
 {
-    return wpl <= 3 && !narrow && !(wpl == 2 && deep && !roomy);
+    return wpl <= 3 && !narrow && (wpl != 2 || (deep && roomy));
 }
 // Least gate entries per class and launch, as the host expects them (every gate open), for which they take it.  Short launches mean
 // young machines, whose masks change at every second or third event, and then an open block is the cheaper place for the outputs.
 // Speed with spans, by expected entries (200 to 5,000 clauses per class of 400 to 2,500 features, s = 2 and 10): 400 0.85 to 0.97, 800 0.93
-// to 1.05, 1,600 1.0 to 1.3, 4,000 1.06 to 1.4, 8,000 1.1 to 1.8; teams 400 0.98, 800 1.05, 1,600 1.16 to 1.4; two slots and DEEP 1,600 0.97, 4,000 1.03.
-__host__ __device__ constexpr int train_spans_from(int wpl, bool roomy, bool deep) { return train_team(wpl, roomy, deep, false) ? 800 : wpl == 2 && deep ? 3000 : 1500; }
+// to 1.05, 1,600 1.0 to 1.3, 4,000 1.06 to 1.4, 8,000 1.1 to 1.8; teams 400 0.98, 800 1.05, 1,600 1.16 to 1.4; two slots 1,600 0.97, 4,000 1.03.
+__host__ __device__ constexpr int train_spans_from(int wpl, bool roomy, bool deep)
+{
+    return train_team(wpl, roomy, deep, false) ? 800 : wpl == 2 ? 3000 : 1500;
+}
 constexpr int TEAM_ROUND = 32;     // gate entries per round
 constexpr int TEAM_DRAWERS = 2;    // wavefronts that draw Type I events
 constexpr int TEAM_HANDED = 36;    // words handed over per round beside rows and draws

@@ -606,7 +606,7 @@ __device__ __forceinline__ void train_spans(const uint32_t *__restrict__ X, cons
                             uint32_t lw = (uint32_t)Map::word(r, lane, d.Wf), ge = ge_init, eq = 0u, thr = d.thr;
                             asm volatile("" : "+v"(lw)); // the first Philox round of every slot is not to be kept
                             RngKey key = d.key;
-                            if (WPL <= 2) asm volatile("" : "+s"(key.seed_lo), "+s"(key.seed_hi), "+s"(thr)); // see LAUNDER
+                            if (WPL == 1) asm volatile("" : "+s"(key.seed_lo), "+s"(key.seed_hi), "+s"(thr)); // see LAUNDER
 #pragma unroll
                             for (int t = 2; t < 4; ++t) {
                                 if (t >= first_blk) {

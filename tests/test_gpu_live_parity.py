@@ -48,8 +48,8 @@ LIVE_SHAPES = [
     (3, 6, 1024, 128, 5, 4.0, 500, 0.2),
     (2, 6, 257, 64, 5, 3.9, 900, 0.3),
     # passes long enough for outputs span by span, T from a quarter of n on: one slot in a team (784 features) and, where no Type I draw is
-    # needed (s = 1), by one wavefront, which reads the live tallies a round ahead; narrow clauses in a team; two and three slots with thresholds of several
-    # Philox blocks and of one
+    # needed (s = 1), by one wavefront, which reads the live tallies a round ahead; narrow clauses in a team; two slots with a threshold of several
+    # Philox blocks (with one: block by block), three with either
     (2, 6, 784, 128, 5, 10.0, 1700, 0.3),
     (2, 6, 500, 128, 5, 1.0, 1700, 0.3),
     (2, 8, 100, 128, 2, 3.9, 1100, 0.4),
