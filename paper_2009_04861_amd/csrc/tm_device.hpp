@@ -105,17 +105,14 @@ __device__ __forceinline__ U4 draw_from(const PhiloxStart &s, const RngKey &k, u
 }
 
 // Four bits of a comparison u >= thr for 32 literals, least significant first: word k holds bit k of their uniforms (x and z turned
-// over where thr has a 1, see draw_from), t[k] is bit k of thr in all places.  ge: u >= thr by the bits so far; eq: equal in all of them.
-__device__ __forceinline__ void compare_nibble(const U4 &w, const uint32_t (&t)[4], uint32_t &ge, uint32_t &eq)
+// over where thr has a 1, see draw_from), t[k] is bit k of thr in all places.  ge: u >= thr by the bits so far; returns it with these.
+__device__ __forceinline__ uint32_t compare_nibble(const U4 &w, const uint32_t (&t)[4], uint32_t ge)
 {
     // thr bit 0: ge |= u, thr bit 1: ge &= u
     ge = (uint32_t)__builtin_amdgcn_bitop3_b32(w.x, ge, t[0], 0x5C);
     ge = (uint32_t)__builtin_amdgcn_bitop3_b32(w.y, ge, t[1], 0xD4);
     ge = (uint32_t)__builtin_amdgcn_bitop3_b32(w.z, ge, t[2], 0x5C);
-    ge = (uint32_t)__builtin_amdgcn_bitop3_b32(w.w, ge, t[3], 0xD4);
-    eq = (uint32_t)__builtin_amdgcn_bitop3_b32(eq, w.x, w.z, 0x10); // eq & ~x & ~z
-    eq = (uint32_t)__builtin_amdgcn_bitop3_b32(eq, w.y, t[1], 0x90); // eq & ~(y ^ t)
-    eq = (uint32_t)__builtin_amdgcn_bitop3_b32(eq, w.w, t[3], 0x90);
+    return (uint32_t)__builtin_amdgcn_bitop3_b32(w.w, ge, t[3], 0xD4);
 }
 
 // ---- wave64 helpers ------------------------------------------------------

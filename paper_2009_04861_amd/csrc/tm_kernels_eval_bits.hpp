@@ -111,9 +111,13 @@ __global__ __launch_bounds__(64 * BITS_WAVES) void k_eval_bits(const uint32_t *_
                 if (b == 0) break;
                 const int cnt = __builtin_popcountll(b);
                 const int pre = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
-                const uint32_t bit = (uint32_t)__builtin_ctz(mk[r]); // of a word: rows of a word begin at a multiple of PAIRS
                 const bool has = mk[r] != 0u;
-                list[has ? pre : cnt + lane - pre] = has ? first + (bit * ROW | (bit & (PAIRS - 1)) * 8u) : ONES;
+                uint32_t entry = ONES;
+                if (has) { // a word's rows begin at a multiple of PAIRS
+                    const uint32_t bit = (uint32_t)__builtin_ctz(mk[r]);
+                    entry = first + (bit * ROW | (bit & (PAIRS - 1)) * 8u);
+                }
+                list[has ? pre : cnt + lane - pre] = entry;
                 mk[r] &= mk[r] - 1u; // stays 0 once it is 0
                 wave_lds_sync();
                 for (int j = 0; j < cnt; j += 4 * GROUPS) {

@@ -603,7 +603,7 @@ __device__ __forceinline__ void train_spans(const uint32_t *__restrict__ X, cons
                             return ge_at[(n_used * WPL + r) * 64];
                         } else {
                             // the bits of blocks below first_blk cannot decide, see train_clause
-                            uint32_t lw = (uint32_t)Map::word(r, lane, d.Wf), ge = ge_init, eq = 0u, thr = d.thr;
+                            uint32_t lw = (uint32_t)Map::word(r, lane, d.Wf), ge = ge_init, thr = d.thr;
                             asm volatile("" : "+v"(lw)); // the first Philox round of every slot is not to be kept
                             RngKey key = d.key;
                             if (WPL == 1) asm volatile("" : "+s"(key.seed_lo), "+s"(key.seed_hi), "+s"(thr)); // see LAUNDER
@@ -614,7 +614,7 @@ __device__ __forceinline__ void train_spans(const uint32_t *__restrict__ X, cons
 #pragma unroll
                                     for (int k = 0; k < 4; ++k) tm[k] = (uint32_t)__builtin_amdgcn_sbfe((int)thr, 4 * t + k, 1);
                                     const PhiloxStart start = WPL > 1 ? philox_start(4u * lw + (uint32_t)t, STREAM_TYPE1, a.epoch, key) : t == 2 ? start2 : start3;
-                                    compare_nibble(draw_from(start, key, (uint32_t)g, (uint32_t)i, tm[0], tm[2]), tm, ge, eq);
+                                    ge = compare_nibble(draw_from(start, key, (uint32_t)g, (uint32_t)i, tm[0], tm[2]), tm, ge);
                                 }
                             }
                             return ge;
