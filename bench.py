@@ -102,10 +102,11 @@ def train_kernel_ops(counters, W, lits, entries, nominal=False, s=10.0):
     """Algorithmic lane-ops of a run of the training kernel from its event counters.
 
     nominal=False counts what the kernel's own algorithm needs on this run.  A block of 64
-    examples is evaluated only if its stored outputs could be outdated or a gate fired in it:
+    examples is evaluated only if its stored outputs could be outdated or a gate fired in it
+    (or, where outputs are taken span by span, so many outdated examples and fired gates):
     through the clause's literal list (one AND per literal and word of 32 examples, plus the
-    compare and refresh), or from its include masks, lane = example (1.5 operations per
-    non-zero mask word, plus refresh).  One gate draw per listed example whose error is
+    compare and refresh), or from its include masks (1.5 operations per
+    non-zero mask word and example, plus refresh).  One gate draw per listed example whose error is
     positive at the visit.  `lits`, `entries`: mean number of included literals and of non-zero
     feature words per clause, taken from the final state.
     nominal=True counts the method as literally read (every visited pair evaluated against all

@@ -129,7 +129,11 @@ int tm_bind_train(tm_handle *h, const uint32_t *X, const int32_t *y, int64_t q, 
  * launches (tm_train_chunk); an example whose error e is 0 under the tally as
  * it stands at the start of its launch (gate probability 0) is not visited for
  * feedback in that launch, all others are gated on the live tally, which a
- * clause reads in rounds of 64 such examples of its class, one round ahead.
+ * clause reads in rounds of 32 or 64 such examples of its class, at most 128 of
+ * them ahead of the visit.  Tally and previous-output bit of a visited example
+ * may be refreshed later in the launch, under the clause as it was at the visit:
+ * at the latest when the clause changes, after the round in which 2,048 examples
+ * have come to wait, or at the end of the launch.
  * Advances the handle's epoch counter (part of the random counter) by one. */
 int tm_fit_epoch(tm_handle *h, void *stream);
 
@@ -256,13 +260,15 @@ int tm_get_epoch(tm_handle *h, uint32_t *epoch);
  * number of examples of its launch that it walked for its clause), [1] fired gates, [2] Type I feedbacks,
  * [3] tally changes, [4] pairs whose class was trained for the example (gate
  * candidates), [5] Type II feedbacks given to a clause with output 1,
- * [6] blocks of 64 examples that a clause had to evaluate (blocks whose stored
- * outputs are known to be current and in which no gate fires are skipped),
+ * [6] blocks of 64 examples that a clause had to evaluate: whole blocks (those whose
+ * stored outputs are known to be current and in which no gate fires are skipped) or, where
+ * outputs are not taken block by block, a 64th of the examples whose outputs were taken,
+ * once for their refresh and once for a fired gate, rounded up per clause and launch,
  * [7] gate candidates whose error e was positive both at the start of the
  * launch and at the visit (a random draw was needed),
- * [8] those of the blocks of [6] that were evaluated 32 at a time through the
- * clause's literal list (outdated blocks of a sparse clause in which no gate
- * fired) rather than one by one from its include masks,
+ * [8] those of the blocks of [6] that were evaluated 32 examples at a time through the
+ * clause's literal list (outdated examples of a sparse clause) rather than from its
+ * include masks,
  * [9] (clause, launch) pairs for which the clause's automata were fetched and written
  * back (a clause that gets no feedback in a launch only reads its include masks).
  * Synchronises the stream. */

@@ -589,7 +589,8 @@ __device__ __forceinline__ void train_clause(const uint32_t *__restrict__ X, con
 
     // Which stored previous outputs o* can differ from the clause's current output: only
     // those not re-evaluated since the include mask last changed.  Kept per clause as two
-    // example ranges (multiples of 64), a prefix part [plo, phi) and a suffix [slo, qp); a
+    // example ranges, a prefix part [plo, phi) and a suffix [slo, qp), multiples of 64 where this form has left them and
+    // any examples where train_spans has, so that whoever reads them rounds outwards to whole blocks; a
     // block outside both needs no evaluation and no refresh unless one of its gates fires
     // (the result is the same as refreshing every visited pair: o != o* would be false).
     int plo, phi, slo;

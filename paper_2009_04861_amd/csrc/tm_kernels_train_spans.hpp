@@ -17,8 +17,11 @@ __host__ __device__ constexpr int span_lds_words(int wpl, bool team, bool deep)
                 : 64 + span_rows(wpl) * 32 * wpl + (deep ? train_draw_events(wpl) * wpl * 64 + 4 * DRAW_RING : 0);
 }
 
-// Most examples whose outputs wait for a change of the masks before they are taken anyway.  Their tallies wait as long:
-// 2,048 examples are one pass of a sweep.
+// Outputs that wait for a change of the masks are taken anyway once so many examples wait at the end of a round of gate entries (2,048 are one
+// pass of a sweep); their tallies wait as long.  A round covers as many examples as its entries are apart - with 64 of ten classes' entries
+// 320 where every gate is open, thousands where few are -, so up to that many more may wait.  Looking before every event
+// instead holds live training back (10 x 400 clauses of 784 features, T = 20: epoch 0.38 ms, with a bound of 512 examples 0.46, of 64
+// 0.64) and it learns no better for it (test accuracy 0.98, 0.98 and 0.90).
 constexpr int SPAN_MOST = 2048;
 
 // One wavefront = one clause of class c, as train_clause below, but no block of examples is ever opened.  The rows of the fired
@@ -26,7 +29,7 @@ constexpr int SPAN_MOST = 2048;
 // included literals that are 0 in it cost one operation per slot and a ballot, for eight rows side by side, so that Type II events
 // of a clause whose output is 0 (nearly all of them) are dropped before the loop over the events.  The outputs of all
 // examples since the last change of the masks (`pend`) are taken when the masks change next, at the end of the launch, or when SPAN_MOST
-// of them wait: one walk of the literal list over the rows of XB, lane = word of 32 examples.  Masks change at 2 to 3 % of
+// of them wait after a round: one walk of the literal list over the rows of XB, lane = word of 32 examples.  Masks change at 2 to 3 % of
 // the feedback events of an image-like machine with every gate open: 60 to 90 walks of 18 literals take the place of 1,000
 // evaluations of blocks of 64 examples, which were a sixth of the vector instructions of such a pass.
 // What bounds it is vector issue (0.85 of the peak rate).  20,000 clauses of 784 features, 60,000 examples, s = 10: vector
@@ -658,7 +661,8 @@ __device__ __forceinline__ void train_spans(const uint32_t *__restrict__ X, cons
     }
     for (int sh = 32; sh > 0; sh >>= 1) n_changes_v += __shfl_xor(n_changes_v, sh, 64);
     n_changes += n_changes_v;
-    store_counters(a, g, lane, (n_listed_blocks + 63) >> 6, n_fired, n_type1, n_changes, n_type2, (n_eval + 63) >> 6, n_draw, !LAZY || have_planes);
+    // outputs taken: those of spans, and one per fired gate from its row
+    store_counters(a, g, lane, (n_listed_blocks + 63) >> 6, n_fired, n_type1, n_changes, n_type2, (n_eval + n_fired + 63) >> 6, n_draw, !LAZY || have_planes);
 }
 
 } // namespace tsetlin

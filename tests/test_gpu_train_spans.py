@@ -81,3 +81,27 @@ def test_long_and_short_passes_of_narrow_clauses(m, n, o, N, s, device):
         assert np.array_equal(gpu_state_as_oracle(gpu), ora.state), ep
         assert np.array_equal(gpu.tallies().cpu().numpy(), tally), ep
         assert np.array_equal(bits_to_u8(gpu.prev_outputs(), q), ostar), ep
+
+
+def test_outputs_of_fired_gates_are_counted_where_no_span_is_swept(device):
+    """A pass in which no mask changes: the only outputs taken are those of the examples whose gates fire."""
+    m, n, o, T, q = 2, 6, 784, 3, 1700
+    rng = np.random.default_rng(4)
+    ora, gpu = make_pair(m, n, o, 128, T, 10.0, 79)
+    X = (rng.random((q, o)) < 0.3).astype(np.uint8)
+    y = rng.integers(0, m, size=q).astype(np.int32)
+    gpu.bind_train(dev_bits(gpu, X), dev_i32(gpu, y))
+    ora.state[:] = 1                                           # empty clauses, far from including anything
+    push_state(gpu, ora.state)
+    gpu.sync_tallies()
+    tally, ostar = ora.sync_tallies(X)
+    snap = np.full((q, m), -T, dtype=np.int32)                 # closes every gate but those of 60 examples
+    snap[np.arange(q), y] = T
+    snap[::29] = 0
+    gpu.counters()
+    gpu.feedback_step(dev_i32(gpu, snap), 0, q)
+    fired = ora.feedback_step(X, y, snap, tally, ostar, 0, 0, q)
+    assert np.array_equal(gpu_state_as_oracle(gpu), ora.state)
+    c = gpu.counters()
+    assert c["fired"] == fired > 100 and c["blocks_listed"] == 0 and c["tally_changes"] == 0
+    assert fired / 64 <= c["blocks_evaluated"] <= ora.C
