@@ -165,7 +165,9 @@ __device__ __forceinline__ uint64_t eval64(const uint32_t *eoff, const uint2 *em
 //   6 to 10 slots: 1.15 with 500 to 1,000 clauses, 0.85 to 0.97 with many
 //   12 to 20 slots: one loop; two would not leave room for two wavefronts
 // train_min_waves: the wavefronts per SIMD that a form is held to.  DEEP, time without the bound divided by time with
-// it: 1 slot (4 wavefronts instead of 5), 20,000 clauses 1.05; 10 slots (2 instead of 3) 1.25.
+// it: 1 slot (4 wavefronts instead of 5), 20,000 clauses 1.05; 10 slots (2 instead of 3) 1.25.  With spans the bound costs one slot twelve
+// spilled registers (32 bytes of scratch per lane) and still pays: four wavefronts without any, 8,000 to 40,000 clauses of 300 and 784
+// features 1.05 to 1.09, up to 4,000 clauses 0.99 to 1.0.
 __host__ __device__ constexpr bool train_split(int wpl, bool roomy, bool deep) { return (roomy && (wpl != 2 || deep)) || wpl == 4 || (!deep && (wpl == 1 || wpl == 3)); }
 __host__ __device__ constexpr int train_min_waves(int wpl, bool roomy) { return roomy ? 1 : wpl <= 2 ? 5 : wpl <= 6 ? 4 : wpl <= 10 ? 3 : 2; }
 

@@ -44,7 +44,8 @@ void launch_train_form(const TrainPtrs &p, TrainArgs a, bool full, hipStream_t s
     }
     // Clauses per workgroup: one of several wavefronts (team), else one per wavefront, and these do not interact.  A workgroup's
     // slots are handed on only when its slowest clause is done, so one is best once every SIMD holds several wavefronts (speed against
-    // two: 16,384 clauses of 20,000 features 1.12, 20,000 of 10,000 features 1.06, 20,000 of 784 features 1.02), and two
+    // two: 3,000 to 20,000 clauses of 20,000 features 1.09 to 1.2, of 10,000 features 1.0 to 1.06; 3,000 and 8,000 of 300 to 784 features 1.15 and
+    // 1.09, 20,000 of them 1.0), and two
     // where clauses have few gate entries to work through and few slots (20,000 clauses of 300 to 784 features, 200 entries: one 0.98 of
     // two).  With about one clause per SIMD four are better: they land on the four SIMDs of a CU, while two workgroups of two may share a
     // pair of SIMDs (1,000 clauses: 4.0 ms per epoch against 5.0 ms).  Live passes that swing hold two: neighbours, one of either polarity,
