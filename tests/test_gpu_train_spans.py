@@ -105,3 +105,28 @@ def test_outputs_of_fired_gates_are_counted_where_no_span_is_swept(device):
     c = gpu.counters()
     assert c["fired"] == fired > 100 and c["blocks_listed"] == 0 and c["tally_changes"] == 0
     assert fired / 64 <= c["blocks_evaluated"] <= ora.C
+
+
+# one machine, passes long enough for spans and short ones that open blocks: either form reads what the other has left of the ranges
+# of outdated outputs, whose ends spans put anywhere and blocks at multiples of 64
+@pytest.mark.parametrize("m,n,o,N,s", [(2, 6, 300, 100, 3.9), (2, 6, 784, 128, 1.0), (2, 6, 1100, 128, 10.0), (2, 6, 2100, 128, 2.0), (2, 6, 2500, 20, 5.0)])
+def test_passes_by_span_and_by_block_alternate(m, n, o, N, s, device):
+    print(m, n, o, N, s, flush=True)
+    rng = np.random.default_rng(o)
+    q, T = 3200, 3
+    ora, gpu = make_pair(m, n, o, N, T, s, 80)
+    X = (rng.random((q, o)) < 0.2).astype(np.uint8)
+    y = rng.integers(0, m, size=q).astype(np.int32)
+    gpu.bind_train(dev_bits(gpu, X), dev_i32(gpu, y))
+    ora.state[:] = sparse_random_state(rng, ora.C, ora.L, N, 2.5 / o)
+    push_state(gpu, ora.state)
+    gpu.sync_tallies()
+    tally, ostar = ora.sync_tallies(X)
+    for ep, (i0, cnt) in enumerate([(0, q), (1001, 333), (0, q), (2500, 64), (40, q - 45), (7, 250), (3000, 200), (0, q)]):
+        snap = rng.integers(-T, T + 1, size=(q, m)).astype(np.int32)
+        B.tm_set_epoch(gpu.h, ep)
+        gpu.feedback_step(dev_i32(gpu, snap), i0, cnt)
+        ora.feedback_step(X, y, snap, tally, ostar, ep, i0, cnt)
+        assert np.array_equal(gpu_state_as_oracle(gpu), ora.state), ep
+        assert np.array_equal(gpu.tallies().cpu().numpy(), tally), ep
+        assert np.array_equal(bits_to_u8(gpu.prev_outputs(), q), ostar), ep
