@@ -165,9 +165,9 @@ __device__ __forceinline__ uint64_t eval64(const uint32_t *eoff, const uint2 *em
 //   6 to 10 slots: 1.15 with 500 to 1,000 clauses, 0.85 to 0.97 with many
 //   12 to 20 slots: one loop; two would not leave room for two wavefronts
 // train_min_waves: the wavefronts per SIMD that a form is held to.  DEEP, time without the bound divided by time with
-// it: 1 slot (4 wavefronts instead of 5), 20,000 clauses 1.05; 10 slots (2 instead of 3) 1.25.  With spans the bound costs one slot twelve
-// spilled registers (32 bytes of scratch per lane) and still pays: four wavefronts without any, 8,000 to 40,000 clauses of 300 and 784
-// features 1.05 to 1.09, up to 4,000 clauses 0.99 to 1.0.
+// it: 1 slot (4 wavefronts instead of 5), 20,000 clauses 1.05; 10 slots (2 instead of 3) 1.25.  With spans the bound costs one slot
+// spilled registers (12 when this was measured, now 17: 40 bytes of scratch per lane) and still pays: four wavefronts without any, 8,000 to 40,000
+// clauses of 300 and 784 features 1.05 to 1.09, up to 4,000 clauses 0.99 to 1.0.
 __host__ __device__ constexpr bool train_split(int wpl, bool roomy, bool deep) { return (roomy && (wpl != 2 || deep)) || wpl == 4 || (!deep && (wpl == 1 || wpl == 3)); }
 __host__ __device__ constexpr int train_min_waves(int wpl, bool roomy) { return roomy ? 1 : wpl <= 2 ? 5 : wpl <= 6 ? 4 : wpl <= 10 ? 3 : 2; }
 
@@ -256,10 +256,11 @@ constexpr int DRAW_RING = 128; // words of literals waiting for their last two b
 // They meet at one barrier per round; what is handed over lies in LDS twice.
 // Four wavefronts with train_spans, two with train_clause.
 __host__ __device__ constexpr bool train_team(int wpl, bool roomy, bool deep, bool narrow) { return wpl == 1 && roomy && deep && !narrow; }
-// Forms that come with train_spans as well, for classification.  Spans gain where masks change seldom and lose where they change at every
-// second event, as on bag-of-words data: speed with against without, 60 to 20,000 clauses with s = 2 and 10, noisy images / bags of words: one
-// slot, teams 1.5 to 2.0 / 0.96 to 1.15, wavefronts 1.15 to 1.5 / 0.85 to 1.15; two slots, DEEP and few clauses 1.18 / 0.88, DEEP and many 0.88
-// to 0.92 (images), not DEEP 1.04 to 1.11 / 0.77 to 0.84 (without); three slots 1.15 to 1.5 / 0.74 to 1.05.
+// Forms that come with train_spans as well, for classification.  Spans gain most where masks change seldom; where they change at every second
+// event, as on bag-of-words data, spans are short and taken row by row.  Speed with against without, first eight epochs of 60 to 20,000 clauses with
+// s = 2 to 10, noisy images / bags of words: one slot, teams 1.6 to 1.8 / 1.2, wavefronts DEEP 1.3 / 1.05, not DEEP 1.1 / 0.86 to 0.9 (1.2 settled);
+// two slots, DEEP and few clauses 1.08 / 0.97; three slots 1.16 to 1.27 / 0.97 to 1.15.  Two slots, DEEP and many clauses 0.88 to 0.92 on images,
+// not DEEP 1.04 to 1.11 / 0.77 to 0.84 (measured when a block was evaluated for every short span): without.
 __host__ __device__ constexpr bool train_has_spans(int wpl, bool roomy, bool deep, bool narrow)
 {
     return wpl <= 3 && !narrow && (wpl != 2 || (deep && roomy));

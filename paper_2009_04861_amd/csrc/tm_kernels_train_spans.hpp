@@ -23,13 +23,22 @@ __host__ __device__ constexpr int span_lds_words(int wpl, bool team, bool deep)
 // instead holds live training back (10 x 400 clauses of 784 features, T = 20: epoch 0.38 ms, with a bound of 512 examples 0.46, of 64
 // 0.64) and it learns no better for it (test accuracy 0.98, 0.98 and 0.90).
 constexpr int SPAN_MOST = 2048;
+// Most examples of a span that are taken row by row.  Where masks change at every second event, as young machines' and those of bags of words
+// do, a span is a handful of examples, and a list of literals or entries for a block of 64 is not worth making for it: the rows come eight
+// (four) at a time, and a row costs what a row in LDS does.  First epoch and sum of the first eight, a block for every span / row by row: 2 x 400
+// clauses of 1,000 bag-of-words features, s = 5 2.14, 12.4 / 1.54, 9.4 ms; 2 x 8,000, s = 2 7.5, 35.8 / 6.4, 31.6; 2 x 200 of 1,500 5.5, 34.7 /
+// 4.5, 29.7; 2 x 6,000 of 3,000, s = 5 9.6, 75.0 / 8.2, 59.9; machines of noisy images 0.99 to 1.03 of the time.  24 instead of 16: the same
+// within 2 %.  The other way, a clause whose masks change often taken block by block by the same
+// kernel, costs settled machines up to 3 % with one slot and 19 % with three (scalar registers).
+constexpr int SPAN_DIRECT = 16;
 
 // One wavefront = one clause of class c, as train_clause below, but no block of examples is ever opened.  The rows of the fired
 // examples of a round go into LDS a handful at a time, and the output that an example's feedback needs comes from there: the
 // included literals that are 0 in it cost one operation per slot and a ballot, for eight rows side by side, so that Type II events
 // of a clause whose output is 0 (nearly all of them) are dropped before the loop over the events.  The outputs of all
 // examples since the last change of the masks (`pend`) are taken when the masks change next, at the end of the launch, or when SPAN_MOST
-// of them wait after a round: one walk of the literal list over the rows of XB, lane = word of 32 examples.  Masks change at 2 to 3 % of
+// of them wait after a round: one walk of the literal list over the rows of XB, lane = word of 32 examples, or up to SPAN_DIRECT of them from their
+// rows.  Masks change at 2 to 3 % of
 // the feedback events of an image-like machine with every gate open: 60 to 90 walks of 18 literals take the place of 1,000
 // evaluations of blocks of 64 examples, which were a sixth of the vector instructions of such a pass.
 // What bounds it is vector issue (0.85 of the peak rate).  20,000 clauses of 784 features, 60,000 examples, s = 10: vector
@@ -270,6 +279,12 @@ __device__ __forceinline__ void train_spans(const uint32_t *__restrict__ X, cons
         neg[r] = PAIRED ? ((r & 1) ? ~0u : 0u) : lw >= d.Wf ? ~0u : 0u;
         valid[r] = Map::held(r, lane, d.Wf) ? (fw == d.Wf - 1 ? d.tailmask : ~0u) : 0u;
     }
+    uint32_t row_at[NX]; // where a lane finds its words in a row: the feature words of its literal words
+#pragma unroll
+    for (int r = 0; r < NX; ++r) {
+        const int slot = PAIRED ? 2 * r : r, lw = Map::word(slot, lane, d.Wf);
+        row_at[r] = Map::held(slot, lane, d.Wf) ? (uint32_t)(lw >= d.Wf ? lw - d.Wf : lw) : 0u;
+    }
     // ---- outputs, tallies and stored outputs of a span of examples ----
     // Stored outputs that may differ from the clause's present ones lie in [plo, phi) and [slo, q); everything else needs neither
     // evaluation nor refresh (o = o* there).
@@ -362,6 +377,51 @@ __device__ __forceinline__ void train_spans(const uint32_t *__restrict__ X, cons
             }
         }
     };
+    // Examples [lo, hi), at most SPAN_DIRECT, from their rows, a few of them in flight at a time.
+    auto direct = [&](int lo, int hi, const uint32_t (&m7)[WPL]) {
+        constexpr int GROUP = NX == 1 ? 8 : 4;
+        const int w = lo >> 5, w_last = (hi - 1) >> 5;
+        const uint32_t o0 = ostar_row[w], o1 = ostar_row[w_last];
+        uint32_t out = 0u; // bit k: output on example lo + k
+        uint32_t in_row[NX];
+        int ln = lane;
+        if (WPL > 1) asm volatile("" : "+v"(ln)); // addresses are formed here, not kept for every slot; with one slot they are (1.03 of the speed)
+#pragma unroll
+        for (int r = 0; r < NX; ++r) {
+            in_row[r] = row_at[r] * 4u;
+            if (WPL > 1) asm volatile("" : "+v"(in_row[r]));
+        }
+#pragma unroll 1
+        for (int i = lo; i < hi; i += GROUP) {
+            uint32_t x[GROUP][NX], bits = 0u;
+#pragma unroll
+            for (int u = 0; u < GROUP; ++u) { // past the end: the last one again, which counts no more below
+                const char *row = reinterpret_cast<const char *>(X + (int64_t)min(i + u, hi - 1) * d.Wf);
+#pragma unroll
+                for (int r = 0; r < NX; ++r) x[u][r] = *reinterpret_cast<const uint32_t *>(row + in_row[r]);
+            }
+#pragma unroll
+            for (int u = 0; u < GROUP; ++u) {
+                uint32_t viol = 0u;
+#pragma unroll
+                for (int r = 0; r < NX; ++r) viol |= PAIRED ? bitselect(x[u][r], m7[PAIRED ? 2 * r + 1 : 0], m7[PAIRED ? 2 * r : 0]) : m7[r] & ~(x[u][r] ^ neg[r]);
+                bits |= ballot(viol != 0u) == 0 ? 1u << u : 0u;
+            }
+            out |= bits << (i - lo);
+        }
+        const uint64_t os = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)o0) |
+                            ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)o1) << 32); // o1 counts where there are two words
+        const uint32_t diff = ((uint32_t)(os >> (lo & 31)) ^ out) & ((1u << (hi - lo)) - 1u);
+        if (diff) {
+            if (ln < 32 && ((diff >> ln) & 1u)) atomicAdd(&a.tally[(int64_t)c * a.qp + lo + ln], ((out >> ln) & 1u) ? sign : -sign);
+            const uint64_t nw = os ^ ((uint64_t)diff << (lo & 31));
+            if (ln == 0) {
+                ostar_row[w] = (uint32_t)nw;
+                if (w_last > w) ostar_row[w_last] = (uint32_t)(nw >> 32);
+            }
+            n_changes += (uint32_t)__builtin_popcount(diff);
+        }
+    };
     // Refresh (last lines of Algorithm 1) of the examples [from, to) under the masks m7, and the note that they are current.
     auto refresh = [&](int from, int to, const uint32_t (&m7)[WPL]) {
         if (from >= to) return;
@@ -371,7 +431,11 @@ __device__ __forceinline__ void train_spans(const uint32_t *__restrict__ X, cons
             e1 = max(s1, min(to, phi));
         }
         int s2 = max(max(from, slo), e1);
-        if (s1 < e1 || s2 < to) {
+        if ((s1 < e1 || s2 < to) && have == NOTHING && to - from <= SPAN_DIRECT) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); // as below
+            n_eval += (uint32_t)(to - from);
+            direct(from, to, m7);
+        } else if (s1 < e1 || s2 < to) {
             // One block is evaluated from entries: building the list costs as much as that does.
             const bool brief = ((to + 63) >> 6) - (from >> 6) <= 1;
             if (have == NOTHING || (have == ENTRIES && !brief)) {
@@ -457,12 +521,6 @@ __device__ __forceinline__ void train_spans(const uint32_t *__restrict__ X, cons
         v_cur = load_v(ent_cur);
         ent_nxt = load_ent(64 + lane);
     }
-    uint32_t row_at[NX]; // where a lane finds its words in a row: the feature words of its literal words
-#pragma unroll
-    for (int r = 0; r < NX; ++r) {
-        const int slot = PAIRED ? 2 * r : r, lw = Map::word(slot, lane, d.Wf);
-        row_at[r] = Map::held(slot, lane, d.Wf) ? (uint32_t)(lw >= d.Wf ? lw - d.Wf : lw) : 0u;
-    }
     for (int k0 = 0;; k0 += ROUND) {
         const bool last = k0 >= k_hi;
         int end = i_end;     // outputs may wait beyond this example of the range
@@ -502,7 +560,7 @@ __device__ __forceinline__ void train_spans(const uint32_t *__restrict__ X, cons
         int n_ahead = 0, n_used = 0; // events drawn ahead, those of them used
         int at = 0, from = 0, to = 0; // next event; those whose rows are in LDS
         uint32_t act = 0u, outs = 0u; // of these, beginning with the from-th: to be worked on; the clause's outputs
-        bool known = false;           // ... with the present masks
+        bool wide = true;             // the masks may hold for a while: outputs on all of these at once
         for (;;) {
             uint32_t flip[WPL] = {};
             bool moved = false;
@@ -512,7 +570,6 @@ __device__ __forceinline__ void train_spans(const uint32_t *__restrict__ X, cons
                 if (at == to) { // the rows of the next fired examples into LDS
                     from = at;
                     to = TEAM ? nf : min(at + STAGED, nf);
-                    known = false;
                     if constexpr (!TEAM && WPL == 1) { // two rows a load
                         const int half = lane >> 5, word = lane & 31;
                         uint32_t x[STAGED / 2];
@@ -548,29 +605,28 @@ __device__ __forceinline__ void train_spans(const uint32_t *__restrict__ X, cons
                         wave_lds_sync();
                     }
                 }
-                if (!known) { // outputs of the clause on the events to come, the state before each of them being the present one
-                    known = true;
-                    outs = 0u;
-                    const int n = to - from;
-                    for (int j = (at - from) & ~7; j < n; j += 8) {
-                        uint32_t viol[8];
+                // outputs of the clause on the events to come, the state before each of them being the present one: all of those in LDS, or
+                // after a change, which another may follow soon, the next eight at most
+                const int first = (at - from) & ~7, n = wide ? to - from : min(to - from, first + 8);
+                outs = 0u;
+                for (int j = first; j < n; j += 8) {
+                    uint32_t viol[8];
 #pragma unroll
-                        for (int u = 0; u < 8; ++u) {
-                            viol[u] = 0u;
+                    for (int u = 0; u < 8; ++u) {
+                        viol[u] = 0u;
 #pragma unroll
-                            for (int r = 0; r < NX; ++r) {
-                                const uint32_t x = rows_now[(j + u) * PITCH + row_at[r]];
-                                viol[u] |= PAIRED ? bitselect(x, p[PAIRED ? 2 * r + 1 : 0][7], p[PAIRED ? 2 * r : 0][7]) : p[r][7] & ~(x ^ neg[r]);
-                            }
+                        for (int r = 0; r < NX; ++r) {
+                            const uint32_t x = rows_now[(j + u) * PITCH + row_at[r]];
+                            viol[u] |= PAIRED ? bitselect(x, p[PAIRED ? 2 * r + 1 : 0][7], p[PAIRED ? 2 * r : 0][7]) : p[r][7] & ~(x ^ neg[r]);
                         }
-                        uint32_t byte = 0u;
-#pragma unroll
-                        for (int u = 0; u < 8; ++u) byte |= ballot(viol[u] != 0u) == 0 ? 1u << u : 0u;
-                        outs |= byte << j;
                     }
-                    // Type II feedback to a clause whose output is 0 changes nothing (Table 2)
-                    act = ((uint32_t)(t1mask >> from) | outs) & (n < 32 ? (1u << n) - 1u : ~0u) & ~((1u << (at - from)) - 1u);
+                    uint32_t byte = 0u;
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) byte |= ballot(viol[u] != 0u) == 0 ? 1u << u : 0u;
+                    outs |= byte << j;
                 }
+                // Type II feedback to a clause whose output is 0 changes nothing (Table 2)
+                act = ((uint32_t)(t1mask >> from) | outs) & (n < 32 ? (1u << n) - 1u : ~0u) & ~((1u << (at - from)) - 1u);
                 uint32_t xnext[NX], genext = 0u; // of the next event: words, and where they are there (TEAM) the draws of the next Type I event
                 int j = act ? __builtin_ctz(act) : 0;
 #pragma unroll
@@ -627,7 +683,8 @@ __device__ __forceinline__ void train_spans(const uint32_t *__restrict__ X, cons
                     if (moved) break;
                 }
                 if (moved) break;
-                at = to;
+                at = from + n;
+                wide = true;
             }
             if (!moved) upto = last ? i_end : end - pend >= SPAN_MOST ? end & ~31 : pend;
             uint32_t m7[WPL]; // the masks those examples were visited with
@@ -639,7 +696,7 @@ __device__ __forceinline__ void train_spans(const uint32_t *__restrict__ X, cons
             plo = 0; // the conjunction changed: whatever was visited before is outdated, and so is all that comes
             phi = slo = upto;
             have = NOTHING;
-            known = false;
+            wide = TEAM; // eight at a time costs a team 2 % on noisy images (1,000 clauses of 784 features) and gains 3 % on bags of words
         }
         if (last) break;
     }

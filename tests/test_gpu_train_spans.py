@@ -3,6 +3,7 @@ in launches of many gate entries, with a wavefront or a team of them per clause.
 small machines and on sampled clauses of machines that fill the GPU."""
 import numpy as np
 import pytest
+import torch
 
 from paper_2009_04861_amd import binding as B
 from tests.helpers import bits_to_u8, dev_bits, dev_i32, gpu_state_as_oracle, make_pair, push_state, sparse_random_state
@@ -130,3 +131,69 @@ def test_passes_by_span_and_by_block_alternate(m, n, o, N, s, device):
         assert np.array_equal(gpu_state_as_oracle(gpu), ora.state), ep
         assert np.array_equal(gpu.tallies().cpu().numpy(), tally), ep
         assert np.array_equal(bits_to_u8(gpu.prev_outputs(), q), ostar), ep
+
+
+# clauses whose masks change at every other event, so that spans are short, inside a word of stored outputs and across two, beside clauses at rest;
+# young automata (half of all literals) and sparse ones.  Forms: team, one slot beyond a SIMD per clause (with draws made ahead and without), two
+# slots, three with few and many clauses
+@pytest.mark.parametrize("m,n,o,N,s", [(2, 6, 784, 128, 5.0), (2, 520, 300, 128, 10.0), (2, 520, 300, 100, 2.0), (2, 6, 500, 128, 1.0),
+                                       (2, 6, 1100, 128, 10.0), (2, 6, 2500, 128, 2.0), (2, 520, 2100, 128, 3.9), (5, 6, 784, 128, 5.0)])
+def test_short_spans(m, n, o, N, s, device):
+    print(m, n, o, N, s, flush=True)
+    rng = np.random.default_rng(o + n)
+    q, T = 3200 if m == 2 else 4800, max(4, n // 2)
+    ora, gpu = make_pair(m, n, o, N, T, s, 81)
+    X = (rng.random((q, o)) < 0.1).astype(np.uint8)
+    y = rng.integers(0, m, size=q).astype(np.int32)
+    gpu.bind_train(dev_bits(gpu, X), dev_i32(gpu, y))
+    ids = np.unique(np.r_[0:6, rng.choice(ora.C, size=min(ora.C, 12), replace=False)]).astype(np.int32)
+    for again in range(2):
+        if again:
+            ora.state[:] = sparse_random_state(rng, ora.C, ora.L, N, 2.5 / o)
+        ora.state[1] = 1                                       # far from any change
+        ora.state[4] = 1
+        push_state(gpu, ora.state)
+        gpu.sync_tallies()
+        ostar = ora.clause_outputs_subset(X, ids)
+        for ep, (i0, cnt) in enumerate([(0, q), (0, q), (11, q - 30), (0, 900), (0, q)]):
+            snap = rng.integers(-T, T + 1, size=(q, m)).astype(np.int32)
+            B.tm_set_epoch(gpu.h, ep)
+            gpu.feedback_step(dev_i32(gpu, snap), i0, cnt)
+            assert ora.feedback_step_subset(X, y, snap, ostar, ep, i0, cnt, ids) > 0
+            assert np.array_equal(gpu_state_as_oracle(gpu)[ids], ora.state[ids]), (again, ep)
+            prev = bits_to_u8(gpu.prev_outputs(), q)
+            assert np.array_equal(prev[ids], ostar), (again, ep)
+            sign = np.where(np.arange(ora.C) % n % 2 == 1, 1, -1)
+            want = np.stack([sign[c * n:(c + 1) * n] @ prev[c * n:(c + 1) * n].astype(np.int64) for c in range(m)], 1)
+            assert np.array_equal(gpu.tallies().cpu().numpy(), want), (again, ep)
+            if ep == 1:
+                gpu.sync_tallies()
+                ostar = ora.clause_outputs_subset(X, ids)
+
+
+# First epochs, in which masks change at every other event: one launch, long enough for spans, against three that are not (1.21 times as
+# long; 1.36 with a block evaluated for every span).
+def test_a_long_launch_of_young_clauses_is_about_as_fast_as_short_ones(device):
+    n, o, s = 8000, 1000, 2.0
+    q, best = 3000, {}
+    rng = np.random.default_rng(7)
+    X = (rng.random((q, o)) < 0.06).astype(np.uint8)
+    y = rng.integers(0, 2, size=q).astype(np.int32)
+    snap = rng.integers(-n // 2, n // 2, size=(q, 2)).astype(np.int32)
+    gpu = B.TsetlinMachine(2, n, o, 128, (4 * n) // 5, s, 5)
+    gpu.bind_train(dev_bits(gpu, X), dev_i32(gpu, y))
+    young, snap = gpu.get_ta_state(), dev_i32(gpu, snap)
+    for attempt in range(4):
+        for pieces in (1, 3):
+            gpu.set_ta_state(young)
+            gpu.sync_tallies()
+            B.tm_set_epoch(gpu.h, 0)
+            begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            begin.record()
+            for k in range(pieces):
+                gpu.feedback_step(snap, k * q // pieces, q // pieces)
+            end.record()
+            torch.cuda.synchronize()
+            best[pieces] = min(best.get(pieces, 1e9), begin.elapsed_time(end))
+            print(n, o, pieces, best[pieces], flush=True)
+    assert best[1] < 1.3 * best[3], best
