@@ -385,11 +385,14 @@ __device__ __forceinline__ void train_spans(const uint32_t *__restrict__ X, cons
         uint32_t out = 0u; // bit k: output on example lo + k
         uint32_t in_row[NX];
         int ln = lane;
-        if (WPL > 1) asm volatile("" : "+v"(ln)); // addresses are formed here, not kept for every slot; with one slot they are (1.03 of the speed)
+        // Addresses are formed here, not kept for every slot.  They are where registers are left (three slots, roomy, DEEP: 1.03 of the speed), and
+        // with one slot, where it makes 1.03 as well.
+        constexpr bool FORMED = WPL == 2 || (WPL == 3 && !(ROOMY && DEEP));
+        if (FORMED) asm volatile("" : "+v"(ln));
 #pragma unroll
         for (int r = 0; r < NX; ++r) {
             in_row[r] = row_at[r] * 4u;
-            if (WPL > 1) asm volatile("" : "+v"(in_row[r]));
+            if (FORMED) asm volatile("" : "+v"(in_row[r]));
         }
 #pragma unroll 1
         for (int i = lo; i < hi; i += GROUP) {
@@ -606,8 +609,9 @@ __device__ __forceinline__ void train_spans(const uint32_t *__restrict__ X, cons
                     }
                 }
                 // outputs of the clause on the events to come, the state before each of them being the present one: all of those in LDS, or
-                // after a change, which another may follow soon, the next eight at most
-                const int first = (at - from) & ~7, n = wide ? to - from : min(to - from, first + 8);
+                // after a change, which another may follow soon, the next eight at most (with two and three slots there are no more; with two the
+                // compiler makes 3 % faster code if it is not told)
+                const int first = (at - from) & ~7, n = wide || WPL == 3 ? to - from : min(to - from, first + 8);
                 outs = 0u;
                 for (int j = first; j < n; j += 8) {
                     uint32_t viol[8];
